@@ -1202,7 +1202,8 @@ SFOC_DEV void direct_item(const MatchArgs& A, int i, char* lds, double* red) {
         // channel rather than hoisted out of the loop and kept live)
         const int tl = tid_local(), ln = tl & 63, wl = __builtin_amdgcn_readfirstlane(tl >> 6);
         const uint16_t* rp = refp + h * plane_r + (int64_t)wl * A.Wr;   // wave-uniform bases
-        const uint16_t* sp = senp + h * plane_s + (int64_t)wl * A.Ws;
+        const int wt = min(wl, m - 1);   // (m = 3: the fourth wave has no template row of its own)
+        const uint16_t* sp = senp + h * plane_s + (int64_t)wt * A.Ws;
 #pragma unroll
         for (int c = 0; c < KC; ++c) {
             const uint32_t x = (uint32_t)min(ln + 64 * c, M - 1);
@@ -1212,7 +1213,7 @@ SFOC_DEV void direct_item(const MatchArgs& A, int i, char* lds, double* red) {
         }
         const uint32_t xt = (uint32_t)min(ln, m - 1);
 #pragma unroll
-        for (int j = 0; j < KT; ++j) tv[j] = sp[(uint32_t)(min(wl + 4 * j, m - 1) - wl) * (uint32_t)A.Ws + xt];
+        for (int j = 0; j < KT; ++j) tv[j] = sp[(uint32_t)(min(wl + 4 * j, m - 1) - wt) * (uint32_t)A.Ws + xt];
     };
     auto store = [&]() {
         const int tl = tid_local(), ln = tl & 63, wl = __builtin_amdgcn_readfirstlane(tl >> 6);

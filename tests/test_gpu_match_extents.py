@@ -1,0 +1,38 @@
+"""Fast-NCC surfaces at the extents where the match kernels change form."""
+import numpy as np
+import pytest
+
+from oracle import sfoc_oracle as O
+from paper_2202_13347_amd import sfoc as S
+from paper_2202_13347_amd import synth
+from tests.gpu_util import compare_cps, to_chw
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+
+
+def check_surface(m, r, dt):
+    """Surfaces and records of windows that touch the image borders against
+    the oracle on the same (rounded) descriptors, integral images per window."""
+    print("extents", m, r, dt, flush=True)
+    size = m + 2 * r + 9
+    pr = synth.make_pair(500 + m + r, size, min(6.0, max(0.5, r - 2.0)))
+    lo, hi = m // 2 + r, size - (m - m // 2) - r
+    ips = np.array([[lo, lo], [hi, hi], [(lo + hi) // 2, hi], [hi, lo]], np.int32)   # windows on the borders
+    Fs, Fr = (torch.from_numpy(np.ascontiguousarray(to_chw(O.sfoc(x)), np.float32)).to(DTYPES[dt])
+              for x in (pr.sen, pr.ref))
+    o, so = O.match(Fs.double().numpy().transpose(1, 2, 0), Fr.double().numpy().transpose(1, 2, 0), ips, m, r,
+                    want_surfaces=True)
+    cps, ncc = S.fastncc_match(Fs.cuda(), Fr.cuda(), None, None, torch.from_numpy(ips).cuda(), m, r, want_ncc=True)
+    torch.cuda.synchronize()
+    st = compare_cps(S.cps_to_numpy(cps), o, so, r, ncc.cpu().numpy(), check_consistency=False)
+    assert st["compared"] > 0
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("m", [3, 4, 5])
+def test_direct_form_smallest_templates(m, dt):
+    """The direct form deals template rows to four waves; a template of three
+    rows leaves the fourth none."""
+    check_surface(m, 2, dt)
