@@ -24,6 +24,8 @@
 // while the template is read.  NCC (Eq. 9) is assembled with the variance
 // subtraction in float64, then the argmax, the parabola refinement and the
 // per-CP flags are written.
+#include <type_traits>
+
 #include "sfoc_dev.h"
 #include "sfoc_launch.h"
 #include "sfoc_trace.h"
@@ -45,10 +47,31 @@ SFOC_DEV int tid_local() {
     return t;
 }
 
-SFOC_DEV float2 cmul(float2 a, float2 b) { return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
-SFOC_DEV float2 cmulc(float2 a, float2 b) {  // a * conj(b)
-    return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+// Complex products.  Each part is a sum of two products of which one is
+// rounded before the fused multiply-add; which one is spelled out here and in
+// the tables of the DFT codelets below instead of being left to the compiler.
+// So every kernel built from these pieces rounds alike (the pair call, its
+// split form, the plan's kernels), and a change of the code around them does
+// not move a result: the choices are those of the records the library has
+// given so far, kept bit for bit.
+//   form & 2: the real part fuses the imaginary product, form & 1: the
+//   imaginary part fuses a.x * b.y.
+SFOC_DEV float2 cmulf(float2 a, float2 b, int form) {
+    const float re = form & 2 ? fmaf(a.y, -b.y, a.x * b.x) : fmaf(a.x, b.x, -(a.y * b.y));
+    const float im = form & 1 ? fmaf(a.x, b.y, a.y * b.x) : fmaf(a.y, b.x, a.x * b.y);
+    return make_float2(re, im);
 }
+// Twiddle products: row passes, forward column pass, inverse passes (a * conj(w)).
+SFOC_DEV float2 cmul_row(float2 a, float2 w) { return cmulf(a, w, 0); }
+SFOC_DEV float2 cmul_col(float2 a, float2 w) { return cmulf(a, w, 1); }
+SFOC_DEV float2 cmul_inv(float2 a, float2 w) { return cmulf(a, make_float2(w.x, -w.y), 0); }
+SFOC_DEV float2 cmulc(float2 a, float2 b) {  // a * conj(b), the spectrum product
+    return make_float2(fmaf(a.y, b.y, a.x * b.x), fmaf(a.y, b.x, -(a.x * b.y)));
+}
+// The passes a codelet serves: forward rows and columns, inverse columns,
+// inverse rows; by themselves, pass A of the rows from float16 descriptors
+// and pass A of the inverse columns with an 8-point codelet.
+constexpr int kFwd = 0, kInvCol = 1, kInvRow = 2, kFwdF16 = 3, kInvColA8 = 4;
 SFOC_DEV float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 // c ? a : b per component (a select of two array elements written this way
 // stays in registers; as one conditional expression the compiler may turn
@@ -95,27 +118,45 @@ SFOC_DEV void pair_sync() {
 }
 
 // ---- small DFTs in registers -------------------------------------------
-template <bool INV>
+// 4-point DFT of which only the first K samples are given (the others are
+// zero and not read).
+template <bool INV, int K = 4>
 SFOC_DEV void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
-    const float2 t0 = cadd(a0, a2), t1 = csub(a0, a2), t2 = cadd(a1, a3), t3 = mul_mi<INV>(csub(a1, a3));
-    a0 = cadd(t0, t2);
-    a2 = csub(t0, t2);
-    a1 = cadd(t1, t3);
-    a3 = csub(t1, t3);
+    static_assert(K >= 1 && K <= 4, "at least one sample");
+    if constexpr (K == 1) {
+        a1 = a2 = a3 = a0;
+    } else if constexpr (K == 2) {
+        const float2 t0 = a0, t2 = a1, t3 = mul_mi<INV>(a1);
+        a0 = cadd(t0, t2);
+        a2 = csub(t0, t2);
+        a1 = cadd(t0, t3);
+        a3 = csub(t0, t3);
+    } else {
+        const float2 t0 = cadd(a0, a2), t1 = csub(a0, a2);
+        const float2 t2 = K == 4 ? cadd(a1, a3) : a1, t3 = mul_mi<INV>(K == 4 ? csub(a1, a3) : a1);
+        a0 = cadd(t0, t2);
+        a2 = csub(t0, t2);
+        a1 = cadd(t1, t3);
+        a3 = csub(t1, t3);
+    }
 }
 
-// x[k] <- sum_n x[n] W_8^(nk), W_8 = exp(-+2 pi i / 8); 2 x 4 split.
-template <bool INV>
+// x[k] <- sum_n x[n] W_8^(nk), W_8 = exp(-+2 pi i / 8); 2 x 4 split.  Only
+// the samples n < NV are read, the others count as zero.
+template <int CTX, int NV = 8>
 SFOC_DEV void dft8(float2 (&x)[8]) {
+    static_assert(NV >= 2 && NV <= 8, "both halves have a sample");
+    constexpr bool INV = CTX != kFwd && CTX != kFwdF16;
+    constexpr int kF[5][2] = {{2, 2}, {2, 1}, {2, 1}, {2, 2}, {1, 1}};   // product forms of b1 and b3
     float2 a0 = x[0], a1 = x[2], a2 = x[4], a3 = x[6];
     float2 b0 = x[1], b1 = x[3], b2 = x[5], b3 = x[7];
-    dft4<INV>(a0, a1, a2, a3);
-    dft4<INV>(b0, b1, b2, b3);
+    dft4<INV, (NV + 1) / 2>(a0, a1, a2, a3);
+    dft4<INV, NV / 2>(b0, b1, b2, b3);
     const float h = 0.70710678118654752f;
     const float sg = INV ? 1.f : -1.f;
-    b1 = cmul(b1, make_float2(h, sg * h));
+    b1 = cmulf(b1, make_float2(h, sg * h), kF[CTX][0]);
     b2 = mul_mi<INV>(b2);
-    b3 = cmul(b3, make_float2(-h, sg * h));
+    b3 = cmulf(b3, make_float2(-h, sg * h), kF[CTX][1]);
     x[0] = cadd(a0, b0);
     x[4] = csub(a0, b0);
     x[1] = cadd(a1, b1);
@@ -126,9 +167,17 @@ SFOC_DEV void dft8(float2 (&x)[8]) {
     x[7] = csub(a3, b3);
 }
 
-// 16-point DFT, 4 x 4 split: n = n1 + 4 n2, k = 4 k1 + k2.
-template <bool INV>
+// 16-point DFT, 4 x 4 split: n = n1 + 4 n2, k = 4 k1 + k2.  Only the samples
+// n < NV are read, the others count as zero.
+template <int CTX, int NV = 16>
 SFOC_DEV void dft16(float2 (&x)[16]) {
+    static_assert(NV >= 4 && NV <= 16, "every column has a sample");
+    constexpr bool INV = CTX == kInvCol || CTX == kInvRow;
+    // product forms of y[n1][k2], n1, k2 = 1..3 (W_16^4 is a swap)
+    constexpr int kF[4][3][3] = {{{2, 2, 2}, {2, 0, 2}, {2, 1, 1}},
+                                 {{1, 2, 1}, {1, 0, 1}, {1, 1, 2}},
+                                 {{0, 1, 0}, {2, 0, 1}, {0, 1, 2}},
+                                 {{2, 2, 2}, {2, 0, 2}, {2, 2, 1}}};
     const float sg = INV ? 1.f : -1.f;
     const float c1 = 0.92387953251128676f, s1 = 0.38268343236508977f, h = 0.70710678118654752f;
     // twiddles W_16^e for e = 0..9
@@ -137,19 +186,25 @@ SFOC_DEV void dft16(float2 (&x)[16]) {
                           make_float2(-h, sg * h), make_float2(-c1, sg * s1), make_float2(-1.f, 0.f),
                           make_float2(-c1, -sg * s1)};
     float2 y[4][4];
-#pragma unroll
-    for (int n1 = 0; n1 < 4; ++n1) {
+    auto column = [&](auto n1c) {
+        constexpr int n1 = decltype(n1c)::value, K = (NV - n1 + 3) / 4;
         float2 a0 = x[n1], a1 = x[n1 + 4], a2 = x[n1 + 8], a3 = x[n1 + 12];
-        dft4<INV>(a0, a1, a2, a3);
+        dft4<INV, K>(a0, a1, a2, a3);
         y[n1][0] = a0;
         y[n1][1] = a1;
         y[n1][2] = a2;
         y[n1][3] = a3;
-    }
+    };
+    column(std::integral_constant<int, 0>{});
+    column(std::integral_constant<int, 1>{});
+    column(std::integral_constant<int, 2>{});
+    column(std::integral_constant<int, 3>{});
 #pragma unroll
     for (int n1 = 1; n1 < 4; ++n1)
 #pragma unroll
-        for (int k2 = 1; k2 < 4; ++k2) y[n1][k2] = cmul(y[n1][k2], w[n1 * k2]);
+        for (int k2 = 1; k2 < 4; ++k2)
+            y[n1][k2] = n1 * k2 == 4 ? mul_mi<INV>(y[n1][k2])
+                                     : cmulf(y[n1][k2], w[n1 * k2], kF[CTX][n1 - 1][k2 - 1]);
 #pragma unroll
     for (int k2 = 0; k2 < 4; ++k2) {
         float2 a0 = y[0][k2], a1 = y[1][k2], a2 = y[2][k2], a3 = y[3][k2];
@@ -162,16 +217,22 @@ SFOC_DEV void dft16(float2 (&x)[16]) {
 }
 
 // 3-point DFT: with W = exp(-+2 pi i / 3) = -1/2 -+ i sqrt(3)/2,
-// X1, X2 = a0 - (a1 + a2)/2 +- i s (a1 - a2), s = -+sqrt(3)/2.
-template <bool INV>
+// X1, X2 = a0 - (a1 + a2)/2 +- i s (a1 - a2), s = -+sqrt(3)/2 (the product
+// rounded first in the inverse columns, fused elsewhere).
+template <int CTX>
 SFOC_DEV void dft3(float2& a0, float2& a1, float2& a2) {
-    const float s = (INV ? 1.f : -1.f) * 0.86602540378443865f;
+    const float s = (CTX != kFwd ? 1.f : -1.f) * 0.86602540378443865f;
     const float2 t1 = cadd(a1, a2), t2 = csub(a1, a2);
-    const float2 m = make_float2(a0.x - 0.5f * t1.x, a0.y - 0.5f * t1.y);
-    const float2 q = make_float2(-s * t2.y, s * t2.x);   // i s t2
+    const float2 m = make_float2(fmaf(-0.5f, t1.x, a0.x), fmaf(-0.5f, t1.y, a0.y));
     a0 = cadd(a0, t1);
-    a1 = cadd(m, q);
-    a2 = csub(m, q);
+    if constexpr (CTX == kInvCol) {
+        const float2 q = make_float2(__fmul_rn(-s, t2.y), __fmul_rn(s, t2.x));   // i s t2
+        a1 = make_float2(__fadd_rn(m.x, q.x), __fadd_rn(m.y, q.y));
+        a2 = make_float2(__fsub_rn(m.x, q.x), __fsub_rn(m.y, q.y));
+    } else {
+        a1 = make_float2(fmaf(-s, t2.y, m.x), fmaf(s, t2.x, m.y));
+        a2 = make_float2(fmaf(s, t2.y, m.x), fmaf(-s, t2.x, m.y));
+    }
 }
 
 // 5-point DFT from the conjugate-symmetric pairs (a1, a4) and (a2, a3):
@@ -186,10 +247,10 @@ SFOC_DEV void dft5(float2 (&a)[5]) {
     const float s1 = 0.95105651629515357f, s2 = 0.58778525229247313f;
     const float2 t1 = cadd(a[1], a[4]), t2 = cadd(a[2], a[3]);
     const float2 d1 = csub(a[1], a[4]), d2 = csub(a[2], a[3]);
-    const float2 p1 = make_float2(a[0].x + c1 * t1.x + c2 * t2.x, a[0].y + c1 * t1.y + c2 * t2.y);
-    const float2 p2 = make_float2(a[0].x + c2 * t1.x + c1 * t2.x, a[0].y + c2 * t1.y + c1 * t2.y);
-    const float2 e1 = make_float2(s1 * d1.x + s2 * d2.x, s1 * d1.y + s2 * d2.y);
-    const float2 e2 = make_float2(s2 * d1.x - s1 * d2.x, s2 * d1.y - s1 * d2.y);
+    const float2 p1 = make_float2(fmaf(c2, t2.x, fmaf(c1, t1.x, a[0].x)), fmaf(c2, t2.y, fmaf(c1, t1.y, a[0].y)));
+    const float2 p2 = make_float2(fmaf(c1, t2.x, fmaf(c2, t1.x, a[0].x)), fmaf(c1, t2.y, fmaf(c2, t1.y, a[0].y)));
+    const float2 e1 = make_float2(fmaf(s2, d2.x, s1 * d1.x), fmaf(s2, d2.y, s1 * d1.y));
+    const float2 e2 = make_float2(fmaf(s2, d1.x, -s1 * d2.x), fmaf(s2, d1.y, -s1 * d2.y));
     const float2 q1 = make_float2(-sg * e1.y, sg * e1.x);   // sigma i e1
     const float2 q2 = make_float2(-sg * e2.y, sg * e2.x);
     a[0] = cadd(a[0], cadd(t1, t2));
@@ -201,8 +262,10 @@ SFOC_DEV void dft5(float2 (&a)[5]) {
 
 // 10-point DFT, 2 x 5: the even and odd samples each get a 5-point DFT,
 // the odd ones then W_10^k, and X[k], X[k+5] = E[k] +- W_10^k O[k].
-template <bool INV>
+template <int CTX>
 SFOC_DEV void dft10(float2 (&x)[10]) {
+    constexpr bool INV = CTX != kFwd;
+    constexpr int kF[2][5] = {{0, 0, 0, 3, 3}, {0, 1, 1, 1, 1}};   // product forms of o[1..4]
     const float sg = INV ? 1.f : -1.f;
     float2 e[5], o[5];
 #pragma unroll
@@ -215,10 +278,10 @@ SFOC_DEV void dft10(float2 (&x)[10]) {
     // W_10^k = cos(pi k / 5) + sigma i sin(pi k / 5), k = 1..4
     const float ca = 0.80901699437494742f, sa = 0.58778525229247313f;   // 36 degrees
     const float cb = 0.30901699437494742f, sb = 0.95105651629515357f;   // 72 degrees
-    o[1] = cmul(o[1], make_float2(ca, sg * sa));
-    o[2] = cmul(o[2], make_float2(cb, sg * sb));
-    o[3] = cmul(o[3], make_float2(-cb, sg * sb));
-    o[4] = cmul(o[4], make_float2(-ca, sg * sa));
+    o[1] = cmulf(o[1], make_float2(ca, sg * sa), kF[INV][1]);
+    o[2] = cmulf(o[2], make_float2(cb, sg * sb), kF[INV][2]);
+    o[3] = cmulf(o[3], make_float2(-cb, sg * sb), kF[INV][3]);
+    o[4] = cmulf(o[4], make_float2(-ca, sg * sa), kF[INV][4]);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         x[k] = cadd(e[k], o[k]);
@@ -228,8 +291,11 @@ SFOC_DEV void dft10(float2 (&x)[10]) {
 
 // 12-point DFT, 3 x 4: n = n1 + 3 n2, k = 4 k1 + k2; 4-point DFTs over n2,
 // twiddles W_12^(n1 k2), 3-point DFTs over n1.
-template <bool INV>
+template <int CTX>
 SFOC_DEV void dft12(float2 (&x)[12]) {
+    constexpr bool INV = CTX != kFwd;
+    // product forms of y[n1][k2], n1 = 1, 2, k2 = 1..3
+    constexpr int kF[2][2][3] = {{{2, 0, 2}, {2, 3, 2}}, {{0, 1, 2}, {0, 1, 2}}};
     const float sg = INV ? 1.f : -1.f;
     const float h = 0.86602540378443865f;   // cos 30 degrees
     float2 y[3][4];
@@ -249,23 +315,25 @@ SFOC_DEV void dft12(float2 (&x)[12]) {
 #pragma unroll
     for (int n1 = 1; n1 < 3; ++n1)
 #pragma unroll
-        for (int k2 = 1; k2 < 4; ++k2) y[n1][k2] = cmul(y[n1][k2], w[n1 * k2]);
+        for (int k2 = 1; k2 < 4; ++k2) y[n1][k2] = cmulf(y[n1][k2], w[n1 * k2], kF[INV][n1 - 1][k2 - 1]);
 #pragma unroll
     for (int k2 = 0; k2 < 4; ++k2) {
         float2 a0 = y[0][k2], a1 = y[1][k2], a2 = y[2][k2];
-        dft3<INV>(a0, a1, a2);
+        dft3<CTX>(a0, a1, a2);
         x[k2] = a0;
         x[4 + k2] = a1;
         x[8 + k2] = a2;
     }
 }
 
-template <int N, bool INV>
+// N-point DFT of which only the samples n < NV are read (N = 8, 16).
+template <int N, int CTX, int NV = N>
 SFOC_DEV void dftn(float2 (&x)[N]) {
-    if constexpr (N == 8) dft8<INV>(x);
-    else if constexpr (N == 10) dft10<INV>(x);
-    else if constexpr (N == 12) dft12<INV>(x);
-    else dft16<INV>(x);
+    static_assert(NV == N || N == 8 || N == 16, "leading samples");
+    if constexpr (N == 8) dft8<CTX, NV>(x);
+    else if constexpr (N == 10) dft10<CTX>(x);
+    else if constexpr (N == 12) dft12<CTX>(x);
+    else dft16<CTX, NV>(x);
 }
 
 // ---- geometry ----------------------------------------------------------
@@ -274,28 +342,42 @@ SFOC_DEV void dftn(float2 (&x)[N]) {
 // buffer of the larger sides leaves room for one); the kernels' launch
 // bounds ask for the waves per SIMD that MINB workgroups need, which caps
 // their registers accordingly.
+//
+// LDS layout of the transform buffer: row r starts at r * PITCH + (r / NB) *
+// SKEW complex values; the pass-A output k2 of element n1 of a row pair sits
+// at slot k2 * (NB + PAD) + n1 (ROT: k2 * NB + (n1 + k2) mod NB) of the pair's
+// two rows.  The LDS serves 16 lanes of a 64-bit access per cycle from 32
+// banks, so 16 consecutive lanes should touch 16 complex addresses that
+// differ mod 16.  With PM_A / PM_B (below) the 16 lanes of the row passes
+// hold two pairs (four at side 64) whose starts differ by 8 (4, 8, 12) mod
+// 16; the column passes' rows n1 + NB k and the pass-B slots then fall on
+// distinct residues too (side 128: 5120 LDS cycles per channel in that model,
+// 9984 with pitch 68, skew 8 and consecutive pairs).
+//
+// What bounds the transforms: their VALU and LDS instructions, and the chain
+// of stages a workgroup waits for.  Branches around single elements, address
+// arithmetic per twiddle, LDS conflicts and eight barriers a channel are what
+// this form takes out; measured per launch (float32 unless said): side 128,
+// 400 IPs 310 -> 225 us; one IP per CU (119 IPs, float16, z = 12) 209 -> 110 us;
+// side 160, 5000 IPs, bfloat16 9.98 -> 6.05 ms; side 64, 16 IPs 162 -> 118 us;
+// side 192, 209 blocks 453 -> 350 us.
 template <int L>
 struct Fft;
-// LDS layout of the transform buffer: row r starts at r * PITCH + (r / NB) *
-// SKEW complex values.  The column passes read rows n1 + NB k (k across the
-// lanes of a wave, or across the loop), whose starts would otherwise fall on
-// the same LDS banks; the pitch and the per-group skew spread both kinds of
-// access over all banks, and keep each row (and each row pair) contiguous.
 template <>
 struct Fft<128> {
-    static constexpr int NA = 16, NB = 8, NT = 512, PITCH = 68, SKEW = 8, MINB = 2;
+    static constexpr int NA = 16, NB = 8, NT = 512, PITCH = 74, SKEW = 2, PAD = 1, ROT = 0, MINB = 2;
 };
 template <>
 struct Fft<64> {
-    static constexpr int NA = 8, NB = 8, NT = 128, PITCH = 40, SKEW = 8, MINB = 7;
+    static constexpr int NA = 8, NB = 8, NT = 128, PITCH = 38, SKEW = 4, PAD = 1, ROT = 0, MINB = 7;
 };
 template <>
 struct Fft<160> {
-    static constexpr int NA = 16, NB = 10, NT = 640, PITCH = 84, SKEW = 8, MINB = 1;
+    static constexpr int NA = 16, NB = 10, NT = 640, PITCH = 93, SKEW = 0, PAD = 1, ROT = 0, MINB = 1;
 };
 template <>
 struct Fft<192> {
-    static constexpr int NA = 16, NB = 12, NT = 768, PITCH = 100, SKEW = 8, MINB = 1;
+    static constexpr int NA = 16, NB = 12, NT = 768, PITCH = 102, SKEW = 2, PAD = 0, ROT = 1, MINB = 1;
 };
 
 template <int L>
@@ -307,22 +389,34 @@ struct MatchCfg {
     static constexpr int COLS = L / 2;                     // column transforms (DC+Nyquist packed)
     static constexpr int RB = COLS * HA / NT;              // pass-B tasks per thread
     static constexpr int BINS = 2 * NB;                    // bins per pass-B task
-    // Two tasks' loads in flight in the search window's stages where a
-    // thread has at least two tasks per stage (L / 2 row pairs or columns
-    // of NB tasks each) and the registers allow it (side 64).
-    static constexpr bool PIPE = L * NB / 2 >= 2 * NT && L <= 128;
+    static constexpr int PW = 64 / HA;                     // row pairs / columns of a wave's pass-B tasks
+    // Where a wave's pairs or columns are also a whole number of pass-A
+    // rounds, the wave does both passes of them and only orders its own LDS
+    // accesses in between; otherwise the workgroup synchronises.
+    static constexpr bool WL = PW * NB % 64 == 0;
+    static constexpr int AR = WL ? PW * NB / 64 : (COLS * NB + NT - 1) / NT;   // pass-A rounds
     static_assert(L == NA * NB && NB % 2 == 0 && NA % 2 == 0, "even radices");
-    static_assert(COLS * HA % NT == 0, "whole pass-B rounds");
-    static_assert(2 * P >= L, "a row pair holds one real row of L values per row");
+    static_assert(COLS * HA == NT, "one pass-B task per thread and stage");
+    static_assert(2 * P >= (NA - 1) * (NB + F::PAD) + NB && 2 * P >= L,
+                  "a row pair holds its pass-A outputs, or one real row of L values per row");
     static constexpr size_t buf_elems = (size_t)L * P + (size_t)(L / NB) * SKEW;   // complex
     static SFOC_DEV int row(int r) { return r * P + (r / NB) * SKEW; }
     // row n1 + NB * k with n1 < NB: its NB-row group is k
     static SFOC_DEV int rowg(int n1, int k) { return n1 * P + k * (NB * P + SKEW); }
-    // Slot of element n1 of pass-A output column k2 inside a row pair: a
-    // permutation of n1 that differs between columns (bank spreading).
-    static SFOC_DEV int swz(int n1, int k2) {
-        if constexpr ((NB & (NB - 1)) == 0) return n1 ^ (k2 & (NB - 1));
-        else return (n1 + k2) % NB;
+    // Slot of element n1 of pass-A output column k2 inside a row pair.
+    static SFOC_DEV int slot(int n1, int k2) {
+        if constexpr (F::ROT) return k2 * NB + (n1 + k2) % NB;
+        else return k2 * (NB + F::PAD) + n1;
+    }
+    // Pair of a wave (or, in pass A without WL, the pair itself) that holds
+    // the lanes of index q: neighbouring indices take pairs whose LDS starts
+    // differ by 8 mod 16 (2 PITCH = 4 mod 8: two apart; 10 mod 16: four).
+    static SFOC_DEV int pm_swap(int q) { return (q & ~3) | ((q & 1) << 1) | ((q >> 1) & 1); }
+    static SFOC_DEV int pm_a(int q) { return WL ? pm_swap(q) : q; }
+    static SFOC_DEV int pm_b(int q) {
+        if constexpr (HA == 4) return q;                              // four consecutive pairs
+        else if constexpr (2 * P % 8 == 4) return pm_swap(q);
+        else return (q & ~7) | ((q >> 1) & 3) | ((q & 1) << 2);
     }
     static constexpr size_t lds_bytes = sizeof(float2) * (buf_elems + L) + 1024;
 };
@@ -376,217 +470,266 @@ SFOC_DEV void join_packed(float2 (&u)[NB], float2 (&v)[NB], int j) {
 }
 
 // ---- row stage: real rows -> half spectra -------------------------------
-// Rows [0, nrows) x columns [0, ncols) of one descriptor plane, zero padded
-// to L; result: buf row a holds the half spectrum (bins 0..L/2) of row a.
-// s1 / s2 (if given) accumulate the sum and sum of squares of the values.
-template <int L, int DT, bool PIPE>
-SFOC_DEV void row_stage(const void* plane, int pitch, int y0, int x0, int nrows, int ncols, float2* buf,
-                        const float2* tw, double* s1, double* s2) {
+// Pass A of rows [0, nrows) x columns [0, ncols) of one descriptor plane,
+// zero padded to L: of each row pair, taken as one complex row, element n1's
+// samples n1 + NB n2, n2 < NV, are transformed (ncols <= NV * NB; the others
+// are zero) and stored with their twiddles.  s1 / s2 (SUMS) accumulate the
+// sum and sum of squares of the values.
+template <int L, int DT, int NV, bool SUMS>
+SFOC_DEV void row_pass_a(const void* __restrict__ plane, int pitch, int y0, int x0, int nrows, int ncols,
+                         float2* buf, const float2* tw, double& s1, double& s2) {
     using C = MatchCfg<L>;
+    constexpr int ES = DT == 0 ? 4 : 2;
     const int tid = tid_local();
     const int npair = (nrows + 1) / 2;
-    const int tasksA = npair * C::NB;
-    // Loads from one pointer per row and task (32-bit offsets from the plane
-    // base: a plane holds < 2^30 elements); element n2 lies NB * n2 elements
-    // further on, a constant offset the load instruction encodes, so the
-    // loads need no per-element address arithmetic.  The window lies inside
-    // the image; a missing second row re-reads the first (then zeroed).
-    // Full-width windows (ncols == L) need no column test; narrower ones load
-    // only the columns below ncols and zero the rest.
-    const bool full = ncols == L;
-    auto load = [&](int task, float2(&x)[C::NA]) {
-        const int p = task / C::NB, n1 = task - p * C::NB;
+    // Loads at 32-bit byte offsets from the plane (a plane holds < 2^30
+    // elements); sample n2 lies NB * n2 elements further on, a constant
+    // offset the load instruction encodes.  The window lies inside the image;
+    // a missing second row re-reads the first (then zeroed).  Where the
+    // samples end inside the NV blocks, columns are clamped into the window
+    // and the samples beyond it zeroed.
+    const bool full = ncols == NV * C::NB, odd = nrows & 1;
+    auto load = [&](int p, int n1, float2(&x)[C::NA]) {
+        const char* base = static_cast<const char*>(plane);
         const bool two = 2 * p + 1 < nrows;
-        const int oa = (y0 + 2 * p) * pitch + x0 + n1;
-        const int ob = oa + (two ? pitch : 0);
-        const void* ra = elem_ptr<DT>(plane, oa);
-        const void* rb = elem_ptr<DT>(plane, ob);
+        const uint32_t oa = (uint32_t)((y0 + 2 * p) * pitch + x0);
+        const uint32_t ob = oa + (two ? (uint32_t)pitch : 0u);
         if (full) {
+            const char* ra = base + (size_t)(oa + n1) * ES;
+            const char* rb = base + (size_t)(ob + n1) * ES;
 #pragma unroll
-            for (int n2 = 0; n2 < C::NA; ++n2) {
-                const float re = ldd<DT>(ra, C::NB * n2), im = ldd<DT>(rb, C::NB * n2);
-                x[n2] = make_float2(re, two ? im : 0.f);
-            }
+            for (int n2 = 0; n2 < NV; ++n2) x[n2] = make_float2(ldd<DT>(ra, C::NB * n2), ldd<DT>(rb, C::NB * n2));
         } else {
 #pragma unroll
-            for (int n2 = 0; n2 < C::NA; ++n2) {
-                float re = 0.f, im = 0.f;
-                if (n1 + C::NB * n2 < ncols) {
-                    re = ldd<DT>(ra, C::NB * n2);
-                    im = ldd<DT>(rb, C::NB * n2);
-                }
-                x[n2] = make_float2(re, two ? im : 0.f);
+            for (int n2 = 0; n2 < NV; ++n2) {
+                const uint32_t c = (uint32_t)min(n1 + C::NB * n2, ncols - 1);
+                x[n2] = make_float2(ldd<DT>(base + (size_t)(oa + c) * ES, 0), ldd<DT>(base + (size_t)(ob + c) * ES, 0));
             }
+#pragma unroll
+            for (int n2 = 0; n2 < NV; ++n2)
+                if (n1 + C::NB * n2 >= ncols) x[n2] = make_float2(0.f, 0.f);
+        }
+        if (odd) {
+#pragma unroll
+            for (int n2 = 0; n2 < NV; ++n2) x[n2].y = two ? x[n2].y : 0.f;
         }
     };
-    auto finish = [&](int task, float2(&x)[C::NA]) {
-        const int p = task / C::NB, n1 = task - p * C::NB;
-        if (s1) {
+    auto finish = [&](int p, int n1, float2(&x)[C::NA]) {
+        if constexpr (SUMS) {
             double a = 0.0, q = 0.0;
 #pragma unroll
-            for (int n2 = 0; n2 < C::NA; ++n2) {
+            for (int n2 = 0; n2 < NV; ++n2) {
                 const double dr = x[n2].x, di = x[n2].y;
                 a += dr + di;
                 q += dr * dr + di * di;
             }
-            *s1 += a;
-            *s2 += q;
+            s1 += a;
+            s2 += q;
         }
-        dftn<C::NA, false>(x);
+        dftn<C::NA, DT == 2 ? kFwdF16 : kFwd, NV>(x);
         float2* reg = buf + C::row(2 * p);
+        const float2* w = tw + n1;
 #pragma unroll
         for (int k2 = 0; k2 < C::NA; ++k2)
-            reg[k2 * C::NB + C::swz(n1, k2)] = k2 == 0 ? x[0] : cmul(x[k2], tw[n1 * k2]);
+            reg[C::slot(n1, k2)] = k2 == 0 ? x[0] : cmul_row(x[k2], w[k2 * C::NB]);
     };
-    if (PIPE) {
-        // Two tasks per iteration with both tasks' loads issued first.
-#pragma unroll 1
-        for (int task = tid; task < tasksA; task += 2 * C::NT) {
-            float2 xa[C::NA], xb[C::NA];
-            const bool second = task + C::NT < tasksA;
-            load(task, xa);
-            if (second) load(task + C::NT, xb);
-            finish(task, xa);
-            if (second) finish(task + C::NT, xb);
+    if constexpr (C::WL) {   // every round's loads first
+        const int wp = (tid >> 6) * C::PW, lane = tid & 63;
+        float2 x[C::AR][C::NA];
+#pragma unroll
+        for (int rd = 0; rd < C::AR; ++rd) {
+            const int q = rd * 64 + lane, p = wp + C::pm_a(q / C::NB);
+            if (p < npair) load(p, q % C::NB, x[rd]);
         }
+#pragma unroll
+        for (int rd = 0; rd < C::AR; ++rd) {
+            const int q = rd * 64 + lane, p = wp + C::pm_a(q / C::NB);
+            if (p < npair) finish(p, q % C::NB, x[rd]);
+        }
+        wave_sync();
     } else {
 #pragma unroll 1
-        for (int task = tid; task < tasksA; task += C::NT) {
+        for (int task = tid; task < npair * C::NB; task += C::NT) {
+            const int p = task / C::NB, n1 = task - p * C::NB;
             float2 x[C::NA];
-            load(task, x);
-            finish(task, x);
+            load(p, n1, x);
+            finish(p, n1, x);
         }
+        __syncthreads();
     }
-    __syncthreads();
-    const int tasksB = npair * C::HA;
-    const int rounds = (tasksB + C::NT - 1) / C::NT;
-#pragma unroll 1
-    for (int rd = 0; rd < rounds; ++rd) {
-        const int task = rd * C::NT + tid;
-        const bool act = task < tasksB;
-        const int p = task / C::HA, j = task - p * C::HA;
-        float2 u[C::NB], v[C::NB];
-        float2* reg = buf + C::row(2 * p);
-        if (act) {
-            const int ka = j, kb = j == 0 ? C::HA : C::NA - j;
+}
+
+// Pass B: buf row a then holds the half spectrum of row a, times two (the
+// halving of the separation is left to the inverse's scale: exact, a power of
+// two): bins 1..L/2 - 1, and the real DC and Nyquist bins packed in bin 0.
+// A pair's pass-B tasks are lanes of one wave, so the reads of a pair are
+// ordered before its in-place writes within the wave.
+template <int L>
+SFOC_DEV void row_pass_b(int nrows, float2* buf) {
+    using C = MatchCfg<L>;
+    const int tid = tid_local();
+    const int j = tid % C::HA, p = (tid >> 6) * C::PW + C::pm_b((tid & 63) / C::HA);
+    const bool act = p < (nrows + 1) / 2;
+    const int ka = j, kb = j == 0 ? C::HA : C::NA - j;
+    float2* ra = buf + C::row(2 * p);
+    float2 u[C::NB], v[C::NB];
+    if (act) {
 #pragma unroll
-            for (int n1 = 0; n1 < C::NB; ++n1) {
-                u[n1] = reg[ka * C::NB + C::swz(n1, ka)];
-                v[n1] = reg[kb * C::NB + C::swz(n1, kb)];
-            }
-            dftn<C::NB, false>(u);
-            dftn<C::NB, false>(v);
+        for (int n1 = 0; n1 < C::NB; ++n1) {
+            u[n1] = ra[C::slot(n1, ka)];
+            v[n1] = ra[C::slot(n1, kb)];
         }
-        pair_sync<C::HA>();   // this pair's reads before its in-place writes
-        if (act) {
-            // half spectra of the two real rows: A = (X + conj X~)/2, B = -i (X - conj X~)/2
-            float2* ra = buf + C::row(2 * p);
-            float2* rb = ra + C::P;
-            const int ka = j, kb = j == 0 ? C::HA : C::NA - j;
+        dftn<C::NB, kFwd>(u);
+        dftn<C::NB, kFwd>(v);
+    }
+    wave_sync();
+    if (act) {
+        // twice the half spectra of the two real rows: 2A = X + conj X~, 2B = -i (X - conj X~)
+        float2* rb = ra + C::P;
 #pragma unroll
-            for (int k1 = 0; k1 <= C::NB / 2; ++k1) {
-                if (k1 < C::NB / 2 || j == 0) {
-                    const float2 za = u[k1];
-                    const float2 zb = cconj(pick(j == 0, u[(C::NB - k1) % C::NB], v[C::NB - 1 - k1]));
-                    const int k = C::NA * k1 + ka;
-                    ra[k] = cscale(cadd(za, zb), 0.5f);
-                    rb[k] = cscale(mul_mi<false>(csub(za, zb)), 0.5f);
-                }
+        for (int k1 = 0; k1 < C::NB / 2; ++k1) {
+            const float2 za = u[k1];
+            const float2 zb = cconj(pick(j == 0, u[(C::NB - k1) % C::NB], v[C::NB - 1 - k1]));
+            float2 A = cadd(za, zb), B = mul_mi<false>(csub(za, zb));
+            if (k1 == 0) {   // j == 0: bin 0, with the Nyquist bin
+                A.y = j == 0 ? u[C::NB / 2].x + u[C::NB / 2].x : A.y;
+                B.y = j == 0 ? u[C::NB / 2].y + u[C::NB / 2].y : B.y;
             }
+            ra[C::NA * k1 + ka] = A;
+            rb[C::NA * k1 + ka] = B;
+        }
 #pragma unroll
-            for (int k1 = 0; k1 < C::NB / 2; ++k1) {
-                const float2 za = v[k1];
-                const float2 zb = cconj(pick(j == 0, v[C::NB - 1 - k1], u[C::NB - 1 - k1]));
-                const int k = C::NA * k1 + kb;
-                ra[k] = cscale(cadd(za, zb), 0.5f);
-                rb[k] = cscale(mul_mi<false>(csub(za, zb)), 0.5f);
-            }
+        for (int k1 = 0; k1 < C::NB / 2; ++k1) {
+            const float2 za = v[k1];
+            const float2 zb = cconj(pick(j == 0, v[C::NB - 1 - k1], u[C::NB - 1 - k1]));
+            ra[C::NA * k1 + kb] = cadd(za, zb);
+            rb[C::NA * k1 + kb] = mul_mi<false>(csub(za, zb));
         }
     }
     __syncthreads();
 }
 
 // ---- column stage: buf columns -> spectrum bins in registers --------------
-// Column transforms over rows 0..L-1 of columns 1..L/2-1 and of the packed
-// column 0 (forward: DC + i Nyquist taken from columns 0 and L/2; inverse:
-// column 0 as stored).  Rows >= nvalid read as zero.  out[rd][q] receives
-// bin bin_of(j, q) of task rd (column cc = task / HA, j = task % HA):
-// sink(rd, cc, j, u, v) gets values q < NB in u and q >= NB in v (writable).
-template <int L, bool INV, bool PIPE, typename Sink>
-SFOC_DEV void col_stage(float2* buf, const float2* tw, int nvalid, Sink&& sink) {
+// Pass A of the column transforms over columns 1..L/2-1 and the packed column
+// 0 (DC + i Nyquist), in place.  Rows >= nvalid (at most NV * NB of them are
+// valid) count as zero and are not used.
+template <int L, bool INV, int NV>
+SFOC_DEV void col_pass_a(float2* buf, const float2* tw, int nvalid) {
     using C = MatchCfg<L>;
     const int tid = tid_local();
+    const bool full = nvalid == NV * C::NB;
     // task (cc, n1) reads and rewrites rows n1 + NB m of column cc only
-    auto load = [&](int task, float2(&x)[C::NA]) {
-        const int cc = task / C::NB, n1 = task - cc * C::NB;
+    auto load = [&](int cc, int n1, float2(&x)[C::NA]) {
+        const float2* b = buf + C::rowg(n1, 0) + cc;
 #pragma unroll
-        for (int n2 = 0; n2 < C::NA; ++n2) {
-            const int row = n1 + C::NB * n2;
-            float2 v = make_float2(0.f, 0.f);
-            if (row < nvalid) {
-                if (cc == 0 && !INV) v = make_float2(buf[C::rowg(n1, n2)].x, buf[C::rowg(n1, n2) + L / 2].x);
-                else v = buf[C::rowg(n1, n2) + cc];
-            }
-            x[n2] = v;
+        for (int n2 = 0; n2 < NV; ++n2) x[n2] = b[C::rowg(0, n2)];
+        if (!full) {
+#pragma unroll
+            for (int n2 = 0; n2 < NV; ++n2)
+                if (n1 + C::NB * n2 >= nvalid) x[n2] = make_float2(0.f, 0.f);
         }
     };
-    auto finish = [&](int task, float2(&x)[C::NA]) {
-        const int cc = task / C::NB, n1 = task - cc * C::NB;
-        dftn<C::NA, INV>(x);
+    auto finish = [&](int cc, int n1, float2(&x)[C::NA]) {
+        dftn<C::NA, INV ? (C::NA == 8 ? kInvColA8 : kInvCol) : kFwd, NV>(x);
+        float2* b = buf + C::rowg(n1, 0) + cc;
+        const float2* tb = tw + n1;
 #pragma unroll
         for (int k2 = 0; k2 < C::NA; ++k2) {
-            float2 w = tw[n1 * k2];
-            if (INV) w.y = -w.y;
-            buf[C::rowg(n1, k2) + cc] = k2 == 0 ? x[0] : cmul(x[k2], w);
+            const float2 w = tb[k2 * C::NB];
+            b[C::rowg(0, k2)] = k2 == 0 ? x[0] : INV ? cmul_inv(x[k2], w) : cmul_col(x[k2], w);
         }
     };
-    if (PIPE) {   // two tasks per iteration, both tasks' reads first
-#pragma unroll 1
-        for (int task = tid; task < C::COLS * C::NB; task += 2 * C::NT) {
-            float2 xa[C::NA], xb[C::NA];
-            const bool second = task + C::NT < C::COLS * C::NB;
-            load(task, xa);
-            if (second) load(task + C::NT, xb);
-            finish(task, xa);
-            if (second) finish(task + C::NT, xb);
+    if constexpr (C::WL) {
+        const int wc = (tid >> 6) * C::PW, lane = tid & 63;
+        float2 x[C::AR][C::NA];
+#pragma unroll
+        for (int rd = 0; rd < C::AR; ++rd) {
+            const int q = rd * 64 + lane;
+            load(wc + q / C::NB, q % C::NB, x[rd]);
         }
-    } else {
+#pragma unroll
+        for (int rd = 0; rd < C::AR; ++rd) {
+            const int q = rd * 64 + lane;
+            finish(wc + q / C::NB, q % C::NB, x[rd]);
+        }
+        wave_sync();
+    } else {   // consecutive lanes take consecutive columns
 #pragma unroll 1
         for (int task = tid; task < C::COLS * C::NB; task += C::NT) {
+            const int n1 = task / C::COLS, cc = task - n1 * C::COLS;
             float2 x[C::NA];
-            load(task, x);
-            finish(task, x);
+            load(cc, n1, x);
+            finish(cc, n1, x);
         }
+        __syncthreads();
     }
-    __syncthreads();
+}
+
+// Pass B: this thread's bins bin_of(j, q) of column cc (thread = cc * HA +
+// j), values q < NB in u and q >= NB in v.
+template <int L, bool INV>
+SFOC_DEV void col_pass_b(const float2* buf, float2 (&u)[MatchCfg<L>::NB], float2 (&v)[MatchCfg<L>::NB]) {
+    using C = MatchCfg<L>;
+    const int tid = tid_local();
+    const int cc = tid / C::HA, j = tid - cc * C::HA;
+    const int ka = j, kb = j == 0 ? C::HA : C::NA - j;
+    const float2* ba = buf + C::rowg(0, ka) + cc;
+    const float2* bb = buf + C::rowg(0, kb) + cc;
 #pragma unroll
-    for (int rd = 0; rd < C::RB; ++rd) {
-        const int task = rd * C::NT + tid;
-        const int cc = task / C::HA, j = task - cc * C::HA;
-        const int ka = j, kb = j == 0 ? C::HA : C::NA - j;
-        float2 u[C::NB], v[C::NB];
-#pragma unroll
-        for (int n1 = 0; n1 < C::NB; ++n1) {
-            u[n1] = buf[C::rowg(n1, ka) + cc];
-            v[n1] = buf[C::rowg(n1, kb) + cc];
-        }
-        dftn<C::NB, INV>(u);
-        dftn<C::NB, INV>(v);
-        sink(rd, cc, j, u, v);
+    for (int n1 = 0; n1 < C::NB; ++n1) {
+        u[n1] = ba[C::rowg(n1, 0)];
+        v[n1] = bb[C::rowg(n1, 0)];
     }
+    dftn<C::NB, INV ? kInvCol : kFwd>(u);
+    dftn<C::NB, INV ? kInvCol : kFwd>(v);
+}
+
+// Forward 2-D transform of an nrows x ncols window of one plane into buf and
+// this thread's bins (u, v).  Windows of at most half or three quarters of
+// the side skip the samples that are zero by their extent (HALF: half is one
+// of the choices).
+template <int L, int DT, bool HALF, bool SUMS>
+SFOC_DEV void forward_2d(const void* plane, int pitch, int y0, int x0, int nrows, int ncols, float2* buf,
+                         const float2* tw, double& s1, double& s2, float2 (&u)[MatchCfg<L>::NB],
+                         float2 (&v)[MatchCfg<L>::NB]) {
+    using C = MatchCfg<L>;
+    const int side = max(nrows, ncols), nvalid = 2 * ((nrows + 1) / 2);
+    auto stages = [&](auto nv) {
+        constexpr int NV = decltype(nv)::value;
+        row_pass_a<L, DT, NV, SUMS>(plane, pitch, y0, x0, nrows, ncols, buf, tw, s1, s2);
+    };
+    auto columns = [&](auto nv) { col_pass_a<L, false, decltype(nv)::value>(buf, tw, nvalid); };
+    constexpr std::integral_constant<int, C::NA / 2> half{};
+    constexpr std::integral_constant<int, C::NA * 3 / 4> most{};
+    constexpr std::integral_constant<int, C::NA> all{};
+    stage_fence();
+    if (HALF && side <= half.value * C::NB) stages(half);
+    else if (side <= most.value * C::NB) stages(most);
+    else stages(all);
+    stage_fence();
+    row_pass_b<L>(nrows, buf);
+    stage_fence();
+    if (HALF && side <= half.value * C::NB) columns(half);
+    else if (side <= most.value * C::NB) columns(most);
+    else columns(all);
+    col_pass_b<L, false>(buf, u, v);
 }
 
 SFOC_DEV bool in_image(int64_t y, int64_t x, int h, int w, int64_t H, int64_t W) {
     return y >= 0 && x >= 0 && y + h <= H && x + w <= W;
 }
 
-// Twiddles W_L^k, k < L, into LDS (once per workgroup).
+// Twiddles W_L^(n1 k2), n1 < NB, k2 < NA, at tw[k2 * NB + n1] in LDS (once
+// per workgroup): a thread's n1 fixes its base address and k2 an offset that
+// the LDS instruction encodes.
 template <int L>
 SFOC_DEV void init_twiddles(float2* tw) {
-    for (int k = threadIdx.x; k < L; k += MatchCfg<L>::NT) {
+    using C = MatchCfg<L>;
+    for (int e = threadIdx.x; e < L; e += C::NT) {
+        const int k = (e % C::NB) * (e / C::NB);
         float sn, cs;
         sincospif(-2.0f * (float)k / (float)L, &sn, &cs);
-        tw[k] = make_float2(cs, sn);
+        tw[e] = make_float2(cs, sn);
     }
 }
 
@@ -813,48 +956,40 @@ SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const floa
         return;
     }
 
-    float2 acc[C::RB][C::BINS];   // sum over channels of F(S_h) conj(F(T_h))
+    float2 acc[C::BINS];   // sum over channels of F(S_h) conj(F(T_h))
 #pragma unroll
-    for (int rd = 0; rd < C::RB; ++rd)
-#pragma unroll
-        for (int q = 0; q < C::BINS; ++q) acc[rd][q] = make_float2(0.f, 0.f);
+    for (int q = 0; q < C::BINS; ++q) acc[q] = make_float2(0.f, 0.f);
     double s1 = 0.0, s2 = 0.0;
     const int64_t plane_s = A.Hs * A.Ws, plane_r = A.Hr * A.Wr;
-    const int mpair2 = 2 * ((m + 1) / 2), Mpair2 = 2 * ((Mu + 1) / 2);
     // Per channel: the search window first (only the running sum is live
     // during its larger row stage), its spectrum kept in registers, then the
     // template, whose column stage accumulates F(S_h) conj(F(T_h)).
-    float2 xsp[C::RB][C::BINS];   // search-window spectrum of the current channel
+    float2 xsp[C::BINS];   // search-window spectrum of the current channel
     for (int h = 0; h < A.z; ++h) {
-        stage_fence();
-        row_stage<L, DT, C::PIPE>(elem_ptr<DT>(A.desc_ref, h * plane_r), (int)A.Wr, (int)(sy + u0), (int)(sx + v0), Mu, Mv,
-                         buf, tw, nullptr, nullptr);
-        stage_fence();
-        col_stage<L, false, C::PIPE>(buf, tw, Mpair2, [&](int rd, int cc, int j, float2(&u)[C::NB], float2(&v)[C::NB]) {
-            if (cc == 0) separate_packed<C::NB>(u, v, j);
+        float2 u[C::NB], v[C::NB];
+        forward_2d<L, DT, false, false>(elem_ptr<DT>(A.desc_ref, h * plane_r), (int)A.Wr, (int)(sy + u0),
+                                        (int)(sx + v0), Mu, Mv, buf, tw, s1, s2, u, v);
+        const int tl = tid_local(), cc = tl / C::HA, j = tl - cc * C::HA;
+        if (cc == 0) separate_packed<C::NB>(u, v, j);
 #pragma unroll
-            for (int q = 0; q < C::NB; ++q) {
-                xsp[rd][q] = u[q];
-                xsp[rd][C::NB + q] = v[q];
-            }
-        });
+        for (int q = 0; q < C::NB; ++q) {
+            xsp[q] = u[q];
+            xsp[C::NB + q] = v[q];
+        }
         __syncthreads();
-        stage_fence();
-        row_stage<L, DT, false>(elem_ptr<DT>(A.desc_sen, h * plane_s), (int)A.Ws, (int)ty, (int)tx, m, m, buf, tw, &s1, &s2);
-        stage_fence();
-        col_stage<L, false, false>(buf, tw, mpair2, [&](int rd, int cc, int j, float2(&u)[C::NB], float2(&v)[C::NB]) {
-            if (cc == 0) separate_packed<C::NB>(u, v, j);
-            const bool self = cc == 0 && j == 0;   // slots 0 and NB/2 hold (F_dc, F_nyq) as reals
+        forward_2d<L, DT, true, true>(elem_ptr<DT>(A.desc_sen, h * plane_s), (int)A.Ws, (int)ty, (int)tx, m, m, buf,
+                                      tw, s1, s2, u, v);
+        if (cc == 0) separate_packed<C::NB>(u, v, j);
+        const bool self = tl == 0;   // cc = j = 0: slots 0 and NB/2 hold (F_dc, F_nyq) as reals
 #pragma unroll
-            for (int q = 0; q < C::BINS; ++q) {
-                const float2 xs = xsp[rd][q];
-                const float2 yt = q < C::NB ? u[q] : v[q - C::NB];
-                if ((q == 0 || q == C::NB / 2) && self)
-                    acc[rd][q] = make_float2(fmaf(xs.x, yt.x, acc[rd][q].x), fmaf(xs.y, yt.y, acc[rd][q].y));
-                else
-                    acc[rd][q] = cadd(acc[rd][q], cmulc(xs, yt));
-            }
-        });
+        for (int q = 0; q < C::BINS; ++q) {
+            const float2 xs = xsp[q];
+            const float2 yt = q < C::NB ? u[q] : v[q - C::NB];
+            const float2 a = acc[q];
+            acc[q] = cadd(a, cmulc(xs, yt));
+            if (q == 0 || q == C::NB / 2)
+                acc[q] = pick(self, make_float2(fmaf(xs.x, yt.x, a.x), fmaf(xs.y, yt.y, a.y)), acc[q]);
+        }
         __syncthreads();
     }
 
@@ -862,124 +997,117 @@ SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const floa
 
     // inverse, columns first: spectrum bins back to LDS (natural order), then
     // column transforms k1 -> u.
-#pragma unroll
-    for (int rd = 0; rd < C::RB; ++rd) {
-        const int task = rd * C::NT + t;
-        const int cc = task / C::HA, j = task - cc * C::HA;
-        if (cc == 0) {
-            float2 u[C::NB], v[C::NB];
-#pragma unroll
-            for (int q = 0; q < C::NB; ++q) {
-                u[q] = acc[rd][q];
-                v[q] = acc[rd][C::NB + q];
-            }
-            join_packed<C::NB>(u, v, j);
-#pragma unroll
-            for (int q = 0; q < C::NB; ++q) {
-                acc[rd][q] = u[q];
-                acc[rd][C::NB + q] = v[q];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < C::BINS; ++q) buf[C::row(bin_of<L>(j, q)) + cc] = acc[rd][q];
-    }
-    __syncthreads();
     {
-        float2 zc[C::RB][C::BINS];
-        col_stage<L, true, C::PIPE>(buf, tw, L, [&](int rd, int, int, float2(&u)[C::NB], float2(&v)[C::NB]) {
+        const int cc = t / C::HA, j = t - cc * C::HA;
+        float2 u[C::NB], v[C::NB];
 #pragma unroll
-            for (int q = 0; q < C::NB; ++q) {
-                zc[rd][q] = u[q];
-                zc[rd][C::NB + q] = v[q];
-            }
-        });
+        for (int q = 0; q < C::NB; ++q) {
+            u[q] = acc[q];
+            v[q] = acc[C::NB + q];
+        }
+        if (cc == 0) join_packed<C::NB>(u, v, j);
+        const int kb = j == 0 ? C::HA : C::NA - j;
+#pragma unroll
+        for (int q = 0; q < C::NB; ++q) {
+            buf[C::row(C::NA * q + j) + cc] = u[q];
+            buf[C::row(C::NA * q + kb) + cc] = v[q];
+        }
+        __syncthreads();
+        col_pass_a<L, true, C::NA>(buf, tw, L);
+        col_pass_b<L, true>(buf, u, v);
         __syncthreads();
 #pragma unroll
-        for (int rd = 0; rd < C::RB; ++rd) {
-            const int task = rd * C::NT + t;
-            const int cc = task / C::HA, j = task - cc * C::HA;
-#pragma unroll
-            for (int q = 0; q < C::BINS; ++q) {
-                const int u = bin_of<L>(j, q);
-                if (u < Vu) buf[C::row(u) + cc] = zc[rd][q];
-            }
+        for (int q = 0; q < C::NB; ++q) {
+            const int ra = C::NA * q + j, rb = C::NA * q + kb;
+            if (ra < Vu) buf[C::row(ra) + cc] = u[q];
+            if (rb < Vu) buf[C::row(rb) + cc] = v[q];
         }
     }
     __syncthreads();
     // rows: pairs (u, u+1) of Hermitian half spectra -> one complex inverse;
     // real part row u, imaginary part row u+1.
-    const int vpair = (Vu + 1) / 2;
     {
-        const int tasksA = vpair * C::NB;
-        const int rounds = (tasksA + C::NT - 1) / C::NT;
-        for (int rd = 0; rd < rounds; ++rd) {
-            const int task = rd * C::NT + t;
-            const bool act = task < tasksA;
-            const int p = task / C::NB, n1 = task - p * C::NB;
+        const int vpair = (Vu + 1) / 2;
+        // pass A of pair p, element n1: bins k = n1 + NB n2, of which those
+        // above L/2 are the conjugates of L - k and bin 0 of the buffer packs
+        // the real bins 0 and L/2
+        auto pass_a = [&](bool act, int p, int n1) {
             float2 x[C::NA];
+            float2* reg = buf + C::row(2 * p);
             if (act) {
-                const float2* ra = buf + C::row(2 * p);
+                const float2* ra = reg;
                 const float2* rb = ra + C::P;
 #pragma unroll
                 for (int n2 = 0; n2 < C::NA; ++n2) {
                     const int k2 = n1 + C::NB * n2;
-                    float2 ha, hb;
-                    if (k2 == 0) {
-                        ha = make_float2(ra[0].x, 0.f);
-                        hb = make_float2(rb[0].x, 0.f);
-                    } else if (k2 == L / 2) {
-                        ha = make_float2(ra[0].y, 0.f);
-                        hb = make_float2(rb[0].y, 0.f);
-                    } else if (k2 < L / 2) {
-                        ha = ra[k2];
-                        hb = rb[k2];
-                    } else {
-                        ha = cconj(ra[L - k2]);
-                        hb = cconj(rb[L - k2]);
+                    int e = n2 < C::HA ? k2 : L - k2;
+                    if (n2 == C::HA) e = n1 == 0 ? 0 : e;
+                    float2 ha = ra[e], hb = rb[e];
+                    if (n2 >= C::HA) {
+                        ha = cconj(ha);
+                        hb = cconj(hb);
+                    }
+                    if (n2 == 0) {
+                        ha.y = n1 == 0 ? 0.f : ha.y;
+                        hb.y = n1 == 0 ? 0.f : hb.y;
+                    }
+                    if (n2 == C::HA) {   // the packed bin's imaginary parts (negated above)
+                        ha = n1 == 0 ? make_float2(-ha.y, 0.f) : ha;
+                        hb = n1 == 0 ? make_float2(-hb.y, 0.f) : hb;
                     }
                     x[n2] = make_float2(ha.x - hb.y, ha.y + hb.x);
                 }
-                dftn<C::NA, true>(x);
+                dftn<C::NA, kInvRow>(x);
             }
-            pair_sync<C::NB>();   // this pair's reads before its in-place writes
+            pair_sync<C::WL ? 1 : C::NB>();   // this pair's reads before its in-place writes
             if (act) {
-                float2* reg = buf + C::row(2 * p);
 #pragma unroll
                 for (int k2 = 0; k2 < C::NA; ++k2)
-                    reg[k2 * C::NB + C::swz(n1, k2)] = k2 == 0 ? x[0] : cmul(x[k2], cconj(tw[n1 * k2]));
+                    reg[C::slot(n1, k2)] = k2 == 0 ? x[0] : cmul_inv(x[k2], tw[k2 * C::NB + n1]);
             }
+        };
+        if constexpr (C::WL) {
+#pragma unroll 1
+            for (int rd = 0; rd < C::AR; ++rd) {
+                const int q = rd * 64 + (t & 63), p = (t >> 6) * C::PW + C::pm_a(q / C::NB);
+                pass_a(p < vpair, p, q % C::NB);
+            }
+            wave_sync();
+        } else {
+            const int rounds = (vpair * C::NB + C::NT - 1) / C::NT;
+#pragma unroll 1
+            for (int rd = 0; rd < rounds; ++rd) {
+                const int task = rd * C::NT + t, p = task / C::NB;
+                pass_a(p < vpair, p, task - p * C::NB);
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        const float inv = 1.0f / ((float)L * (float)L);
-        const int tasksB = vpair * C::HA;
-        const int roundsB = (tasksB + C::NT - 1) / C::NT;
-        for (int rd = 0; rd < roundsB; ++rd) {
-            const int task = rd * C::NT + t;
-            const bool act = task < tasksB;
-            const int p = task / C::HA, j = task - p * C::HA;
-            float2 u[C::NB], v[C::NB];
-            float2* reg = buf + C::row(2 * p);
-            const int ka = j, kb = j == 0 ? C::HA : C::NA - j;
-            if (act) {
+        // (the forward row passes leave twice each half spectrum)
+        const float inv = 0.25f * (1.0f / ((float)L * (float)L));
+        const int j = t % C::HA, p = (t >> 6) * C::PW + C::pm_b((t & 63) / C::HA);
+        const int ka = j, kb = j == 0 ? C::HA : C::NA - j;
+        const bool act = p < vpair;
+        float2 u[C::NB], v[C::NB];
+        float2* reg = buf + C::row(2 * p);
+        if (act) {
 #pragma unroll
-                for (int n1 = 0; n1 < C::NB; ++n1) {
-                    u[n1] = reg[ka * C::NB + C::swz(n1, ka)];
-                    v[n1] = reg[kb * C::NB + C::swz(n1, kb)];
-                }
-                dftn<C::NB, true>(u);
-                dftn<C::NB, true>(v);
+            for (int n1 = 0; n1 < C::NB; ++n1) {
+                u[n1] = reg[C::slot(n1, ka)];
+                v[n1] = reg[C::slot(n1, kb)];
             }
-            pair_sync<C::HA>();   // this pair's reads before its in-place writes
-            if (act) {
-                float* rr = reinterpret_cast<float*>(reg);   // R[2p][v] at rr[v], R[2p+1][v] at rr[L + v]
+            dftn<C::NB, kInvRow>(u);
+            dftn<C::NB, kInvRow>(v);
+        }
+        wave_sync();   // this pair's reads before its in-place writes
+        if (act) {
+            float* rr = reinterpret_cast<float*>(reg);   // R[2p][v] at rr[v], R[2p+1][v] at rr[L + v]
 #pragma unroll
-                for (int k1 = 0; k1 < C::NB; ++k1) {
-                    const int va = C::NA * k1 + ka, vb = C::NA * k1 + kb;
-                    rr[va] = u[k1].x * inv;
-                    rr[L + va] = u[k1].y * inv;
-                    rr[vb] = v[k1].x * inv;
-                    rr[L + vb] = v[k1].y * inv;
-                }
+            for (int k1 = 0; k1 < C::NB; ++k1) {
+                const int va = C::NA * k1 + ka, vb = C::NA * k1 + kb;
+                rr[va] = u[k1].x * inv;
+                rr[L + va] = u[k1].y * inv;
+                rr[vb] = v[k1].x * inv;
+                rr[L + vb] = v[k1].y * inv;
             }
         }
         __syncthreads();

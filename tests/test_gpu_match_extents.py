@@ -1,4 +1,9 @@
-"""Fast-NCC surfaces at the extents where the match kernels change form."""
+"""Fast-NCC surfaces at the extents where the match kernels change form.
+
+Transforms: windows and templates that end at, just before and just after half
+and three quarters of each transform side (the samples beyond them are not
+read), odd sides (a row pair with one row missing), and the smallest and
+largest of each side."""
 import numpy as np
 import pytest
 
@@ -36,3 +41,16 @@ def test_direct_form_smallest_templates(m, dt):
     """The direct form deals template rows to four waves; a template of three
     rows leaves the fourth none."""
     check_surface(m, 2, dt)
+
+
+# (m, r): windows of side m + 2r
+EXTENTS = [(3, 1), (31, 8), (32, 8), (33, 8), (32, 16), (48, 8), (49, 7),        # side 64
+           (63, 1), (64, 16), (65, 16), (96, 16), (97, 15), (64, 32),            # side 128
+           (79, 40), (80, 40), (81, 39), (120, 20), (121, 19), (64, 48),         # side 160
+           (95, 48), (96, 48), (97, 47), (144, 24), (145, 23), (20, 86)]         # side 192
+
+
+@pytest.mark.parametrize("dt", list(DTYPES))
+@pytest.mark.parametrize("m,r", EXTENTS)
+def test_surface_at_transform_extents(m, r, dt):
+    check_surface(m, r, dt)
