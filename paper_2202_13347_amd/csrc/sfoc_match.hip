@@ -1643,14 +1643,33 @@ __global__ __launch_bounds__(kConsNT) void consistency_kernel(sfoc_cp* cps, cons
 // ---- per-window integral images (Eq. 14-16 over one search window) --------
 // One workgroup per IP: G1 / G2 are the (M+1) x (M+1) exclusive prefix sums
 // of sum_c g and sum_c g^2 (float64, of the stored values) over the IP's
-// M x M search window, zero first row and column.  The per-pixel sums run
-// over the channels in order, then each row is summed left to right and
-// each column top to bottom: a fixed order, so results are reproducible.
-// An IP whose windows leave the images is skipped (the match flags it and
-// reads nothing).
+// M x M search window, zero first row and column.  The window is taken in
+// bands of rows that fit LDS: a wave takes a row, 64 columns at a time (a
+// lane sums its pixel's channels in order, sixteen channels' loads in flight;
+// a scan over the lanes and the carry of the columns before give the row
+// prefix), then a thread per column and map adds the band's rows to the
+// column's running sum and stores them.  Every sum is taken in a fixed order,
+// so results are reproducible.  An IP whose windows leave the images is
+// skipped (the match flags it and reads nothing).
+// Bound by the windows' cache lines (a row of 52 bfloat16 values is 104 bytes
+// of one or two 128-byte lines: 85 MB for 400 IPs at z = 16, 17 us at the rate
+// of a large copy): 92 us with rows and columns walked one element at a time
+// through global memory by one thread each, 24 us in this form (1024 threads:
+// 27 us; eight channels in flight: 25 us).
+constexpr int kWinNT = 512, kWinU = 16;   // threads; channels whose loads are in flight
+constexpr int kWinLds = 48 << 10;   // LDS of a band: three workgroups per CU
+
+// Rows of a band for windows of side M: what fits kWinLds (two float64 maps),
+// at least one row per two waves (at the widest window, M = 1213, 78 KB).
+static int window_band_rows(int M) {
+    const int r = kWinLds / (16 * M);
+    return r < 4 ? 4 : (r > M ? M : r);
+}
+
 template <int DT>
-__global__ __launch_bounds__(256) void window_integral_kernel(const MatchArgs A) {
-    const int i = blockIdx.x, t = threadIdx.x;
+__global__ __launch_bounds__(kWinNT) void window_integral_kernel(const MatchArgs A, int R) {
+    extern __shared__ double band[];   // [map][row][column]
+    const int i = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int m = A.m, r = A.r, M = m + 2 * r, P = M + 1;
     const int py = A.ips[2 * i], px = A.ips[2 * i + 1];
     const int pry = A.prior ? A.prior[2 * i] : 0, prx = A.prior ? A.prior[2 * i + 1] : 0;
@@ -1660,40 +1679,89 @@ __global__ __launch_bounds__(256) void window_integral_kernel(const MatchArgs A)
     double* __restrict__ G1 = const_cast<double*>(A.integ1) + (int64_t)i * P * P;
     double* __restrict__ G2 = const_cast<double*>(A.integ2) + (int64_t)i * P * P;
     const int64_t plane = A.Hr * A.Wr;
-    for (int e = t; e < P * P; e += 256) {
-        const int y = e / P, x = e - y * P;
-        double s1 = 0.0, s2 = 0.0;
-        if (y > 0 && x > 0) {
-            const int o = (int)((sy + y - 1) * A.Wr + sx + x - 1);   // within one plane (< 2^30)
-            for (int h = 0; h < A.z; ++h) {
-                const double g = (double)ldd<DT>(elem_ptr<DT>(A.desc_ref, h * plane), o);
-                s1 += g;
-                s2 = fma(g, g, s2);
+    for (int e = t; e < P; e += kWinNT) {
+        G1[e] = G2[e] = 0.0;
+        G1[(int64_t)e * P] = G2[(int64_t)e * P] = 0.0;
+    }
+    // column work item: map q, column x; its running sum (one item per thread
+    // up to M = 256, up to five for the widest window)
+    constexpr int kItems = 5;
+    double run[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) run[k] = 0.0;
+    for (int y0 = 0; y0 < M; y0 += R) {
+        const int rows = min(R, M - y0);
+        for (int y = wv; y < rows; y += kWinNT / 64) {
+            double c1 = 0.0, c2 = 0.0;   // sums of the columns before this chunk
+            for (int x0 = 0; x0 < M; x0 += 64) {
+                const int x = x0 + lane;
+                const bool ok = x < M;
+                const int o = (int)((sy + y0 + y) * A.Wr + sx + min(x, M - 1));   // within one plane (< 2^30)
+                double s1 = 0.0, s2 = 0.0;
+                for (int h0 = 0; h0 < A.z; h0 += kWinU) {
+                    float g[kWinU];
+#pragma unroll
+                    for (int k = 0; k < kWinU; ++k)
+                        g[k] = ldd<DT>(elem_ptr<DT>(A.desc_ref, (int64_t)min(h0 + k, A.z - 1) * plane), o);
+#pragma unroll
+                    for (int k = 0; k < kWinU; ++k)
+                        if (h0 + k < A.z) {
+                            const double d = (double)g[k];
+                            s1 += d;
+                            s2 = fma(d, d, s2);
+                        }
+                }
+                s1 = ok ? s1 : 0.0;
+                s2 = ok ? s2 : 0.0;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const double u1 = __shfl_up(s1, d, 64), u2 = __shfl_up(s2, d, 64);
+                    if (lane >= d) {
+                        s1 += u1;
+                        s2 += u2;
+                    }
+                }
+                s1 += c1;
+                s2 += c2;
+                if (ok) {
+                    band[y * M + x] = s1;
+                    band[(R + y) * M + x] = s2;
+                }
+                c1 = __shfl(s1, 63, 64);
+                c2 = __shfl(s2, 63, 64);
             }
         }
-        G1[e] = s1;
-        G2[e] = s2;
-    }
-    __syncthreads();
-    for (int y = 1 + t; y < P; y += 256) {   // rows, left to right
-        double a = 0.0, b = 0.0;
-        for (int x = 1; x < P; ++x) {
-            a += G1[(int64_t)y * P + x];
-            b += G2[(int64_t)y * P + x];
-            G1[(int64_t)y * P + x] = a;
-            G2[(int64_t)y * P + x] = b;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const int e = t + k * kWinNT;
+            if (e < 2 * M) {
+                const int q = e >= M, x = e - q * M;
+                const double* b = band + q * R * M + x;
+                double* g = (q ? G2 : G1) + (int64_t)(y0 + 1) * P + x + 1;
+                double a = run[k];
+#pragma unroll 4
+                for (int y = 0; y < rows; ++y) {
+                    a += b[y * M];
+                    g[(int64_t)y * P] = a;
+                }
+                run[k] = a;
+            }
         }
+        __syncthreads();
     }
-    __syncthreads();
-    for (int x = 1 + t; x < P; x += 256) {   // columns, top to bottom
-        double a = 0.0, b = 0.0;
-        for (int y = 1; y < P; ++y) {
-            a += G1[(int64_t)y * P + x];
-            b += G2[(int64_t)y * P + x];
-            G1[(int64_t)y * P + x] = a;
-            G2[(int64_t)y * P + x] = b;
-        }
-    }
+}
+
+template <int DT>
+static hipError_t launch_window_integral(const MatchArgs& a, hipStream_t st) {
+    const int M = a.m + 2 * a.r, R = window_band_rows(M);
+    static_assert(5 * kWinNT >= 2 * (kMaxTemplate + 2 * kMaxRadiusMatch), "a column item for every column");
+    const int lds = 2 * R * M * (int)sizeof(double);
+    auto kern = window_integral_kernel<DT>;
+    hipError_t e = ensure_dynamic_lds((const void*)kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.n), dim3(kWinNT), lds, st, a, R);
+    return hipGetLastError();
 }
 
 // ---- launch -------------------------------------------------------------
@@ -1876,11 +1944,10 @@ hipError_t launch_match(const void* desc_sen, int64_t Hs, int64_t Ws, const void
         a.integ2 = g + (size_t)n * per;
         a.integ_win = 1;
         trace_begin(st, SFOC_K_INTEGRAL);
-        if (dtype == 0) hipLaunchKernelGGL(window_integral_kernel<0>, dim3(n), dim3(256), 0, st, a);
-        else if (dtype == 1) hipLaunchKernelGGL(window_integral_kernel<1>, dim3(n), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(window_integral_kernel<2>, dim3(n), dim3(256), 0, st, a);
+        e = dtype == 0 ? launch_window_integral<0>(a, st)
+                       : dtype == 1 ? launch_window_integral<1>(a, st) : launch_window_integral<2>(a, st);
         trace_end(st, SFOC_K_INTEGRAL);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (e != hipSuccess) return e;
     }
     switch (L) {
         case 64: e = launch_match_side<64>(a, dtype, st); break;

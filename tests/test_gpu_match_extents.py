@@ -54,3 +54,28 @@ EXTENTS = [(3, 1), (31, 8), (32, 8), (33, 8), (32, 16), (48, 8), (49, 7),       
 @pytest.mark.parametrize("m,r", EXTENTS)
 def test_surface_at_transform_extents(m, r, dt):
     check_surface(m, r, dt)
+
+
+@pytest.mark.parametrize("m,r", [(5, 30), (9, 92), (100, 100), (30, 300)])
+def test_window_integrals_at_wide_windows(m, r):
+    """Integral images per window at one, several and many bands of rows and
+    more columns than a wave, against those of the whole reference image."""
+    print("window integrals", m, r, flush=True)
+    g = torch.Generator().manual_seed(m + r)
+    size = m + 2 * r + 5
+    d = torch.rand(6, size, size, generator=g).cuda()
+    s = torch.rand(6, size, size, generator=g).cuda()
+    lo = m // 2 + r
+    ips = torch.tensor([[lo, lo], [lo + 3, lo + 5]], dtype=torch.int32).cuda()
+    I = []
+    for k in (1, 2):
+        i = torch.zeros(size + 1, size + 1, dtype=torch.float64, device="cuda")
+        i[1:, 1:] = (d.double() ** k).sum(0).cumsum(0).cumsum(1)
+        I.append(i)
+    cw, nw = S.fastncc_match(s, d, None, None, ips, m, r, want_ncc=True)
+    cg, ng = S.fastncc_match(s, d, I[0], I[1], ips, m, r, want_ncc=True)
+    torch.cuda.synchronize()
+    # the box sums differ by float64 rounding of sums of up to 6 size^2 values (relative 1e-12),
+    # the variances (their difference, at least 1e-3 of the sums here) by 1e-9 at most
+    assert float((nw - ng).abs().max()) <= 1e-6
+    assert torch.equal(cw[:, :4], cg[:, :4])
