@@ -7,20 +7,23 @@
 //     largest threshold at which 9 contiguous pixels of the radius-3 circle
 //     are all brighter, or all darker, than the centre) for the tile and a
 //     1-pixel ring; then 3 x 3 non-maximum suppression with a raster-order
-//     tie rule.  Kept corners are sparse: their strengths go to a map in
-//     the workspace (other entries are never written), and a bit mask, one
-//     32-bit word per row of a tile (from a wave ballot: a wave covers two
-//     tile rows), marks them.
-//     Per pixel the 16 arc minima and maxima of the 16 circle differences
-//     come from a doubling network (pairs, fours, eights, then the ninth
-//     element): 64 min and 64 max instead of 128 each.  Only float32
-//     subtractions and min / max are involved, so V is exact.
+//     tie rule.  Kept corners are sparse: a bit mask, one 32-bit word per
+//     row of a tile (from wave ballots), marks them, and their strengths go
+//     to a list per tile in raster order; with its bits a mask word holds the
+//     place in that list of its first corner.  (A map of the image, written
+//     and read at the corners alone, moved a cache line per corner.)
+//     Bound by the three-operand minima and maxima, about 80 a pixel and
+//     13 % of ring pixels (min / max do not fuse: one a lane and cycle).
+//     Only float32 subtractions and min / max are involved, so V is exact.
 //  2. selection, one workgroup per block: the threads walk the block's mask
-//     words, read the strengths of the set bits, and each keeps the best
-//     K >= per_block corners it sees as sorted 64-bit keys (strength
-//     descending, raster index within the block ascending) in registers; a
-//     bitonic sort of all threads' lists in LDS gives the block's first
-//     per_block.
+//     words, read the strengths of the set bits from the tiles' lists, and
+//     each keeps the best K >= per_block corners it sees as sorted 64-bit keys
+//     (strength descending, raster index within the block ascending) in
+//     registers; a bitonic sort of all threads' lists in LDS (K = 1: a
+//     minimum) gives the block's first per_block.
+// 10000 x 10000 pixels, 71 x 71 blocks of one point: strength 580 -> 385 us
+// (149 -> 96 VALU instructions a pixel, four pixels a tile load, branch-free
+// suppression), selection 98 -> 40 us (lists instead of the map).
 //  3. compaction (one workgroup): block counts prefix-summed, each block's
 //     interest points copied to its place in one list.
 #include <hip/hip_runtime.h>
@@ -38,6 +41,9 @@ namespace fast {
 
 constexpr int kTS = 32, kHalo = 4, kIS = kTS + 2 * kHalo, kVS = kTS + 2;   // tile, image and strength sides
 constexpr int kNT = 256;
+// Corners a tile can keep: no two are neighbours (of two, the later one would
+// have to be larger and the earlier one not smaller), so one per 2 x 2 block.
+constexpr int kTileMax = kTS * kTS / 4;
 constexpr int kSelNT = 256, kMaxPer = 32, kMaxBlocks = 1 << 16;
 constexpr int kCompNT = 1024;
 
@@ -58,51 +64,79 @@ SFOC_DEV int bound(int lo, int n, int i, int nb) { return lo + (int)(((int64_t)i
 constexpr int kCy[16] = {-3, -3, -2, -1, 0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3};
 constexpr int kCx[16] = {0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3, -3, -3, -2, -1};
 
+// Three-operand minimum and maximum (one instruction each; exact).
+SFOC_DEV float min3(float a, float b, float c) { return fminf(fminf(a, b), c); }
+SFOC_DEV float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+
+// Largest of the 16 values (eight instructions).
+template <typename F>
+SFOC_DEV float fold16(const float (&x)[16], F&& f) {
+    return f(f(f(x[0], x[1], x[2]), f(x[3], x[4], x[5]), f(x[6], x[7], x[8])), f(x[9], x[10], x[11]),
+             f(x[12], f(x[13], x[14], x[15]), x[15]));
+}
+
+// V from the circle's raw values: subtraction rounds monotonically, so the
+// minimum (maximum) over an arc of the rounded differences is the rounded
+// difference of the arc's minimum (maximum), and the maximum over the arcs of
+// those likewise.  The arcs of nine are three arcs of three: 32 three-operand
+// minima and 32 maxima for the 16 arcs, then 16 to fold them.
 SFOC_DEV float strength(const float* tile, int ty, int tx) {
     const float* nb = tile + (ty - 3) * kIS + (tx - 3);
     const float c = nb[3 * kIS + 3];
-    float u[16];
+    float p[16], mn[16], mx[16], lo[16], hi[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) u[i] = nb[(kCy[i] + 3) * kIS + kCx[i] + 3] - c;
-    // windows of 9 starting at k (cyclic): min / max of u[k .. k+8]
-    float mn2[16], mx2[16], mn4[16], mx4[16], mn8[16], mx8[16];
+    for (int i = 0; i < 16; ++i) p[i] = nb[(kCy[i] + 3) * kIS + kCx[i] + 3];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        mn2[i] = fminf(u[i], u[(i + 1) & 15]);
-        mx2[i] = fmaxf(u[i], u[(i + 1) & 15]);
+        mn[i] = min3(p[i], p[(i + 1) & 15], p[(i + 2) & 15]);
+        mx[i] = max3(p[i], p[(i + 1) & 15], p[(i + 2) & 15]);
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        mn4[i] = fminf(mn2[i], mn2[(i + 2) & 15]);
-        mx4[i] = fmaxf(mx2[i], mx2[(i + 2) & 15]);
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        mn8[i] = fminf(mn4[i], mn4[(i + 4) & 15]);
-        mx8[i] = fmaxf(mx4[i], mx4[(i + 4) & 15]);
-    }
-    float v = -INFINITY;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        const float lo = fminf(mn8[k], u[(k + 8) & 15]);    // min over the arc of (I_x - I_p)
-        const float hi = fmaxf(mx8[k], u[(k + 8) & 15]);    // so min over the arc of (I_p - I_x) = -hi
-        v = fmaxf(v, fmaxf(lo, -hi));
+        lo[k] = min3(mn[k], mn[(k + 3) & 15], mn[(k + 6) & 15]);
+        hi[k] = max3(mx[k], mx[(k + 3) & 15], mx[(k + 6) & 15]);
     }
-    return v;
+    const float bright = fold16(lo, [](float a, float b, float d) { return max3(a, b, d); });
+    const float dark = fold16(hi, [](float a, float b, float d) { return min3(a, b, d); });
+    return fmaxf(bright - c, c - dark);
 }
 
 __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__ img, int64_t ld, Region R,
                                                        float thr, float* __restrict__ S,
-                                                       uint32_t* __restrict__ mask, int mask_words, int tiles_x) {
+                                                       uint2* __restrict__ mask, int mask_words, int tiles_x) {
     static_assert(kTS == 32 && kNT % 64 == 0, "a wave covers two tile rows");
-    __shared__ float tile[kIS * kIS];
+    __shared__ __align__(16) float tile[kIS * kIS];
     __shared__ float vs[kVS * kVS];
+    __shared__ int wcount[kNT / 64];
     const int t = threadIdx.x, lane = t & 63;
     const int ty0 = (blockIdx.x / tiles_x) * kTS, tx0 = (blockIdx.x % tiles_x) * kTS;
-    for (int e = t; e < kIS * kIS; e += kNT) {
-        const int a = e / kIS, c = e - a * kIS;
-        const int y = ty0 - kHalo + a, x = tx0 - kHalo + c;
-        tile[e] = (y >= 0 && y < R.H && x >= 0 && x < R.W) ? img[(int64_t)y * ld + x] : 0.f;
+    {   // every load of the tile first, then the stores; pixels outside the
+        // image (only tiles at its border have any) read as zero
+        constexpr int kLoads = (kIS * kIS + kNT - 1) / kNT;
+        const int y0 = ty0 - kHalo, x0 = tx0 - kHalo;
+        const bool inside = y0 >= 0 && x0 >= 0 && y0 + kIS <= R.H && x0 + kIS <= R.W;
+        const float* src = img + (int64_t)y0 * ld + x0;
+        if (inside && (ld & 3) == 0 && ((uintptr_t)src & 15) == 0) {
+            // four pixels a load: a tenth of the address arithmetic
+            constexpr int kQ = kIS / 4, kQuads = kIS * kQ;
+            static_assert(kIS % 4 == 0 && kQuads <= 2 * kNT, "two rounds of four pixels");
+            const int e1 = min(t + kNT, kQuads - 1);
+            const float4 v0 = *reinterpret_cast<const float4*>(src + (int64_t)(t / kQ) * ld + 4 * (t % kQ));
+            const float4 v1 = *reinterpret_cast<const float4*>(src + (int64_t)(e1 / kQ) * ld + 4 * (e1 % kQ));
+            reinterpret_cast<float4*>(tile)[t] = v0;
+            if (t + kNT < kQuads) reinterpret_cast<float4*>(tile)[t + kNT] = v1;
+        } else {
+            float v[kLoads];
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k) {
+                const int e = min(t + k * kNT, kIS * kIS - 1), a = e / kIS, c = e - a * kIS;
+                const int y = y0 + a, x = x0 + c;
+                v[k] = (y >= 0 && y < R.H && x >= 0 && x < R.W) ? img[(int64_t)y * ld + x] : 0.f;
+            }
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k)
+                if (t + k * kNT < kIS * kIS) tile[t + k * kNT] = v[k];
+        }
     }
     __syncthreads();
     // strengths of the tile and a 1-pixel ring; -inf outside the region
@@ -113,24 +147,47 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
         vs[e] = in ? strength(tile, a + kHalo - 1, c + kHalo - 1) : -INFINITY;
     }
     __syncthreads();
-    // every lane runs every pass (the ballot needs the whole wave); a pass
-    // of wave w covers tile rows 2w + 8 pass and the row after it
-    for (int e = t; e < kTS * kTS; e += kNT) {
-        const int a = e / kTS, c = e - a * kTS;
-        const int y = ty0 + a, x = tx0 + c;
-        bool keep = false;
-        float v = 0.f;
-        if (y >= R.b && y < R.H - R.b && x >= R.b && x < R.W - R.b) {
-            const float* q = vs + (a + 1) * kVS + (c + 1);
-            v = q[0];
-            keep = v > thr;
-            // neighbours before in raster order: strictly smaller; after: not larger
-            keep = keep && v > q[-kVS - 1] && v > q[-kVS] && v > q[-kVS + 1] && v > q[-1];
-            keep = keep && v >= q[1] && v >= q[kVS - 1] && v >= q[kVS] && v >= q[kVS + 1];
+    // Thread t suppresses column t % 32 of rows 4 (t / 32) .. + 3, so a wave
+    // covers two groups of four rows; every lane takes part in the ballots.
+    // Neighbours before in raster order: strictly smaller; after: not larger.
+    {
+        constexpr int kRows = kTS * kTS / kNT;
+        const int c = t % kTS, a0 = (t / kTS) * kRows;
+        const float* q = vs + a0 * kVS + c;   // the 3 x 3 block of the first pixel, from its top left
+        float l[kRows + 2], m[kRows + 2], r[kRows + 2];
+#pragma unroll
+        for (int k = 0; k < kRows + 2; ++k) {
+            l[k] = q[k * kVS];
+            m[k] = q[k * kVS + 1];
+            r[k] = q[k * kVS + 2];
         }
-        if (keep) S[(int64_t)y * R.W + x] = v;
-        const uint64_t bal = __ballot(keep);
-        if ((lane & 31) == 0 && y < R.H) mask[(int64_t)y * mask_words + tx0 / kTS] = (uint32_t)(bal >> (lane & 32));
+        bool keep[kRows];
+        uint64_t bal[kRows];
+        int before_lo = 0, before_hi = 0;   // kept corners of the wave's first and second group
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+            const float v = m[k + 1];
+            const float before = fmaxf(max3(l[k], m[k], r[k]), l[k + 1]);
+            const float after = fmaxf(max3(l[k + 2], m[k + 2], r[k + 2]), r[k + 1]);
+            // (a strength outside the region is -inf, below any threshold)
+            keep[k] = v > thr && v > before && v >= after;
+            bal[k] = __ballot(keep[k]);
+            before_lo += __popc((uint32_t)bal[k]);
+            before_hi += __popc((uint32_t)(bal[k] >> 32));
+        }
+        if (lane == 0) wcount[t >> 6] = before_lo + before_hi;
+        __syncthreads();
+        int base = 0;   // kept corners of the tile's rows before this thread's group
+        for (int w = 0; w < kNT / 64; ++w) base += w < (t >> 6) ? wcount[w] : 0;
+        if (lane & 32) base += before_lo;
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+            const int y = ty0 + a0 + k;
+            const uint32_t bits = (uint32_t)(bal[k] >> (lane & 32));
+            if (keep[k]) S[(int64_t)blockIdx.x * kTileMax + base + __popc(bits & ((1u << c) - 1u))] = m[k + 1];
+            if (c == 0 && y < R.H) mask[(int64_t)y * mask_words + tx0 / kTS] = make_uint2(bits, (uint32_t)base);
+            base += __popc(bits);
+        }
     }
 }
 
@@ -143,7 +200,7 @@ SFOC_DEV uint64_t make_key(float v, uint32_t e) {
 
 template <int K>
 __global__ __launch_bounds__(kSelNT) void select_kernel(const float* __restrict__ S,
-                                                        const uint32_t* __restrict__ mask, int mask_words, Region R,
+                                                        const uint2* __restrict__ mask, int mask_words, Region R,
                                                         Blocks B, int32_t* __restrict__ bips,
                                                         float* __restrict__ bsc, int32_t* __restrict__ bcnt) {
     extern __shared__ uint64_t keys[];   // kSelNT * K
@@ -161,30 +218,33 @@ __global__ __launch_bounds__(kSelNT) void select_kernel(const float* __restrict_
     for (int i = 0; i < K; ++i) best[i] = ~0ull;
     constexpr int kU = 4;   // mask loads in flight per thread
     for (int q0 = t; q0 < nwords; q0 += kU * kSelNT) {
-        uint32_t m[kU];
+        uint2 m[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int q = q0 + u * kSelNT;
-            m[u] = 0u;
+            m[u] = make_uint2(0u, 0u);
             if (q < nwords) {
                 const int a = q / nw, wi = q - a * nw;
                 const int xw = 32 * (w0 + wi);
-                uint32_t bits = mask[(int64_t)(y0 + a) * mask_words + w0 + wi];
+                const uint2 e = mask[(int64_t)(y0 + a) * mask_words + w0 + wi];
+                uint32_t bits = e.x;
                 if (xw < x0) bits &= ~0u << (x0 - xw);                              // columns before the block
                 if (x1 - xw < 32) bits &= (1u << (x1 - xw)) - 1u;                   // columns after it
-                m[u] = bits;
+                // with the place of the first corner that is left in the tile's list
+                m[u] = make_uint2(bits, bits ? e.y + __popc(e.x & ((1u << (__ffs(bits) - 1)) - 1u)) : 0u);
             }
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            uint32_t bits = m[u];
+            uint32_t bits = m[u].x;
             if (!bits) continue;
             const int q = q0 + u * kSelNT;
-            const int a = q / nw, xw = 32 * (w0 + q - a * nw);
+            const int a = q / nw, wi = q - a * nw, xw = 32 * (w0 + wi);
+            const float* list = S + ((int64_t)((y0 + a) / kTS) * mask_words + w0 + wi) * kTileMax + m[u].y;
             while (bits) {
                 const int x = xw + __ffs(bits) - 1;
                 bits &= bits - 1u;
-                const float v = S[(int64_t)(y0 + a) * R.W + x];
+                const float v = *list++;
                 const uint64_t k = make_key(v, (uint32_t)a * (uint32_t)bw + (uint32_t)(x - x0));
                 if (k >= best[K - 1]) continue;
                 // sorted insertion with compile-time indices
@@ -194,11 +254,24 @@ __global__ __launch_bounds__(kSelNT) void select_kernel(const float* __restrict_
             }
         }
     }
+    if constexpr (K == 1) {   // one point a block: the smallest key, a butterfly and then the waves
+        uint64_t k = best[0];
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint64_t o = __shfl_xor(k, d, 64);
+            k = o < k ? o : k;
+        }
+        if ((t & 63) == 0) keys[t >> 6] = k;
+        __syncthreads();
+        if (t == 0)
+            for (int w = 1; w < kSelNT / 64; ++w) keys[0] = keys[w] < keys[0] ? keys[w] : keys[0];
+    } else {
 #pragma unroll
     for (int i = 0; i < K; ++i) keys[t * K + i] = best[i];
+    }
     __syncthreads();
     // bitonic sort, ascending, of kSelNT * K keys
-    constexpr int N = kSelNT * K;
+    constexpr int N = K == 1 ? 1 : kSelNT * K;
     for (int size = 2; size <= N; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
             for (int i = t; i < N / 2; i += kSelNT) {
@@ -278,8 +351,8 @@ Layout layout(int64_t H, int64_t W, int nblocks, int per) {
         return at;
     };
     L.mask_words = (int)((W + kTS - 1) / kTS);
-    L.smap = take(sizeof(float) * (size_t)H * (size_t)W);
-    L.mask = take(sizeof(uint32_t) * (size_t)H * L.mask_words);
+    L.smap = take(sizeof(float) * kTileMax * (size_t)((H + kTS - 1) / kTS) * L.mask_words);
+    L.mask = take(sizeof(uint2) * (size_t)H * L.mask_words);
     L.bips = take(sizeof(int32_t) * 2 * (size_t)nblocks * per);
     L.bsc = take(sizeof(float) * (size_t)nblocks * per);
     L.bcnt = take(sizeof(int32_t) * (size_t)nblocks);
@@ -296,7 +369,7 @@ int check(int64_t H, int64_t W, int nby, int nbx, int per) {
 }
 
 template <int K>
-hipError_t launch_select(const float* S, const uint32_t* mask, int mask_words, Region R, Blocks B, int32_t* bips,
+hipError_t launch_select(const float* S, const uint2* mask, int mask_words, Region R, Blocks B, int32_t* bips,
                          float* bsc, int32_t* bcnt, hipStream_t st) {
     const size_t lds = sizeof(uint64_t) * kSelNT * K;
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&select_kernel<K>), lds);
@@ -332,7 +405,7 @@ extern "C" int sfoc_detect_ips(const float* img, int64_t H, int64_t W, int64_t l
     if (ws_bytes < L.total) return SFOC_E_WORKSPACE;
     char* w = (char*)ws;
     float* S = (float*)(w + L.smap);
-    uint32_t* mask = (uint32_t*)(w + L.mask);
+    uint2* mask = (uint2*)(w + L.mask);
     int32_t* bips = (int32_t*)(w + L.bips);
     float* bsc = (float*)(w + L.bsc);
     int32_t* bcnt = (int32_t*)(w + L.bcnt);
