@@ -1,12 +1,10 @@
 // Learned CP-validity / sub-pixel head: features from the NCC surfaces,
 // network forward, backward and Adam, and the inference decision.
 //
-// The network is small next to the matching (about 4 Mflop per sample), so
-// the kernels favour simple, fixed-order arithmetic: one thread per output
-// pixel with all 32 output channels in registers and the (bfloat16-rounded,
-// transposed) weights read as wave-uniform scalars; weight gradients are
-// per-chunk partial sums reduced in a fixed order, so every result is
-// bit-reproducible.
+// A launch of one workgroup per sample carries each sample through the whole
+// network (and back, in training) in LDS on the FP32 matrix cores; a second
+// launch sums the weight gradients over the batch and applies Adam.  Every sum
+// is taken in a fixed order, so every result is bit-reproducible.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -33,136 +31,332 @@ static_assert(kNParams == SFOC_HEAD_PARAMS, "parameter layout");
 constexpr float kLambda = 4.0f, kBeta = 0.1f, kClip = 1.5f;
 constexpr int kMaxN = 65536;
 
-SFOC_DEV float bf16_round(float w) { return bf16_bits_to_f32(f32_to_bf16_bits(w)); }
+// To bfloat16 (nearest even) and back, by the conversion instruction.
+SFOC_DEV float bf16_round(float w) { return static_cast<float>(static_cast<__bf16>(w)); }
+// The thread index laundered through an empty asm: what a phase derives from
+// it is recomputed there instead of being hoisted out of the sample loop and
+// kept in registers across the other phases.
+SFOC_DEV int tid_here() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 
-// ---- weights: rounded copies in the layouts the kernels read ------------
-// wf[k]: [c][i][j][o] (forward, o fastest); wb[k]: [o][i][j][c] (backward
-// data, c fastest); fc1q, fc2q: [o][k] as stored.
-struct QWeights {
-    float* wf[4];
-    float* wb[4];
-    float* fc1q;
-    float* fc2q;
+// ---- network: one workgroup per sample ---------------------------------------
+// A sample's whole pass runs in LDS: nothing but the crop and the parameters
+// is read from HBM, and in training nothing but the sample's weight-gradient
+// partials and the small vectors of the fully connected layers is written.
+// The convolutions, their data gradients and their weight gradients are
+// products on the FP32 matrix cores (16 x 16 x 4: FP32 operands and sums):
+//   forward        D[o][pos]  = sum over (tap, c) of W[o][c][tap] in[c][S pos + tap]
+//   data gradient  D[c][pos]  = sum over (tap, o) of W[o][c][tap] g[o][(pos - tap) / S],
+//                  one product per parity class of the position (its taps)
+//   weight grad.   D[o][c]    = sum over pos of g[o][pos] in[c][S pos + tap], per tap
+// The input of conv2 (32 x 33 x 33 floats) would fill the LDS, so conv2 works
+// in three bands of output rows and conv1 is computed per band, again in the
+// backward pass (9 of 290 multiply-adds a sample).  Every sum has a fixed
+// order: results are bit-reproducible.
+// What bounds it: with one workgroup a CU, the LDS reads and the barriers
+// between phases; the matrix-core instructions alone (10.8 k of 32 cycles a
+// sample in training, a quarter of them on each SIMD) are 36 us.  A training
+// step of 256 samples took 2043 us with a thread per output pixel (or weight)
+// and every activation in HBM, 166 us now (this launch 155 us of it, the update
+// 10 us); the forward pass of 400 samples 153 us and 81 us (two rounds of 256
+// CUs; without conv2 46 us, without the other phases 67 to 78 us each).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kNetNT = 512, kWaves = kNetNT / 64;
+constexpr int kWP = 40;                          // LDS pitch of W[(tap, c)][o] (four rows on 32 banks)
+constexpr int kBandRows = 6, kBands = 3;         // conv2 output rows per band
+constexpr int kBR = 2 * kBandRows + 1;           // a1 rows of a band
+// LDS planes (floats per channel) and row pitches, with a border of zeros
+// where the next layer reads past the map.  Odd planes: the 16 channels that
+// a matrix operand spans fall on different banks.
+constexpr int kP1 = kS1 + 2, kL1 = kBR * kP1;    // a1 band: columns -1 .. 33
+constexpr int kP2 = kS2 + 2, kL2 = kP2 * kP2;    // a2 (later its gradient), rows and columns -1 .. 17
+constexpr int kP3 = kS3 + 2, kL3 = kP3 * kP3;
+constexpr int kL4 = kS4 * kS4;
+constexpr int kPC = kS0 + 2;                     // crop, rows and columns -1 .. 33
+static_assert(kL1 % 2 == 1 && kL2 % 2 == 1 && kL3 % 2 == 1 && kL4 % 2 == 1, "odd planes");
+constexpr int kConvParams = kF1;                 // conv1..conv4 weights and biases: a prefix of the vector
+struct NetLds {
+    float w[9 * kCh * kWP];     // the layer's rounded weights [(tap, c)][o]
+    float a2[kCh * kL2];
+    union {
+        float a1[kCh * kL1];
+        struct {
+            float a3[kCh * kL3];
+            float a4[kFlat];
+        };
+    };
+    float crop[kPC * kPC + 3];
+    float w1[9 * kCh];          // conv1 weights [tap][o]
+    float h1[kCh], dh1[kCh], out[4], dout[4], stats[kNStat];
+    int job;
 };
+static_assert(sizeof(NetLds) <= 160 * 1024 && kWaves * kCh * 16 <= kCh * kL1, "LDS of a CU; the wave sums fit a1");
 
-__global__ void prep_weights_kernel(const float* __restrict__ th, QWeights q) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nconv1 = kCh * 9, nconv = kCh * kCh * 9;
-    if (e < nconv1) {   // conv1: o = e / 9, tap = e % 9 (one input channel)
-        const int o = e / 9, tap = e - o * 9;
-        const float w = bf16_round(th[kW1 + e]);
-        q.wf[0][tap * kCh + o] = w;
-        q.wb[0][o * 9 + tap] = w;
-        return;
-    }
-    int f = e - nconv1;
-    if (f < 3 * nconv) {
-        const int k = 1 + f / nconv;
-        const int g = f - (k - 1) * nconv;
-        const int o = g / (kCh * 9), rem = g - o * kCh * 9, c = rem / 9, tap = rem - c * 9;
-        const int base = k == 1 ? kW2 : k == 2 ? kW3 : kW4;
-        const float w = bf16_round(th[base + g]);
-        q.wf[k][(c * 9 + tap) * kCh + o] = w;
-        q.wb[k][(o * 9 + tap) * kCh + c] = w;
-        return;
-    }
-    f -= 3 * nconv;
-    if (f < kCh * kFcIn) {
-        q.fc1q[f] = bf16_round(th[kF1 + f]);
-        return;
-    }
-    f -= kCh * kFcIn;
-    if (f < 3 * kCh) q.fc2q[f] = bf16_round(th[kF2 + f]);
+SFOC_DEV f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// One layer's weights (32 x 32 x 9): loaded into registers ahead of the phase
+// before, then rounded to bfloat16 into w[(tap, c)][o].
+constexpr int kWRegs = kCh * kCh * 9 / kNetNT;
+static_assert(kWRegs * kNetNT == kCh * kCh * 9, "whole rounds");
+SFOC_DEV void load_weights(const float* __restrict__ th, float (&v)[kWRegs]) {
+#pragma unroll
+    for (int k = 0; k < kWRegs; ++k) v[k] = th[threadIdx.x + k * kNetNT];
 }
-constexpr int kPrepCount = kCh * 9 + 3 * kCh * kCh * 9 + kCh * kFcIn + 3 * kCh;
+SFOC_DEV void stage_weights(const float (&v)[kWRegs], float* w) {
+    const int t = tid_here();
+#pragma unroll
+    for (int k = 0; k < kWRegs; ++k) {
+        const int e = t + k * kNetNT, o = e / (kCh * 9), rem = e - o * kCh * 9, c = rem / 9, tap = rem - c * 9;
+        w[(tap * kCh + c) * kWP + o] = bf16_round(v[k]);
+    }
+}
 
-// ---- convolution forward --------------------------------------------------
-// out[b][o][y][x] = relu(bias[o] + sum_{c,i,j} w[o][c][i][j] in[b][c][S y + i - 1][S x + j - 1]).
-// One thread per output pixel with the 32 output channels in registers; the
-// layer's weights are staged in LDS once per workgroup (read back as
-// wave-uniform broadcasts) and the input loads of several channels are
-// issued together.
-constexpr int kOG = 4;            // output-channel groups per pixel
-constexpr int kOPG = kCh / kOG;   // output channels per thread
-template <int CIN, int S, int HIN, int HOUT>
-__global__ __launch_bounds__(256) void conv_fwd_kernel(const float* __restrict__ in, const float* __restrict__ wf,
-                                                       const float* __restrict__ bias, float* __restrict__ out,
-                                                       int B) {
-    __shared__ float4 sw[CIN * 9 * kCh / 4];
-    for (int e = threadIdx.x; e < CIN * 9 * kCh / 4; e += 256) sw[e] = reinterpret_cast<const float4*>(wf)[e];
-    __syncthreads();
-    // thread -> (output pixel, group of kOPG output channels); the groups of
-    // a pixel are adjacent lanes, so their input loads coincide
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * HOUT * HOUT * kOG) return;
-    const int g = idx % kOG, pix = idx / kOG;
-    const int b = pix / (HOUT * HOUT), p = pix - b * HOUT * HOUT;
-    const int y = p / HOUT, x = p - y * HOUT;
-    float acc[kOPG];
+// conv1 (+ ReLU) for the a1 rows r0 .. r0 + kBR - 1 into the band; rows and
+// columns outside the map are zero.  Lane o of a half-wave owns output channel
+// o and slides along a row.
+SFOC_DEV void conv1_band(NetLds& S, const float* __restrict__ th, int r0) {
+    const int t = tid_here(), o = t % kCh, grp = t / kCh;
+    constexpr int kGrps = kNetNT / kCh, kSeg = 11, kSegs = kS1 / kSeg;
+    float w[9];
 #pragma unroll
-    for (int o = 0; o < kOPG; ++o) acc[o] = bias[g * kOPG + o];
-    int off[9];
-    bool ok[9];
+    for (int k = 0; k < 9; ++k) w[k] = S.w1[k * kCh + o];
+    const float bias = th[kB1 + o];
+    for (int q = grp; q < kBR * kSegs; q += kGrps) {
+        const int rr = q / kSegs, x0 = (q - rr * kSegs) * kSeg, y = r0 + rr;
+        float* dst = S.a1 + o * kL1 + rr * kP1 + 1 + x0;
+        if (x0 == 0) dst[-1] = 0.f;
+        if (x0 + kSeg == kS1) dst[kSeg] = 0.f;
+        if (y < 0 || y >= kS1) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const int yy = S * y + i - 1, xx = S * x + j - 1;
-            ok[i * 3 + j] = yy >= 0 && yy < HIN && xx >= 0 && xx < HIN;
-            off[i * 3 + j] = ok[i * 3 + j] ? yy * HIN + xx : 0;
+            for (int x = 0; x < kSeg; ++x) dst[x] = 0.f;
+            continue;
         }
-    const float* src = in + (size_t)b * CIN * HIN * HIN;
-    constexpr int CU = CIN >= 4 ? 4 : CIN;   // channels whose loads are issued together
-#pragma unroll 1
-    for (int c0 = 0; c0 < CIN; c0 += CU) {
-        float v[CU][9];
+        const float* src = S.crop + y * kPC + x0;   // rows y - 1 .. y + 1, columns x0 - 1 ..
+        float v[3][kSeg + 2];
 #pragma unroll
-        for (int cc = 0; cc < CU; ++cc)
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int k = 0; k < 9; ++k) v[cc][k] = ok[k] ? src[(size_t)(c0 + cc) * HIN * HIN + off[k]] : 0.f;
+            for (int x = 0; x < kSeg + 2; ++x) v[i][x] = src[i * kPC + x];
 #pragma unroll
-        for (int cc = 0; cc < CU; ++cc)
+        for (int x = 0; x < kSeg; ++x) {
+            float acc = bias;
 #pragma unroll
-            for (int k = 0; k < 9; ++k) {
-                const float4* w = sw + ((c0 + cc) * 9 + k) * (kCh / 4) + g * (kOPG / 4);
+            for (int i = 0; i < 3; ++i)
 #pragma unroll
-                for (int q = 0; q < kOPG / 4; ++q) {
-                    const float4 wq = w[q];
-                    acc[4 * q] = fmaf(wq.x, v[cc][k], acc[4 * q]);
-                    acc[4 * q + 1] = fmaf(wq.y, v[cc][k], acc[4 * q + 1]);
-                    acc[4 * q + 2] = fmaf(wq.z, v[cc][k], acc[4 * q + 2]);
-                    acc[4 * q + 3] = fmaf(wq.w, v[cc][k], acc[4 * q + 3]);
-                }
-            }
+                for (int j = 0; j < 3; ++j) acc = fmaf(w[i * 3 + j], v[i][x + j], acc);
+            dst[x] = fmaxf(acc, 0.f);
+        }
     }
-#pragma unroll
-    for (int o = 0; o < kOPG; ++o)
-        out[(((size_t)b * kCh + g * kOPG + o) * HOUT + y) * HOUT + x] = fmaxf(acc[o], 0.f);
 }
 
-// ---- fully connected forward: one 64-thread workgroup per sample ----------
-__global__ __launch_bounds__(64) void fc_fwd_kernel(const float* __restrict__ a4, const float* __restrict__ stats,
-                                                    const float* __restrict__ fc1q, const float* __restrict__ th,
-                                                    const float* __restrict__ fc2q, float* __restrict__ h1,
-                                                    float* __restrict__ out) {
-    __shared__ float hs[kCh];
-    const int b = blockIdx.x, t = threadIdx.x;
-    if (t < kCh) {
-        const float* w = fc1q + t * kFcIn;
-        const float* x = a4 + (size_t)b * kFlat;
-        float acc = th[kC1 + t];
-        for (int k = 0; k < kFlat; ++k) acc = fmaf(w[k], x[k], acc);
-        for (int k = 0; k < kNStat; ++k) acc = fmaf(w[kFlat + k], stats[(size_t)b * kNStat + k], acc);
-        const float h = fmaxf(acc, 0.f);
-        hs[t] = h;
-        h1[(size_t)b * kCh + t] = h;
+// Stride-2 convolution + bias + ReLU of `rows` output rows from a zero-bordered
+// LDS map `in` (plane LI, pitch PI; its first row is the row above output row
+// 0's centre) into `out` (plane LO, pitch PO, first pixel at OO).  A wave takes
+// tiles of 16 positions and 16 HALVES channels; a tap's operands are read
+// while the matrix instructions of the tap before run.  Two sums a tile, each
+// over half of the channels: shorter chains round less.
+template <int HOUT, int LI, int PI, int LO, int PO, int OO, int HALVES>
+SFOC_DEV void conv_tiles(const float* in, const float* w, const float* __restrict__ bias, float* out, int rows) {
+    const int t = tid_here(), lane = t & 63, wv = t >> 6, n = lane & 15, g = lane >> 4;
+    constexpr int kSplit = 2 / HALVES, kS = kCh / 4;
+    const int npos = rows * HOUT, jobs = kSplit * ((npos + 15) / 16);
+    for (int job = wv; job < jobs; job += kWaves) {
+        const int h0 = job % kSplit, p = (job / kSplit) * 16 + n, pc = min(p, npos - 1);
+        const int y = pc / HOUT, x = pc - y * HOUT;
+        const float* b0 = in + g * LI + 2 * y * PI + 2 * x;
+        const float* a0 = w + g * kWP + h0 * 16 + n;
+        f32x4 acc[2][HALVES];
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) acc[0][h] = acc[1][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float av[2][HALVES][kS], bv[2][kS];
+        auto read = [&](int tap, int buf) {
+#pragma unroll
+            for (int cs = 0; cs < kS; ++cs) {
+                bv[buf][cs] = b0[(tap / 3) * PI + tap % 3 + 4 * cs * LI];
+#pragma unroll
+                for (int h = 0; h < HALVES; ++h) av[buf][h][cs] = a0[(tap * kCh + 4 * cs) * kWP + 16 * h];
+            }
+        };
+        read(0, 0);
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            if (tap + 1 < 9) read(tap + 1, (tap + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int cs = 0; cs < kS; ++cs)
+#pragma unroll
+                for (int h = 0; h < HALVES; ++h)
+                    acc[cs & 1][h] = mfma4(av[tap & 1][h][cs], bv[tap & 1][cs], acc[cs & 1][h]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (p < npos) {
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int o = (h0 + h) * 16 + 4 * g + r;
+                    out[o * LO + OO + y * PO + x] = fmaxf(acc[0][h][r] + acc[1][h][r] + bias[o], 0.f);
+                }
+        }
     }
-    __syncthreads();
-    if (t < 3) {
-        float acc = th[kC2 + t];
-        for (int o = 0; o < kCh; ++o) acc = fmaf(fc2q[t * kCh + o], hs[o], acc);
-        out[(size_t)b * 3 + t] = acc;
+}
+
+// Gradient of a stride-2 convolution's input at rows [2 ya, R1) of the map
+// `act` (plane LI, pitch PI; pixel (y, x) at OI + (y - y0) PI + x), masked by
+// act > 0 and written over it; g is the output gradient (plane LG, pitch PG,
+// first pixel at OG).  Position (2a + cy, 2b + cx) gets the taps i = 1 - cy (of
+// output row a + cy) and, for cy = 1, i = 2 (of row a); columns likewise.  The
+// waves draw (class, 16 positions, 16 channels) tiles from a counter, longest
+// first; what a tile computes does not depend on who draws it.
+template <int HOUT, int LG, int PG, int OG, int LI, int PI, int OI>
+SFOC_DEV void dgrad_tiles(const float* g, const float* w, float* act, int y0, int ya, int R1, int* counter) {
+    const int lane = tid_here() & 63, n = lane & 15, q = lane >> 4;
+    int ntile[4], first[4], total = 0;   // classes cy, cx = 11, 10, 01, 00
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int cy = k < 2, cx = !(k & 1);
+        const int ny = max(0, (R1 - 2 * ya - cy + 1) / 2), nx = HOUT - cx;
+        ntile[k] = (ny * nx + 15) / 16;
+        first[k] = total;
+        total += 2 * ntile[k];
     }
+    for (;;) {
+        int job = 0;
+        if (lane == 0) job = atomicAdd(counter, 1);
+        job = __builtin_amdgcn_readfirstlane(job);
+        if (job >= total) break;
+        const int k = job >= first[3] ? 3 : job >= first[2] ? 2 : job >= first[1] ? 1 : 0;
+        const int cy = k < 2, cx = !(k & 1), jk = job - first[k], half = jk & 1;
+        const int ny = (R1 - 2 * ya - cy + 1) / 2, nx = HOUT - cx, np = ny * nx;
+        const int p = (jk >> 1) * 16 + n, pc = min(p, np - 1), a = pc / nx, b = pc - a * nx;
+        const float* gp = g + q * LG + OG + (ya + a) * PG + b;
+        const float* wp = w + (half * 16 + n) * kWP + q;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        constexpr int kS = kCh / 4;
+        const int taps = (1 + cy) * (1 + cx);
+        float av[kS], bv[kS], an[kS], bn[kS];
+        auto read = [&](int k, float(&a_)[kS], float(&b_)[kS]) {
+            // cy = 0: tap 1, row a; cy = 1: tap 0, row a + 1, then tap 2, row a
+            const int iy = k >> cx, ix = cx ? k & 1 : 0;
+            const int i = cy ? 2 * iy : 1, j = cx ? 2 * ix : 1;
+            const float* gg = gp + (cy && !iy ? PG : 0) + (cx && !ix ? 1 : 0);
+            const float* ww = wp + (i * 3 + j) * kCh * kWP;
+#pragma unroll
+            for (int os = 0; os < kS; ++os) {
+                a_[os] = ww[4 * os];
+                b_[os] = gg[4 * os * LG];
+            }
+        };
+        read(0, av, bv);
+        for (int k = 0; k < taps; ++k) {   // the next tap's operands are read ahead
+            read(min(k + 1, taps - 1), an, bn);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int os = 0; os < kS; ++os) acc = mfma4(av[os], bv[os], acc);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int os = 0; os < kS; ++os) {
+                av[os] = an[os];
+                bv[os] = bn[os];
+            }
+        }
+        if (p < np) {
+            const int y = 2 * (ya + a) + cy - y0, x = 2 * b + cx;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float* d = act + (half * 16 + 4 * q + r) * LI + OI + y * PI + x;
+                *d = *d > 0.f ? acc[r] : 0.f;
+            }
+        }
+    }
+}
+
+// Weight-gradient tiles of a stride-2 convolution over `rows` output rows: the
+// 36 tiles (o half, tap, c half) are dealt to the waves, tile wv + 8 k to
+// acc[k] (every wave has one o half, so its g operand serves all its tiles).
+constexpr int kWTiles = 36, kWPer = (kWTiles + kWaves - 1) / kWaves;
+template <int HOUT, int LG, int PG, int LI, int PI>
+SFOC_DEV void wgrad_tiles(const float* g, const float* in, int rows, f32x4 (&acc)[kWPer]) {
+    const int td = tid_here(), lane = td & 63, wv = td >> 6, n = lane & 15, q = lane >> 4;
+    const int npos = rows * HOUT;
+    const float* ga = g + ((wv & 1) * 16 + n) * LG;
+    const float* ib[kWPer];
+#pragma unroll
+    for (int k = 0; k < kWPer; ++k) {
+        const int t = min(wv + kWaves * k, kWTiles - 1), tc = t >> 1, tap = tc >> 1, ch = tc & 1;
+        ib[k] = in + (ch * 16 + n) * LI + (tap / 3) * PI + tap % 3;
+    }
+    // position p = q, q + 4, ...; the next two positions' operands are read
+    // while the matrix instructions of the two before run
+    constexpr int kU = 2;
+    int y = q / HOUT, x = q - y * HOUT, p = q;
+    float av[kU], bv[kU][kWPer], an[kU], bn[kU][kWPer];
+    auto read = [&](float(&a_)[kU], float(&b_)[kU][kWPer]) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const bool ok = p < npos;
+            const int go = ok ? y * PG + x : 0, off = ok ? 2 * y * PI + 2 * x : 0;
+            const float v = ga[go];
+            a_[u] = ok ? v : 0.f;
+#pragma unroll
+            for (int k = 0; k < kWPer; ++k) b_[u][k] = ib[k][off];
+            p += 4;
+            x += 4;
+            if (x >= HOUT) {
+                x -= HOUT;
+                ++y;
+            }
+        }
+    };
+    const int steps = (npos + 4 * kU - 1) / (4 * kU);
+    read(av, bv);
+    for (int s = 0; s < steps; ++s) {
+        read(an, bn);   // (past the last position: zero operands at offset 0)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+#pragma unroll
+            for (int k = 0; k < kWPer; ++k)
+                if (k + 1 < kWPer || wv + kWaves * k < kWTiles) acc[k] = mfma4(av[u], bv[u][k], acc[k]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            av[u] = an[u];
+#pragma unroll
+            for (int k = 0; k < kWPer; ++k) bv[u][k] = bn[u][k];
+        }
+    }
+}
+
+// The tiles' sums into the workgroup's partials (added to those of its earlier
+// samples), in the parameter order [o][c][tap].
+SFOC_DEV void store_wgrad(const f32x4 (&acc)[kWPer], float* __restrict__ part, bool add) {
+    const int td = tid_here(), lane = td & 63, wv = td >> 6, n = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int k = 0; k < kWPer; ++k) {
+        const int t = wv + kWaves * k;
+        if (t >= kWTiles) continue;
+        const int tc = t >> 1, tap = tc >> 1, c = (tc & 1) * 16 + n;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float* d = part + (((t & 1) * 16 + 4 * q + r) * kCh + c) * 9 + tap;
+            *d = add ? *d + acc[k][r] : acc[k][r];
+        }
+    }
+}
+
+// Bias gradient: sums of a gradient map's rows x cols per channel.
+template <int LG, int PG>
+SFOC_DEV void store_bgrad(const float* g, int rows, int cols, float* __restrict__ part, bool add) {
+    const int t = tid_here(), o = t / 16, k = t % 16;
+    float s = 0.f;
+    for (int p = k; p < rows * cols; p += 16) s += g[o * LG + (p / cols) * PG + p % cols];
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) s += __shfl_xor(s, d, 64);
+    if (k == 0) part[o] = add ? part[o] + s : s;
 }
 
 // ---- loss and its gradient w.r.t. the outputs -------------------------------
@@ -176,213 +370,328 @@ SFOC_DEV float smooth_l1(float d) {
 }
 SFOC_DEV float smooth_l1_grad(float d) { return fabsf(d) < kBeta ? d / kBeta : (d > 0.f ? 1.f : -1.f); }
 
-__global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ out, const float* __restrict__ label,
-                                                   const float* __restrict__ target, int B, float* __restrict__ dout,
-                                                   float* __restrict__ loss) {
-    __shared__ double red[256];
-    const int t = threadIdx.x;
-    double part = 0.0;
-    const float inv = 1.0f / (float)B;
-    for (int b = t; b < B; b += 256) {
-        const float l = out[b * 3], y = label[b];
-        const float dy = out[b * 3 + 1] - target[2 * b], dx = out[b * 3 + 2] - target[2 * b + 1];
-        const float bce = fmaxf(l, 0.f) - l * y + log1pf(__expf(-fabsf(l)));
-        part += (double)(bce + kLambda * y * (smooth_l1(dy) + smooth_l1(dx)));
-        dout[b * 3] = (sigmoidf_(l) - y) * inv;
-        dout[b * 3 + 1] = kLambda * y * smooth_l1_grad(dy) * inv;
-        dout[b * 3 + 2] = kLambda * y * smooth_l1_grad(dx) * inv;
-    }
-    red[t] = part;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (t < s) red[t] += red[t + s];
+constexpr uint32_t kEligible = SFOC_CP_VALID | SFOC_CP_INCONSISTENT;
+
+// The decision on a CP record (inference).
+SFOC_DEV void apply_decision(sfoc_cp* __restrict__ cps, int i, const float* out, float threshold) {
+    sfoc_cp c = cps[i];
+    if (!(c.flags & kEligible)) return;
+    const float p = sigmoidf_(out[0]);
+    c.flags = (c.flags & ~kEligible) | SFOC_CP_LEARNED | (p >= threshold ? SFOC_CP_VALID : SFOC_CP_INCONSISTENT);
+    c.sub_dy = fminf(kClip, fmaxf(-kClip, out[1]));
+    c.sub_dx = fminf(kClip, fmaxf(-kClip, out[2]));
+    cps[i] = c;
+}
+
+struct NetArgs {
+    const float* th;
+    const float* crops;
+    const float* stats;
+    int n;
+    float* out;            // n x 3
+    sfoc_cp* cps;          // inference: records the decision applies to, or null
+    float threshold;
+    const float* label;    // training
+    const float* target;
+    float* x4;             // n x 800: fc1's input
+    float* h1;             // n x 32
+    float* dh1;            // n x 32
+    float* dout;           // n x 3
+    float* loss;           // n
+    float* part;           // [workgroup][kConvParams]
+};
+
+template <bool TRAIN>
+__global__ __launch_bounds__(kNetNT, 2) void net_kernel(const NetArgs A) {
+    extern __shared__ float4 lds_raw[];
+    NetLds& S = *reinterpret_cast<NetLds*>(lds_raw);
+    const int t = threadIdx.x, lane = t & 63;
+    const float* __restrict__ th = A.th;
+    if (t < 9 * kCh) S.w1[(t % 9) * kCh + t / 9] = bf16_round(th[kW1 + t]);
+    for (int b = blockIdx.x; b < A.n; b += gridDim.x) {
+        const bool add = b != (int)blockIdx.x;   // later samples add to the partials
         __syncthreads();
-    }
-    if (t == 0 && loss) loss[0] = (float)(red[0] / B);
-}
-
-// ---- fully connected backward -------------------------------------------
-// dh1[b][o] = relu'(h1) * sum_t fc2[t][o] d[b][t]
-__global__ void fc2_bwd_data_kernel(const float* __restrict__ dout, const float* __restrict__ h1,
-                                    const float* __restrict__ fc2q, float* __restrict__ dh1, int B) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * kCh) return;
-    const int b = idx / kCh, o = idx - b * kCh;
-    float g = 0.f;
-    for (int t = 0; t < 3; ++t) g = fmaf(fc2q[t * kCh + o], dout[b * 3 + t], g);
-    dh1[idx] = h1[idx] > 0.f ? g : 0.f;
-}
-
-// Weight and bias gradients of fc1 and fc2 (one thread per entry, batch sum
-// in order): entries [0, 32*808) fc1.w, then 32 fc1.b, 96 fc2.w, 3 fc2.b.
-__global__ void fc_bwd_weight_kernel(const float* __restrict__ dout, const float* __restrict__ h1,
-                                     const float* __restrict__ dh1, const float* __restrict__ a4,
-                                     const float* __restrict__ stats, float* __restrict__ grad, int B) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    float acc = 0.f;
-    if (e < kCh * kFcIn) {
-        const int o = e / kFcIn, k = e - o * kFcIn;
-        for (int b = 0; b < B; ++b) {
-            const float x = k < kFlat ? a4[(size_t)b * kFlat + k] : stats[(size_t)b * kNStat + k - kFlat];
-            acc = fmaf(dh1[b * kCh + o], x, acc);
+        const float* crop = A.crops + (size_t)b * kS0 * kS0;
+#pragma unroll
+        for (int e = t; e < kPC * kPC; e += kNetNT) {
+            const int y = e / kPC - 1, x = e % kPC - 1;
+            S.crop[e] = y >= 0 && y < kS0 && x >= 0 && x < kS0 ? crop[y * kS0 + x] : 0.f;
         }
-        grad[kF1 + e] = acc;
-        return;
-    }
-    e -= kCh * kFcIn;
-    if (e < kCh) {
-        for (int b = 0; b < B; ++b) acc += dh1[b * kCh + e];
-        grad[kC1 + e] = acc;
-        return;
-    }
-    e -= kCh;
-    if (e < 3 * kCh) {
-        const int t = e / kCh, o = e - t * kCh;
-        for (int b = 0; b < B; ++b) acc = fmaf(dout[b * 3 + t], h1[b * kCh + o], acc);
-        grad[kF2 + e] = acc;
-        return;
-    }
-    e -= 3 * kCh;
-    if (e < 3) {
-        for (int b = 0; b < B; ++b) acc += dout[b * 3 + e];
-        grad[kC2 + e] = acc;
-    }
-}
-constexpr int kFcGradCount = kCh * kFcIn + kCh + 3 * kCh + 3;
-
-// d_a4[b][k] = sum_o fc1[o][k] dh1[b][o] for the 800 conv values
-__global__ void fc1_bwd_data_kernel(const float* __restrict__ dh1, const float* __restrict__ fc1q,
-                                    float* __restrict__ da4, int B) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * kFlat) return;
-    const int b = idx / kFlat, k = idx - b * kFlat;
-    float g = 0.f;
-    for (int o = 0; o < kCh; ++o) g = fmaf(fc1q[o * kFcIn + k], dh1[b * kCh + o], g);
-    da4[idx] = g;
-}
-
-// ---- convolution backward -------------------------------------------------
-// din[b][c][y][x] = sum_{o,i,j: S yo + i - 1 = y, S xo + j - 1 = x} w[o][c][i][j] g[b][o][yo][xo],
-// g = dout * relu'(aout).
-template <int CIN, int S, int HIN, int HOUT>
-__global__ __launch_bounds__(256) void conv_bwd_data_kernel(const float* __restrict__ dout,
-                                                            const float* __restrict__ aout,
-                                                            const float* __restrict__ wb, float* __restrict__ din,
-                                                            int B) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * HIN * HIN) return;
-    const int b = idx / (HIN * HIN), p = idx - b * HIN * HIN;
-    const int y = p / HIN, x = p - y * HIN;
-    float acc[CIN];
+        for (int e = t; e < kCh * kL2; e += kNetNT) S.a2[e] = 0.f;
+        if (t < kNStat) S.stats[t] = A.stats[(size_t)b * kNStat + t];
+        float wr[kWRegs];
+        load_weights(th + kW2, wr);
+        stage_weights(wr, S.w);
+        load_weights(th + kW3, wr);
+        __syncthreads();
+        // conv1, conv2 by bands of rows
+        for (int band = 0; band < kBands; ++band) {
+            const int r0 = band * kBandRows, rows = min(kBandRows, kS2 - r0);
+            conv1_band(S, th, 2 * r0 - 1);
+            __syncthreads();
+            conv_tiles<kS2, kL1, kP1, kL2, kP2, kP2 + 1, 2>(S.a1, S.w, th + kB2, S.a2 + r0 * kP2, rows);
+            __syncthreads();
+        }
+        for (int e = t; e < kCh * kL3; e += kNetNT) S.a3[e] = 0.f;
+        stage_weights(wr, S.w);
+        load_weights(th + kW4, wr);
+        __syncthreads();
+        conv_tiles<kS3, kL2, kP2, kL3, kP3, kP3 + 1, 1>(S.a2, S.w, th + kB3, S.a3, kS3);
+        __syncthreads();
+        stage_weights(wr, S.w);
+        if (TRAIN) load_weights(th + kW3, wr);
+        __syncthreads();
+        conv_tiles<kS4, kL3, kP3, kL4, kS4, 0, 1>(S.a3, S.w, th + kB4, S.a4, kS4);
+        __syncthreads();
+        // fc1: 16 lanes an output, then fc2
+        {
+            const int o = t / 16, k0 = t % 16;
+            const float* w = th + kF1 + o * kFcIn;
+            float s = 0.f;
+#pragma unroll 10
+            for (int k = k0; k < kFlat; k += 16) s = fmaf(bf16_round(w[k]), S.a4[k], s);
+            if (k0 < kNStat) s = fmaf(bf16_round(w[kFlat + k0]), S.stats[k0], s);
 #pragma unroll
-    for (int c = 0; c < CIN; ++c) acc[c] = 0.f;
-    for (int o = 0; o < kCh; ++o) {
-        const size_t ob = ((size_t)b * kCh + o) * HOUT * HOUT;
+            for (int d = 1; d < 16; d <<= 1) s += __shfl_xor(s, d, 64);
+            if (k0 == 0) S.h1[o] = fmaxf(s + th[kC1 + o], 0.f);
+        }
+        __syncthreads();
+        if (t < 64) {   // fc2 in the first wave
+            float s[3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int ty = y + 1 - i;
-            if (ty < 0 || ty % S) continue;
-            const int yo = ty / S;
-            if (yo >= HOUT) continue;
+            for (int q = 0; q < 3; ++q) {
+                s[q] = lane < kCh ? bf16_round(th[kF2 + q * kCh + lane]) * S.h1[lane] : 0.f;
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const int tx = x + 1 - j;
-                if (tx < 0 || tx % S) continue;
-                const int xo = tx / S;
-                if (xo >= HOUT) continue;
-                const float a = aout[ob + yo * HOUT + xo];
-                const float g = a > 0.f ? dout[ob + yo * HOUT + xo] : 0.f;
-                const float* w = wb + (o * 9 + i * 3 + j) * CIN;
-#pragma unroll
-                for (int c = 0; c < CIN; ++c) acc[c] = fmaf(w[c], g, acc[c]);
+                for (int d = 1; d < 32; d <<= 1) s[q] += __shfl_xor(s[q], d, 64);
             }
-        }
-    }
+            if (lane == 0) {
+                float o[3];
 #pragma unroll
-    for (int c = 0; c < CIN; ++c) din[(((size_t)b * CIN + c) * HIN + y) * HIN + x] = acc[c];
-}
-
-// Partial weight / bias gradients over a chunk of samples: thread t owns
-// output channel o = t / (CIN / CPT) and CPT input channels, all 9 taps.
-// part[chunk][(o * CIN + c) * 9 + tap], then the 32 bias entries.
-template <int CIN, int S, int HIN, int HOUT>
-__global__ __launch_bounds__(256) void conv_bwd_weight_kernel(const float* __restrict__ dout,
-                                                              const float* __restrict__ aout,
-                                                              const float* __restrict__ in, float* __restrict__ part,
-                                                              int B, int spc) {
-    constexpr int CPT = CIN >= 8 ? CIN / 8 : 1;
-    constexpr int GPO = CIN / CPT;   // threads per output channel
-    constexpr int NW = kCh * CIN * 9 + kCh;
-    const int t = threadIdx.x;
-    const int chunk = blockIdx.x;
-    if (t >= kCh * GPO) return;
-    const int o = t / GPO, c0 = (t - o * GPO) * CPT;
-    float acc[CPT][9];
-    float accb = 0.f;
+                for (int q = 0; q < 3; ++q) {
+                    o[q] = s[q] + th[kC2 + q];
+                    if (A.out) A.out[(size_t)b * 3 + q] = o[q];
+                }
+                if constexpr (!TRAIN) {
+                    if (A.cps) apply_decision(A.cps, b, o, A.threshold);
+                } else {
+                    const float inv = 1.0f / (float)A.n;
+                    const float l = o[0], y = A.label[b];
+                    const float dy = o[1] - A.target[2 * b], dx = o[2] - A.target[2 * b + 1];
+                    const float bce = fmaxf(l, 0.f) - l * y + log1pf(__expf(-fabsf(l)));
+                    A.loss[b] = bce + kLambda * y * (smooth_l1(dy) + smooth_l1(dx));
+                    S.dout[0] = (sigmoidf_(l) - y) * inv;
+                    S.dout[1] = kLambda * y * smooth_l1_grad(dy) * inv;
+                    S.dout[2] = kLambda * y * smooth_l1_grad(dx) * inv;
 #pragma unroll
-    for (int cc = 0; cc < CPT; ++cc)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) acc[cc][k] = 0.f;
-    const int b0 = chunk * spc, b1 = min(B, b0 + spc);
-    for (int b = b0; b < b1; ++b) {
-        const size_t ob = ((size_t)b * kCh + o) * HOUT * HOUT;
-        for (int p = 0; p < HOUT * HOUT; ++p) {
-            const int yo = p / HOUT, xo = p - yo * HOUT;
-            const float a = aout[ob + p];
-            const float g = a > 0.f ? dout[ob + p] : 0.f;
-            accb += g;
-#pragma unroll
-            for (int cc = 0; cc < CPT; ++cc) {
-                const float* src = in + ((size_t)b * CIN + c0 + cc) * HIN * HIN;
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const int yy = S * yo + i - 1;
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        const int xx = S * xo + j - 1;
-                        const float v = (yy >= 0 && yy < HIN && xx >= 0 && xx < HIN) ? src[yy * HIN + xx] : 0.f;
-                        acc[cc][i * 3 + j] = fmaf(g, v, acc[cc][i * 3 + j]);
-                    }
+                    for (int q = 0; q < 3; ++q) A.dout[(size_t)b * 3 + q] = S.dout[q];
+                    S.job = 0;
                 }
             }
         }
+        if constexpr (TRAIN) {
+            float* __restrict__ part = A.part + (size_t)blockIdx.x * kConvParams;
+            __syncthreads();
+            if (t < kCh) {
+                float g = 0.f;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) g = fmaf(bf16_round(th[kF2 + q * kCh + t]), S.dout[q], g);
+                const float h = S.h1[t], d = h > 0.f ? g : 0.f;
+                S.dh1[t] = d;
+                A.h1[(size_t)b * kCh + t] = h;
+                A.dh1[(size_t)b * kCh + t] = d;
+            }
+            __syncthreads();
+            // gradient of conv4's output over a4 (kept in HBM as fc1's input)
+            for (int k = t; k < kFlat; k += kNetNT) {
+                float g = 0.f;
+#pragma unroll
+                for (int o = 0; o < kCh; ++o) g = fmaf(bf16_round(th[kF1 + o * kFcIn + k]), S.dh1[o], g);
+                const float a = S.a4[k];
+                A.x4[(size_t)b * kFlat + k] = a;
+                S.a4[k] = a > 0.f ? g : 0.f;
+            }
+            __syncthreads();
+            f32x4 acc[kWPer];
+            auto clear = [&]() {
+#pragma unroll
+                for (int k = 0; k < kWPer; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+            };
+            // conv4: weight and bias gradients, then the gradient over a3
+            clear();
+            wgrad_tiles<kS4, kL4, kS4, kL3, kP3>(S.a4, S.a3, kS4, acc);
+            store_wgrad(acc, part + kW4, add);
+            store_bgrad<kL4, kS4>(S.a4, kS4, kS4, part + kB4, add);
+            __syncthreads();
+            dgrad_tiles<kS4, kL4, kS4, 0, kL3, kP3, kP3 + 1>(S.a4, S.w, S.a3, 0, 0, kS3, &S.job);
+            __syncthreads();
+            // conv3
+            stage_weights(wr, S.w);
+            load_weights(th + kW2, wr);
+            if (t == 0) S.job = 0;
+            clear();
+            wgrad_tiles<kS3, kL3, kP3, kL2, kP2>(S.a3 + kP3 + 1, S.a2, kS3, acc);
+            store_wgrad(acc, part + kW3, add);
+            store_bgrad<kL3, kP3>(S.a3 + kP3 + 1, kS3, kS3, part + kB3, add);
+            __syncthreads();
+            dgrad_tiles<kS3, kL3, kP3, kP3 + 1, kL2, kP2, kP2 + 1>(S.a3, S.w, S.a2, 0, 0, kS2, &S.job);
+            __syncthreads();
+            // conv2 and conv1 by the same bands: a1 again, conv2's weight
+            // gradient, the gradient over the band's own a1 rows, and conv1's
+            // weight gradient D[o][tap] = sum da1[o][pos] crop[pos + tap] with
+            // a constant one as tap 9 (the bias)
+            stage_weights(wr, S.w);
+            store_bgrad<kL2, kP2>(S.a2 + kP2 + 1, kS2, kS2, part + kB2, add);
+            clear();
+            f32x4 acc1[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+            const int n = lane & 15, q = lane >> 4, wv = t >> 6;
+            for (int band = 0; band < kBands; ++band) {
+                const int r0 = band * kBandRows, rows = min(kBandRows, kS2 - r0);
+                const int a0 = 2 * r0, a1 = min(2 * (r0 + rows), kS1);   // the band's own a1 rows
+                conv1_band(S, th, a0 - 1);
+                if (t == 0) S.job = 0;
+                __syncthreads();
+                wgrad_tiles<kS2, kL2, kP2, kL1, kP1>(S.a2 + (r0 + 1) * kP2 + 1, S.a1, rows, acc);
+                __syncthreads();
+                dgrad_tiles<kS2, kL2, kP2, kP2 + 1, kL1, kP1, 1>(S.a2, S.w, S.a1, a0 - 1, r0, a1, &S.job);
+                __syncthreads();
+                const int npos = (a1 - a0) * kS1;
+                const int tap = min(n, 8);
+                const float* cr = S.crop + (a0 + tap / 3) * kPC + tap % 3;
+                for (int p0 = 4 * wv; p0 < npos; p0 += 4 * kWaves) {
+                    const int p = p0 + q, pc = min(p, npos - 1), y = pc / kS1, x = pc - y * kS1;
+                    const bool ok = p < npos;
+                    const float bv = n < 9 ? cr[y * kPC + x] : (n == 9 ? 1.f : 0.f);
+                    const float* ap = S.a1 + n * kL1 + (y + 1) * kP1 + x + 1;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) acc1[h] = mfma4(ok ? ap[h * 16 * kL1] : 0.f, bv, acc1[h]);
+                }
+                __syncthreads();
+            }
+            store_wgrad(acc, part + kW2, add);
+            // conv1: the waves' sums in wave order (a1 is dead)
+            float* red = S.a1;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[(wv * kCh + h * 16 + 4 * q + r) * 16 + n] = acc1[h][r];
+            __syncthreads();
+            for (int e = t; e < kCh * 10; e += kNetNT) {
+                const int o = e / 10, tap = e - o * 10;
+                float s = 0.f;
+                for (int w = 0; w < kWaves; ++w) s += red[(w * kCh + o) * 16 + tap];
+                float* d = part + (tap < 9 ? kW1 + o * 9 + tap : kB1 + o);
+                *d = add ? *d + s : s;
+            }
+        }
     }
-    float* dst = part + (size_t)chunk * NW;
-#pragma unroll
-    for (int cc = 0; cc < CPT; ++cc)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) dst[(o * CIN + c0 + cc) * 9 + k] = acc[cc][k];
-    if (c0 == 0) dst[kCh * CIN * 9 + o] = accb;
 }
 
-// Sum of the chunk partials in chunk order: weights to grad[w0 ..], biases
-// to grad[b0 ..].
-__global__ void reduce_partials_kernel(const float* __restrict__ part, int nchunks, int nw, float* __restrict__ grad,
-                                       int w0, int b0) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = nw + kCh;
-    if (e >= n) return;
-    float s = 0.f;
-    for (int k = 0; k < nchunks; ++k) s += part[(size_t)k * n + e];
-    grad[e < nw ? w0 + e : b0 + (e - nw)] = s;
+// ---- gradients over the batch and Adam ------------------------------------------
+struct UpdateArgs {
+    float* th;
+    float* m;
+    float* v;
+    float* grad;           // kNParams
+    float* loss;           // one float, or null
+    const float* part;     // [parts][kConvParams]
+    const float* x4;
+    const float* stats;
+    const float* h1;
+    const float* dh1;
+    const float* dout;
+    const float* sloss;    // per sample
+    int n, parts;
+    float lr, c1, c2;
+};
+
+SFOC_DEV void adam_step(const UpdateArgs& A, int e, float g) {
+    A.grad[e] = g;
+    const float mm = 0.9f * A.m[e] + 0.1f * g;
+    const float vv = 0.999f * A.v[e] + 0.001f * g * g;
+    A.m[e] = mm;
+    A.v[e] = vv;
+    A.th[e] -= A.lr * (mm * A.c1) / (sqrtf(vv * A.c2) + 1e-8f);
 }
 
-// ---- Adam -------------------------------------------------------------------
-__global__ void adam_kernel(float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
-                            const float* __restrict__ g, int n, float lr, float c1, float c2) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    const float gg = g[e];
-    const float mm = 0.9f * m[e] + 0.1f * gg;
-    const float vv = 0.999f * v[e] + 0.001f * gg * gg;
-    m[e] = mm;
-    v[e] = vv;
-    th[e] -= lr * (mm * c1) / (sqrtf(vv * c2) + 1e-8f);
+// Workgroups of 64 entries x 4 slices of the sum (over the partials, or over
+// the batch); the slices are added in order.  First the convolutions, then
+// fc1's weights (eight groups of four outputs x 64 inputs), the other vectors
+// (a wave an entry) and the loss.
+constexpr int kUpNT = 256, kUpE = 64, kUpS = kUpNT / kUpE;
+constexpr int kUpConv = (kConvParams + kUpE - 1) / kUpE;
+constexpr int kUpK = (kFcIn + kUpE - 1) / kUpE, kUpO = 4, kUpFc = (kCh / kUpO) * kUpK;
+constexpr int kUpVecN = 4 * kCh + 3, kUpVec = (kUpVecN + kUpNT / 64 - 1) / (kUpNT / 64);
+__global__ __launch_bounds__(kUpNT) void update_kernel(const UpdateArgs A) {
+    __shared__ float red[kUpS][kUpO][kUpE];
+    __shared__ double redl[kUpNT];
+    const int t = threadIdx.x, i = t % kUpE, s = t / kUpE;
+    int blk = blockIdx.x;
+    if (blk < kUpConv) {
+        const int e = blk * kUpE + i, ec = min(e, kConvParams - 1);
+        const int per = (A.parts + kUpS - 1) / kUpS, k0 = s * per, k1 = min(A.parts, k0 + per);
+        float a = 0.f;
+#pragma unroll 16
+        for (int k = k0; k < k1; ++k) a += A.part[(size_t)k * kConvParams + ec];
+        red[s][0][i] = a;
+        __syncthreads();
+        if (s == 0 && e < kConvParams) {
+            for (int q = 1; q < kUpS; ++q) a += red[q][0][i];
+            adam_step(A, e, a);
+        }
+        return;
+    }
+    blk -= kUpConv;
+    const int per = (A.n + kUpS - 1) / kUpS, b0 = s * per, b1 = min(A.n, b0 + per);
+    if (blk < kUpFc) {
+        const int o0 = (blk / kUpK) * kUpO, k = (blk % kUpK) * kUpE + i;
+        const float* x = k < kFlat ? A.x4 + k : A.stats + min(k - kFlat, kNStat - 1);
+        const size_t pitch = k < kFlat ? kFlat : kNStat;
+        float a[kUpO] = {};
+#pragma unroll 8
+        for (int b = b0; b < b1; ++b) {
+            const float xv = x[b * pitch];
+            const float4 d = *reinterpret_cast<const float4*>(A.dh1 + (size_t)b * kCh + o0);
+            a[0] = fmaf(d.x, xv, a[0]);
+            a[1] = fmaf(d.y, xv, a[1]);
+            a[2] = fmaf(d.z, xv, a[2]);
+            a[3] = fmaf(d.w, xv, a[3]);
+        }
+#pragma unroll
+        for (int o = 0; o < kUpO; ++o) red[s][o][i] = a[o];
+        __syncthreads();
+        // slice s finishes output o0 + s
+        float g = 0.f;
+        for (int q = 0; q < kUpS; ++q) g += red[q][s][i];
+        if (k < kFcIn) adam_step(A, kF1 + (o0 + s) * kFcIn + k, g);
+        return;
+    }
+    blk -= kUpFc;
+    if (blk < kUpVec) {   // fc1 biases (0..31), fc2 weights (32..127), fc2 biases (128..130): a wave each
+        const int r = blk * (kUpNT / 64) + t / 64, lane = t % 64;
+        if (r >= kUpVecN) return;
+        float g = 0.f;
+        for (int b = lane; b < A.n; b += 64) {
+            if (r < kCh) g += A.dh1[(size_t)b * kCh + r];
+            else if (r < 4 * kCh) g = fmaf(A.dout[(size_t)b * 3 + r / kCh - 1], A.h1[(size_t)b * kCh + r % kCh], g);
+            else g += A.dout[(size_t)b * 3 + r - 4 * kCh];
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) g += __shfl_xor(g, d, 64);
+        if (lane == 0) adam_step(A, r < kCh ? kC1 + r : r < 4 * kCh ? kF2 + r - kCh : kC2 + r - 4 * kCh, g);
+        return;
+    }
+    double a = 0.0;
+    for (int b = t; b < A.n; b += kUpNT) a += (double)A.sloss[b];
+    redl[t] = a;
+    __syncthreads();
+    for (int d = kUpNT / 2; d > 0; d >>= 1) {
+        if (t < d) redl[t] += redl[t + d];
+        __syncthreads();
+    }
+    if (t == 0) A.loss[0] = (float)(redl[0] / A.n);
 }
 
 // ---- features -------------------------------------------------------------
-constexpr uint32_t kEligible = SFOC_CP_VALID | SFOC_CP_INCONSISTENT;
-
 template <int DT>
 SFOC_DEV float ld_desc(const void* p, int64_t i) {
     if (DT == SFOC_DTYPE_F32) return ((const float*)p)[i];
@@ -504,24 +813,11 @@ __global__ __launch_bounds__(kFeatNT) void features_kernel(const FeatArgs A) {
     }
 }
 
-// ---- inference decision -----------------------------------------------------
-__global__ void apply_kernel(const float* __restrict__ out, sfoc_cp* __restrict__ cps, int n, float threshold) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    sfoc_cp c = cps[i];
-    if (!(c.flags & kEligible)) return;
-    const float p = sigmoidf_(out[i * 3]);
-    c.flags = (c.flags & ~kEligible) | SFOC_CP_LEARNED | (p >= threshold ? SFOC_CP_VALID : SFOC_CP_INCONSISTENT);
-    c.sub_dy = fminf(kClip, fmaxf(-kClip, out[i * 3 + 1]));
-    c.sub_dx = fminf(kClip, fmaxf(-kClip, out[i * 3 + 2]));
-    cps[i] = c;
-}
-
 // ---- workspace ------------------------------------------------------------
 struct Layout {
-    size_t wf[4], wb[4], fc1q, fc2q, a1, a2, a3, a4, h1, out;   // forward
-    size_t dout, dh1, da4, da3, da2, da1, part, grad, total;    // training
-    int spc, nchunks;
+    size_t out;                                              // inference
+    size_t x4, h1, dh1, dout, loss, part, grad, total;       // training
+    int parts;
 };
 
 static size_t take(size_t& off, size_t floats) {
@@ -530,87 +826,50 @@ static size_t take(size_t& off, size_t floats) {
     return o;
 }
 
+// Workgroups of a training launch: one a sample up to one a CU (a workgroup
+// fills a CU's LDS), so that the partials stay within 29 MB.
+constexpr int kMaxParts = 256;
+
 static Layout layout(int n, bool train) {
     Layout L{};
     size_t off = 0;
-    L.wf[0] = take(off, 9 * kCh);
-    L.wb[0] = take(off, 9 * kCh);
-    for (int k = 1; k < 4; ++k) {
-        L.wf[k] = take(off, kCh * kCh * 9);
-        L.wb[k] = take(off, kCh * kCh * 9);
-    }
-    L.fc1q = take(off, kCh * kFcIn);
-    L.fc2q = take(off, 3 * kCh);
-    L.a1 = take(off, (size_t)n * kCh * kS1 * kS1);
-    L.a2 = take(off, (size_t)n * kCh * kS2 * kS2);
-    L.a3 = take(off, (size_t)n * kCh * kS3 * kS3);
-    L.a4 = take(off, (size_t)n * kFlat);
-    L.h1 = take(off, (size_t)n * kCh);
     L.out = take(off, (size_t)n * 3);
-    L.spc = (n + 511) / 512;
-    L.nchunks = n > 0 ? (n + L.spc - 1) / L.spc : 0;
+    L.parts = n < kMaxParts ? n : kMaxParts;
     if (train) {
-        L.dout = take(off, (size_t)n * 3);
+        L.x4 = take(off, (size_t)n * kFlat);
+        L.h1 = take(off, (size_t)n * kCh);
         L.dh1 = take(off, (size_t)n * kCh);
-        L.da4 = take(off, (size_t)n * kFlat);
-        L.da3 = take(off, (size_t)n * kCh * kS3 * kS3);
-        L.da2 = take(off, (size_t)n * kCh * kS2 * kS2);
-        L.da1 = take(off, (size_t)n * kCh * kS1 * kS1);
-        L.part = take(off, (size_t)L.nchunks * (kCh * kCh * 9 + kCh));
+        L.dout = take(off, (size_t)n * 3);
+        L.loss = take(off, (size_t)n);
+        L.part = take(off, (size_t)L.parts * kConvParams);
         L.grad = take(off, kNParams);
     }
     L.total = off;
     return L;
 }
 
-static inline int blocks(size_t n, int t) { return (int)((n + t - 1) / t); }
-
-static QWeights qweights(char* ws, const Layout& L) {
-    QWeights q;
-    for (int k = 0; k < 4; ++k) {
-        q.wf[k] = (float*)(ws + L.wf[k]);
-        q.wb[k] = (float*)(ws + L.wb[k]);
-    }
-    q.fc1q = (float*)(ws + L.fc1q);
-    q.fc2q = (float*)(ws + L.fc2q);
-    return q;
-}
-
-static hipError_t forward(const float* th, const float* crops, const float* stats, int n, float* out, char* ws,
-                          const Layout& L, hipStream_t st) {
-    const QWeights q = qweights(ws, L);
-    float* a1 = (float*)(ws + L.a1);
-    float* a2 = (float*)(ws + L.a2);
-    float* a3 = (float*)(ws + L.a3);
-    float* a4 = (float*)(ws + L.a4);
-    float* h1 = (float*)(ws + L.h1);
-    trace_begin(st, SFOC_K_HEAD_FWD);
-    hipLaunchKernelGGL(prep_weights_kernel, dim3(blocks(kPrepCount, 256)), dim3(256), 0, st, th, q);
-    hipLaunchKernelGGL((conv_fwd_kernel<1, 1, kS0, kS1>), dim3(blocks((size_t)n * kS1 * kS1 * kOG, 256)), dim3(256), 0, st,
-                       crops, q.wf[0], th + kB1, a1, n);
-    hipLaunchKernelGGL((conv_fwd_kernel<kCh, 2, kS1, kS2>), dim3(blocks((size_t)n * kS2 * kS2 * kOG, 256)), dim3(256), 0,
-                       st, a1, q.wf[1], th + kB2, a2, n);
-    hipLaunchKernelGGL((conv_fwd_kernel<kCh, 2, kS2, kS3>), dim3(blocks((size_t)n * kS3 * kS3 * kOG, 256)), dim3(256), 0,
-                       st, a2, q.wf[2], th + kB3, a3, n);
-    hipLaunchKernelGGL((conv_fwd_kernel<kCh, 2, kS3, kS4>), dim3(blocks((size_t)n * kS4 * kS4 * kOG, 256)), dim3(256), 0,
-                       st, a3, q.wf[3], th + kB4, a4, n);
-    hipLaunchKernelGGL(fc_fwd_kernel, dim3(n), dim3(64), 0, st, a4, stats, q.fc1q, th, q.fc2q, h1, out);
-    trace_end(st, SFOC_K_HEAD_FWD);
+template <bool TRAIN>
+static hipError_t launch_net(const NetArgs& a, int blocks, int trace, hipStream_t st) {
+    auto kern = net_kernel<TRAIN>;
+    hipError_t e = ensure_dynamic_lds((const void*)kern, (int)sizeof(NetLds));
+    if (e != hipSuccess) return e;
+    trace_begin(st, trace);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kNetNT), sizeof(NetLds), st, a);
+    trace_end(st, trace);
     return hipGetLastError();
 }
 
-template <int CIN, int S, int HIN, int HOUT>
-static void conv_bwd(const float* dout, const float* aout, const float* in, const float* wb, float* din, char* ws,
-                     const Layout& L, int n, float* grad, int w0, int b0, hipStream_t st) {
-    float* part = (float*)(ws + L.part);
-    if (din)
-        hipLaunchKernelGGL((conv_bwd_data_kernel<CIN, S, HIN, HOUT>), dim3(blocks((size_t)n * HIN * HIN, 256)),
-                           dim3(256), 0, st, dout, aout, wb, din, n);
-    hipLaunchKernelGGL((conv_bwd_weight_kernel<CIN, S, HIN, HOUT>), dim3(L.nchunks), dim3(256), 0, st, dout, aout, in,
-                       part, n, L.spc);
-    const int nw = kCh * CIN * 9;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks(nw + kCh, 256)), dim3(256), 0, st, part, L.nchunks, nw,
-                       grad, w0, b0);
+static hipError_t forward(const float* th, const float* crops, const float* stats, int n, float* out, sfoc_cp* cps,
+                          float threshold, hipStream_t st) {
+    NetArgs a{};
+    a.th = th;
+    a.crops = crops;
+    a.stats = stats;
+    a.n = n;
+    a.out = out;
+    a.cps = cps;
+    a.threshold = threshold;
+    return launch_net<false>(a, n, SFOC_K_HEAD_FWD, st);
 }
 
 }  // namespace head
@@ -656,7 +915,7 @@ int sfoc_head_forward(const float* params, const float* crops, const float* stat
     if (!params || !crops || !stats || !out || !ws) return SFOC_E_INVALID_ARG;
     const Layout L = layout(n, false);
     if (ws_bytes < L.total) return SFOC_E_WORKSPACE;
-    return hip_status(forward(params, crops, stats, n, out, (char*)ws, L, (hipStream_t)stream));
+    return hip_status(forward(params, crops, stats, n, out, nullptr, 0.f, (hipStream_t)stream));
 }
 
 int sfoc_head_infer(const float* params, const float* crops, const float* stats, int32_t n, float threshold,
@@ -667,12 +926,7 @@ int sfoc_head_infer(const float* params, const float* crops, const float* stats,
     if (!params || !crops || !stats || !cps || !ws) return SFOC_E_INVALID_ARG;
     const Layout L = layout(n, false);
     if (ws_bytes < L.total) return SFOC_E_WORKSPACE;
-    hipStream_t st = (hipStream_t)stream;
-    float* o = out ? out : (float*)((char*)ws + L.out);
-    hipError_t e = forward(params, crops, stats, n, o, (char*)ws, L, st);
-    if (e != hipSuccess) return hip_status(e);
-    hipLaunchKernelGGL(apply_kernel, dim3(blocks(n, 256)), dim3(256), 0, st, o, cps, n, threshold);
-    return hip_status(hipGetLastError());
+    return hip_status(forward(params, crops, stats, n, out, cps, threshold, (hipStream_t)stream));
 }
 
 int sfoc_head_train_step(float* params, float* adam_m, float* adam_v, int32_t t, float lr, const float* crops,
@@ -686,42 +940,42 @@ int sfoc_head_train_step(float* params, float* adam_m, float* adam_v, int32_t t,
     if (ws_bytes < L.total) return SFOC_E_WORKSPACE;
     char* w = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
-    float* out = (float*)(w + L.out);
-    hipError_t e = forward(params, crops, stats, n, out, w, L, st);
+    NetArgs a{};
+    a.th = params;
+    a.crops = crops;
+    a.stats = stats;
+    a.n = n;
+    a.label = label;
+    a.target = target;
+    a.x4 = (float*)(w + L.x4);
+    a.h1 = (float*)(w + L.h1);
+    a.dh1 = (float*)(w + L.dh1);
+    a.dout = (float*)(w + L.dout);
+    a.loss = (float*)(w + L.loss);
+    a.part = (float*)(w + L.part);
+    hipError_t e = launch_net<true>(a, L.parts, SFOC_K_HEAD_BWD, st);
     if (e != hipSuccess) return hip_status(e);
-    const QWeights q = qweights(w, L);
-    float* g = grad ? grad : (float*)(w + L.grad);
-    float* dout = (float*)(w + L.dout);
-    float* dh1 = (float*)(w + L.dh1);
-    float* da4 = (float*)(w + L.da4);
-    float* da3 = (float*)(w + L.da3);
-    float* da2 = (float*)(w + L.da2);
-    float* da1 = (float*)(w + L.da1);
-    const float* a1 = (const float*)(w + L.a1);
-    const float* a2 = (const float*)(w + L.a2);
-    const float* a3 = (const float*)(w + L.a3);
-    const float* a4 = (const float*)(w + L.a4);
-    const float* h1 = (const float*)(w + L.h1);
-    trace_begin(st, SFOC_K_HEAD_BWD);
-    hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, st, out, label, target, n, dout, loss);
-    hipLaunchKernelGGL(fc2_bwd_data_kernel, dim3(blocks((size_t)n * kCh, 256)), dim3(256), 0, st, dout, h1, q.fc2q,
-                       dh1, n);
-    hipLaunchKernelGGL(fc_bwd_weight_kernel, dim3(blocks(kFcGradCount, 256)), dim3(256), 0, st, dout, h1, dh1, a4,
-                       stats, g, n);
-    hipLaunchKernelGGL(fc1_bwd_data_kernel, dim3(blocks((size_t)n * kFlat, 256)), dim3(256), 0, st, dh1, q.fc1q, da4,
-                       n);
-    conv_bwd<kCh, 2, kS3, kS4>(da4, a4, a3, q.wb[3], da3, w, L, n, g, kW4, kB4, st);
-    conv_bwd<kCh, 2, kS2, kS3>(da3, a3, a2, q.wb[2], da2, w, L, n, g, kW3, kB3, st);
-    conv_bwd<kCh, 2, kS1, kS2>(da2, a2, a1, q.wb[1], da1, w, L, n, g, kW2, kB2, st);
-    conv_bwd<1, 1, kS0, kS1>(da1, a1, crops, q.wb[0], nullptr, w, L, n, g, kW1, kB1, st);
-    trace_end(st, SFOC_K_HEAD_BWD);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_status(e);
+    UpdateArgs u{};
+    u.th = params;
+    u.m = adam_m;
+    u.v = adam_v;
+    u.grad = grad ? grad : (float*)(w + L.grad);
+    u.loss = loss;
+    u.part = a.part;
+    u.x4 = a.x4;
+    u.stats = stats;
+    u.h1 = a.h1;
+    u.dh1 = a.dh1;
+    u.dout = a.dout;
+    u.sloss = a.loss;
+    u.n = n;
+    u.parts = L.parts;
+    u.lr = lr;
     // bias corrections in double on the host
-    const double c1 = 1.0 / (1.0 - pow(0.9, (double)t)), c2 = 1.0 / (1.0 - pow(0.999, (double)t));
+    u.c1 = (float)(1.0 / (1.0 - pow(0.9, (double)t)));
+    u.c2 = (float)(1.0 / (1.0 - pow(0.999, (double)t)));
     trace_begin(st, SFOC_K_HEAD_ADAM);
-    hipLaunchKernelGGL(adam_kernel, dim3(blocks(kNParams, 256)), dim3(256), 0, st, params, adam_m, adam_v, g,
-                       kNParams, lr, (float)c1, (float)c2);
+    hipLaunchKernelGGL(update_kernel, dim3(kUpConv + kUpFc + kUpVec + (loss ? 1 : 0)), dim3(kUpNT), 0, st, u);
     trace_end(st, SFOC_K_HEAD_ADAM);
     return hip_status(hipGetLastError());
 }
