@@ -335,13 +335,9 @@ int sfoc_register_cps_streamed(const float* ref, int64_t Hr, int64_t Wr, int64_t
  * workgroups per CU taking items from a counter) with SFOC_PLAN_PERSISTENT;
  * with SFOC_PLAN_AUTOTUNE each transform side's launch form is also timed
  * at creation and the faster kept.
- * The describe launch has two configurations of its 32 x 32 tile where the
- * parameters allow (K = 1, dilation rates 1, 2, 3, both orders, z <= 16):
- * 0, three workgroups per CU; 1, four workgroups per CU with half-width
- * row-pass maps and one steered channel map at a time.  Both give the same
- * descriptors bit for bit.  SFOC_PLAN_DESCRIBE_ALT selects configuration 1;
- * with SFOC_PLAN_AUTOTUNE both are timed on the plan's tiles at creation
- * and the faster kept (not remembered in tune_cache).
+ * SFOC_PLAN_DESCRIBE_ALT asks for describe configuration 1 where the
+ * parameters have it (K = 1, dilation rates 1, 2, 3, both orders, z <= 16);
+ * sfoc_plan_get_info reports it.  One kernel serves both configurations.
  *
  * Ownership and lifetime: the caller owns every pair buffer (device
  * pointers) and keeps them allocated for the plan's lifetime; the plan
@@ -401,7 +397,7 @@ typedef struct sfoc_plan_info {
     int32_t cached_classes;     /* (m, r) classes taken from tune_cache */
     int32_t graph;              /* 1 once a graph is captured */
     int32_t persistent[4];      /* those launches persistent (1) or one workgroup per item */
-    int32_t describe_config;    /* describe launch configuration: 0, or 1 (four workgroups per CU) */
+    int32_t describe_config;    /* describe configuration asked for: 0 or 1 (one kernel serves both) */
     int32_t direct_items;       /* items of the direct-form launch (SFOC_MATCH_DIRECT) */
     int64_t device_bytes;
 } sfoc_plan_info;

@@ -1,7 +1,8 @@
 // Dense SFOC descriptor (Section 2.1, Eq. 1-7) as one fused gfx950 kernel
 // per 32x32 output tile, plus the float64 integral-image scans (Eq. 14-16).
 //
-// Per tile, everything stays in LDS:
+// Per tile, everything stays in LDS (describe_kernel, any parameters; the
+// shapes in use, K = 1 at rates 1, 2, 3, have describe_k1_kernel):
 //   1. the input tile plus a halo of R (largest kernel radius) + Q (dilated
 //      smoothing reach), read once from HBM with reflect-101 indices;
 //   2. for each distinct sigma, a separable row pass (1-D Gaussian g, first
@@ -39,11 +40,7 @@ struct DescribeGeom {
     size_t bytes;
 };
 
-// Pitch of the half-width row-pass maps of the four-workgroup configuration
-// (20 columns, odd).
-constexpr int kHalfPitch = 21;
-
-static DescribeGeom describe_geom(const DescribeConsts& c, int CG, bool halves) {
+static DescribeGeom describe_geom(const DescribeConsts& c, int CG) {
     DescribeGeom g;
     g.BSP = (kTS + 2 * c.Q + kRun - 1) / kRun * kRun;
     g.ISX = g.BSP + 2 * c.R;
@@ -54,11 +51,30 @@ static DescribeGeom describe_geom(const DescribeConsts& c, int CG, bool halves) 
     // Phase 2 holds the image region and the row-pass maps; phase 3 the five
     // basis maps (over the same memory) and CG steered channels.
     const size_t img = (size_t)g.ISX * g.IPP;
-    const size_t row = 3 * (size_t)g.ISX * (halves ? kHalfPitch : g.BPP);
+    const size_t row = 3 * (size_t)g.ISX * g.BPP;
     const size_t bb = (size_t)g.BSP * g.BPP;
     const size_t p2 = img + row, p3 = (5 + (size_t)CG) * bb;
     g.bytes = (p2 > p3 ? p2 : p3) * sizeof(float);
     return g;
+}
+
+// LDS geometry of the K = 1, rates 1-3 tile (Q = 3): basis and channel maps of
+// 38 x 38 pixels, nothing padded but the pitches.
+constexpr int kB = kTS + 6;           // side of the basis and channel maps
+constexpr int kCP = kB + 1;           // their pitch (odd)
+constexpr int kPix = (kB * kCP + kNT - 1) / kNT;   // map elements per thread, in linear order (6)
+constexpr int kCM = kPix * kNT;       // floats of a map
+constexpr int kRP = kB + 3;           // pitch of the row-pass maps: ten runs of kRun (odd)
+constexpr int kCRun = 3;              // rows of a column-pass run
+constexpr int kCRuns = (kB + kCRun - 1) / kCRun;                 // 13
+constexpr int kCOwn = (kCRuns * kB + kNT - 1) / kNT;             // column-pass runs per thread (2)
+static_assert(kRP % 2 == 1 && kCP % 2 == 1 && kRP >= (kB + kRun - 1) / kRun * kRun, "pitches");
+static_assert(kCRuns * kCRun * kCP <= kCM, "the rows of the last run stay inside a map");
+static size_t describe_k1_lds(int R) {
+    const size_t side = kB + 2 * R;
+    // (the last column run reads one row past its map)
+    const size_t p2 = side * (side | 1) + (3 * side + 1) * kRP, p3 = 5 * (size_t)kCM;
+    return (p2 > p3 ? p2 : p3) * sizeof(float);
 }
 
 // Dilated Gaussian smoothing of one channel for a horizontal run of kRun
@@ -107,8 +123,9 @@ SFOC_DEV void smooth_run_k1_123(const float* s, int i0, int P, float wc, float w
 // taps paired symmetrically, so odd responses of constant input are exactly
 // zero.  p points at the first output's centre.  Correlation form of the
 // convolution: out(x) = sum_k t(-k) I(x + k) -> odd taps act on
-// I(x - k) - I(x + k).
-template <int RHO>
+// I(x - k) - I(x + k).  USE: the orders that have this sigma (bit 0 the first,
+// which needs no dd; bit 1 the second).
+template <int RHO, int USE = 3>
 SFOC_DEV void row_run(const float* p, const float* tg, const float* td, const float* tdd, float og[kRun],
                       float od[kRun], float odd[kRun]) {
     float x[2 * RHO + kRun];
@@ -117,13 +134,13 @@ SFOC_DEV void row_run(const float* p, const float* tg, const float* td, const fl
 #pragma unroll
     for (int j = 0; j < kRun; ++j) {
         const float c = x[j + RHO];
-        float g = tg[0] * c, dd = tdd[0] * c, d = 0.f;
+        float g = tg[0] * c, dd = USE & 2 ? tdd[0] * c : 0.f, d = 0.f;
 #pragma unroll
         for (int k = 1; k <= RHO; ++k) {
             const float l = x[j + RHO - k], r = x[j + RHO + k];
             const float sm = l + r, df = l - r;
             g = fmaf(tg[k], sm, g);
-            dd = fmaf(tdd[k], sm, dd);
+            if (USE & 2) dd = fmaf(tdd[k], sm, dd);
             d = fmaf(td[k], df, d);
         }
         og[j] = g;
@@ -132,21 +149,22 @@ SFOC_DEV void row_run(const float* p, const float* tg, const float* td, const fl
     }
 }
 
-// Even (te) and odd (to) column taps on one map for a vertical run; the
-// first output's centre is element i0 of map s (pitch P).  The top element's
-// index is kept opaque to the compiler, so the reads share one base register
-// and fold their row offsets into the LDS instructions where those fit.
-template <int RHO>
-SFOC_DEV void col_run(const float* s, int i0, int P, const float* te, const float* to, float ev[kRun],
-                      float od[kRun]) {
+// Even (te) and odd (to) column taps on one map for a vertical run of RUN
+// outputs; the first output's centre is element i0 of map s (pitch P).  The
+// top element's index is kept opaque to the compiler, so the reads share one
+// base register and fold their row offsets into the LDS instructions where
+// those fit.
+template <int RHO, int RUN = kRun>
+SFOC_DEV void col_run(const float* s, int i0, int P, const float* te, const float* to, float ev[RUN],
+                      float od[RUN]) {
     int b = i0 - RHO * P;
     asm volatile("" : "+v"(b));
     const float* n = s + b;
-    float x[2 * RHO + kRun];
+    float x[2 * RHO + RUN];
 #pragma unroll
-    for (int q = 0; q < 2 * RHO + kRun; ++q) x[q] = n[q * P];
+    for (int q = 0; q < 2 * RHO + RUN; ++q) x[q] = n[q * P];
 #pragma unroll
-    for (int j = 0; j < kRun; ++j) {
+    for (int j = 0; j < RUN; ++j) {
         const float c = x[j + RHO];
         float e = te ? te[0] * c : 0.f, d = 0.f;
 #pragma unroll
@@ -178,10 +196,11 @@ SFOC_DEV void row_run_any(const float* p, int rho, const float* tg, const float*
         odd[j] = dd;
     }
 }
-SFOC_DEV void col_run_any(const float* p, int P, int rho, const float* te, const float* to, float ev[kRun],
-                          float od[kRun]) {
+template <int RUN = kRun>
+SFOC_DEV void col_run_any(const float* p, int P, int rho, const float* te, const float* to, float ev[RUN],
+                          float od[RUN]) {
 #pragma unroll
-    for (int j = 0; j < kRun; ++j) {
+    for (int j = 0; j < RUN; ++j) {
         const float c = p[j * P];
         float e = te ? te[0] * c : 0.f, d = 0.f;
         for (int k = 1; k <= rho; ++k) {
@@ -211,17 +230,6 @@ SFOC_DEV void col_run_any(const float* p, int P, int rho, const float* te, const
         default: CALL_ANY; break;                 \
     }
 
-// Two launch configurations of the 32 x 32 tile.  Configuration 0: three
-// workgroups per CU, two steered channel maps per group.  Configuration 1
-// (K = 1, rates 1-3, up to 16 channels): four workgroups per CU in at most
-// 40 KB of LDS and 128 VGPRs each: the basis columns in two halves (half-width
-// row-pass maps), one steered channel map per group, and the accumulators of
-// one order at a time.  Both give the same descriptors bit for bit.
-template <int Z, bool FAST, int VAR>
-constexpr int describe_wpc() { return VAR ? 4 : (Z >= 32 ? 2 : 3); }
-template <int Z, bool FAST, int VAR>
-constexpr int describe_cg() { return VAR ? 1 : (FAST ? 2 : (Z >= 4 ? 4 : Z)); }
-
 // The row sums, column sums and total of a tile that is not described, set
 // to zero (the layout of the describe kernel's aggregate output).
 SFOC_DEV void zero_tile_aggregates(const DescribeJob& J, int ty0, int tx0) {
@@ -235,19 +243,13 @@ SFOC_DEV void zero_tile_aggregates(const DescribeJob& J, int ty0, int tx0) {
     }
 }
 
-template <int Z, int CG, bool FAST, int VAR>
-__global__ __launch_bounds__(kNT, (describe_wpc<Z, FAST, VAR>())) void describe_kernel(const DescribeJob single,
-                                                          const DescribeJob* __restrict__ jobs,
-                                                          const int4* __restrict__ tiles,
-                                                          const uint8_t* __restrict__ tmask, const DescribeConsts C,
-                                                          int BSP_, int ISX, int BPP_, int IPP) {
-    extern __shared__ float lds[];
-    const int t = threadIdx.x;
-    DescribeJob J;
-    int ty0, tx0;
-    // Workgroups are dealt to the eight XCDs in turn; renumbered so that each
-    // XCD takes a contiguous run of tiles, whose overlapping input halos then
-    // meet in one L2.
+// The workgroup's job and tile; false where there is nothing to describe.
+// Workgroups are dealt to the eight XCDs in turn; renumbered so that each XCD
+// takes a contiguous run of tiles, whose overlapping input halos then meet in
+// one L2.
+__device__ __forceinline__ bool describe_tile(const DescribeJob& single, const DescribeJob* __restrict__ jobs,
+                            const int4* __restrict__ tiles, const uint8_t* __restrict__ tmask, DescribeJob& J, int& ty0,
+                            int& tx0) {
     const int nblk = (int)(gridDim.x * gridDim.y), q8 = nblk / 8 * 8;
     const int id = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     const int k = id < q8 ? (id % 8) * (q8 / 8) + id / 8 : id;
@@ -259,13 +261,13 @@ __global__ __launch_bounds__(kNT, (describe_wpc<Z, FAST, VAR>())) void describe_
         // zero (the box sums over the tiles that are described stay exact);
         // what = 2: a grid tile that is described if the mask marks it
         const int4 e = tiles[k];
-        if (e.x < 0) return;
+        if (e.x < 0) return false;
         J = jobs ? load_table(jobs, e.x) : single;
         ty0 = e.y;
         tx0 = e.z;
         if (e.w == 1 || (e.w == 2 && !tmask[(ty0 / kTS) * ((J.W + kTS - 1) / kTS) + tx0 / kTS])) {
             if (J.agg) zero_tile_aggregates(J, ty0, tx0);
-            return;
+            return false;
         }
     } else {
         J = single;
@@ -275,64 +277,226 @@ __global__ __launch_bounds__(kNT, (describe_wpc<Z, FAST, VAR>())) void describe_
         // inputs its aggregates are set to zero
         if (tmask && !tmask[(ty0 / kTS) * gridDim.x + tx0 / kTS]) {
             if (J.agg) zero_tile_aggregates(J, ty0, tx0);
-            return;
+            return false;
         }
     }
+    return true;
+}
+
+// The square input region of a tile (side `side`, top-left pixel (y0, x0),
+// reflect-101 borders) into simg (pitch P): eight rows' loads are issued
+// before any of their LDS stores.
+__device__ __forceinline__ void load_region(const DescribeJob& J, int y0, int x0, int side, float* simg, int P) {
     const float* __restrict__ img = J.img;
-    void* __restrict__ desc = J.desc;
+    const int t = threadIdx.x, H = J.H, W = J.W;
+    const int64_t ld = J.ld;
+    const bool inside = y0 >= 0 && x0 >= 0 && y0 + side <= H && x0 + side <= W;
+    constexpr int kRows = kNT / 64, kU = 8;
+    for (int b = t % 64; b < side; b += 64) {
+        const int gx = inside ? x0 + b : reflect101(x0 + b, W);
+        for (int a0 = t / 64; a0 < side; a0 += kRows * kU) {
+            float v[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int a = a0 + u * kRows;
+                v[u] = 0.f;
+                if (a < side) {
+                    const int gy = inside ? y0 + a : reflect101(y0 + a, H);
+                    v[u] = img[(int64_t)gy * ld + gx];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int a = a0 + u * kRows;
+                if (a < side) simg[a * P + b] = v[u];
+            }
+        }
+    }
+}
+
+// What a thread stores: a run of kRun pixels of one row.  Each thread stores
+// its run of a channel as one vector (8 threads cover a 128-byte row segment),
+// so every store instruction writes whole cache lines; unaligned widths, tiles
+// whose column origin is not a multiple of kRun and the right edge fall back
+// to scalar stores.  The channel sums for the integral images (d1, d2)
+// accumulate in channel order.
+struct RunOut {
+    int64_t plane, off0;
+    int gy, gx0, W;
+    bool row, full;    // the row lies in the image; the run can be one vector
+    double d1[kRun], d2[kRun];
+};
+__device__ __forceinline__ void init_run(RunOut& O, const DescribeJob& J, const DescribeConsts& C, int ty0, int tx0) {
+    const int t = threadIdx.x;
+    O.plane = (int64_t)J.H * J.W;
+    O.W = J.W;
+    O.gy = ty0 + t / (kTS / kRun);
+    O.gx0 = tx0 + (t % (kTS / kRun)) * kRun;
+    const size_t align = C.dtype == SFOC_DTYPE_F32 ? 15 : 7;
+    O.full = (J.W & (kRun - 1)) == 0 && (O.gx0 & (kRun - 1)) == 0 && ((uintptr_t)J.desc & align) == 0 &&
+             O.gx0 + kRun <= J.W;
+    O.row = O.gy < J.H;
+    O.off0 = (int64_t)O.gy * J.W + O.gx0;
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) O.d1[j] = O.d2[j] = 0.0;
+}
+
+// One order block, channels [lo, hi) of acc: normalisation, rounding, store
+// (channel c goes to plane c0 + c), channel sums.
+template <int Z>
+__device__ __forceinline__ void emit_block(const float (&acc)[Z][kRun], int lo, int hi, int c0, void* __restrict__ desc, bool sums,
+                         const DescribeConsts& C, RunOut& O) {
+    float inv[kRun];
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) {
+        float s2 = 0.f;
+#pragma unroll
+        for (int c = 0; c < Z; ++c)
+            if (c >= lo && c < hi) s2 = fmaf(acc[c][j], acc[c][j], s2);
+        inv[j] = rsqrtf(s2 + C.eps);
+    }
+    if (!O.row) return;
+#pragma unroll
+    for (int c = 0; c < Z; ++c) {
+        if (c < lo || c >= hi) continue;
+        float v[kRun];
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) v[j] = acc[c][j] * inv[j];
+        if (C.dtype == SFOC_DTYPE_F32) {
+            float* dst = (float*)desc + (c0 + c) * O.plane + O.off0;
+            if (O.full) {
+                *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kRun; ++j)
+                    if (O.gx0 + j < O.W) dst[j] = v[j];
+            }
+        } else {
+            uint16_t q[kRun];
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) {
+                q[j] = C.dtype == SFOC_DTYPE_BF16 ? f32_to_bf16_bits(v[j]) : f32_to_f16_bits(v[j]);
+                v[j] = C.dtype == SFOC_DTYPE_BF16 ? bf16_bits_to_f32(q[j]) : f16_bits_to_f32(q[j]);
+            }
+            uint16_t* dst = (uint16_t*)desc + (c0 + c) * O.plane + O.off0;
+            if (O.full) {
+                *(ushort4*)dst = make_ushort4(q[0], q[1], q[2], q[3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kRun; ++j)
+                    if (O.gx0 + j < O.W) dst[j] = q[j];
+            }
+        }
+        if (sums) {
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) {
+                const double dv = (double)v[j];
+                O.d1[j] += dv;
+                O.d2[j] = fma(dv, dv, O.d2[j]);
+            }
+        }
+    }
+}
+
+// Per-pixel channel sums of the stored values (zero outside the image) into
+// the integral-image buffers, and this tile's aggregates for the prefix pass:
+// row sums (the 8 lanes of a row, butterfly), column sums (the 8 rows of a
+// wave, butterfly, then the 4 waves in order) and the total (the 32 column
+// sums, butterfly).  Every sum is taken in a fixed order, so the integral
+// images are reproducible.  cs: 2 KB of LDS that no thread still reads
+// ([map][wave][column]).
+__device__ __forceinline__ void emit_sums(const DescribeJob& J, RunOut& O, int ty0, int tx0, double* cs) {
+    const int t = threadIdx.x, H = J.H, W = J.W, gy = O.gy, gx0 = O.gx0;
     double* __restrict__ integ1 = J.integ1;
     double* __restrict__ integ2 = J.integ2;
-    const int H = J.H, W = J.W;
-    const int64_t ld = J.ld;
-    // The K = 1, rates 1..3 path has Q = 3: its tile geometry is compile-time,
-    // so the index arithmetic below divides by constants.
-    constexpr int kFastQ = 3, kFastBSP = (kTS + 2 * kFastQ + kRun - 1) / kRun * kRun;
-    const int Q = FAST ? kFastQ : C.Q;
-    const int BSP = FAST ? kFastBSP : BSP_;
-    const int BPP = FAST ? (kFastBSP | 1) : BPP_;
-    const int R = C.R;
+    double(&d1)[kRun] = O.d1;
+    double(&d2)[kRun] = O.d2;
+#pragma unroll
+    for (int j = 0; j < kRun; ++j)
+        if (gy >= H || gx0 + j >= W) d1[j] = d2[j] = 0.0;
+    if (gy < H) {
+        const int64_t io = (int64_t)(gy + 1) * (W + 1) + gx0 + 1;
+#pragma unroll
+        for (int j = 0; j < kRun; ++j)
+            if (gx0 + j < W) {
+                integ1[io + j] = d1[j];
+                integ2[io + j] = d2[j];
+            }
+    }
+    const IntegAgg ag = integ_agg(H, W);
+    double* __restrict__ agg = J.agg;
+    const int tb = tx0 / kTS, ta = ty0 / kTS;
+    double r1 = ((d1[0] + d1[1]) + d1[2]) + d1[3];
+    double r2 = ((d2[0] + d2[1]) + d2[2]) + d2[3];
+#pragma unroll
+    for (int d = 1; d < kTS / kRun; d <<= 1) {
+        r1 += __shfl_xor(r1, d, 64);
+        r2 += __shfl_xor(r2, d, 64);
+    }
+    if ((t & (kTS / kRun - 1)) == 0 && gy < H) {
+        agg[ag.rs1 + tb * (int64_t)H + gy] = r1;
+        agg[ag.rs2 + tb * (int64_t)H + gy] = r2;
+    }
+#pragma unroll
+    for (int j = 0; j < kRun; ++j)
+#pragma unroll
+        for (int d = kTS / kRun; d < 64; d <<= 1) {
+            d1[j] += __shfl_xor(d1[j], d, 64);
+            d2[j] += __shfl_xor(d2[j], d, 64);
+        }
+    const int lane = t & 63, wv = t >> 6;
+    if (lane < kTS / kRun) {
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) {
+            cs[(0 * (kNT / 64) + wv) * kTS + lane * kRun + j] = d1[j];
+            cs[(1 * (kNT / 64) + wv) * kTS + lane * kRun + j] = d2[j];
+        }
+    }
+    __syncthreads();
+    static_assert(2 * kTS == 64, "the column sums of both maps fill one wave");
+    if (t < 2 * kTS) {
+        // wave 0: lane q * 32 + x sums column x of map q over the four
+        // waves in order, then the 32 columns of each map are summed by
+        // a butterfly within its half-wave (a fixed order)
+        const int q = t / kTS, x = t % kTS;
+        double c = 0.0;
+#pragma unroll
+        for (int w = 0; w < kNT / 64; ++w) c += cs[(q * (kNT / 64) + w) * kTS + x];
+        if (tx0 + x < W) agg[(q ? ag.cs2 : ag.cs1) + ta * (int64_t)W + tx0 + x] = c;
+#pragma unroll
+        for (int d = 1; d < kTS; d <<= 1) c += __shfl_xor(c, d, 64);
+        if (x == 0) agg[(q ? ag.tt2 : ag.tt1) + ta * ag.ntx + tb] = c;
+    }
+}
+
+template <int Z, int CG>
+__global__ __launch_bounds__(kNT, Z >= 32 ? 2 : 3) void describe_kernel(const DescribeJob single,
+                                                          const DescribeJob* __restrict__ jobs,
+                                                          const int4* __restrict__ tiles,
+                                                          const uint8_t* __restrict__ tmask, const DescribeConsts C,
+                                                          int BSP, int ISX, int BPP, int IPP) {
+    extern __shared__ float lds[];
+    const int t = threadIdx.x;
+    DescribeJob J;
+    int ty0, tx0;
+    if (!describe_tile(single, jobs, tiles, tmask, J, ty0, tx0)) return;
+    const int Q = C.Q, R = C.R;
     const int nrun = BSP / kRun;
     float* simg = lds;
     float* srow = simg + ISX * IPP;
     float* sbas = lds;   // written once the image and row-pass maps are dead
     const int BB = BSP * BPP;   // one basis / channel map
 
-    // 1. input region (top-left at tile origin - Q - R), reflect-101 borders;
-    //    four rows' loads are issued before any of their LDS stores.
-    {
-        const int y0 = ty0 - Q - R, x0 = tx0 - Q - R;
-        const bool inside = y0 >= 0 && x0 >= 0 && y0 + ISX <= H && x0 + ISX <= W;
-        constexpr int kRows = kNT / 64, kU = 4;
-        for (int b = t % 64; b < ISX; b += 64) {
-            const int gx = inside ? x0 + b : reflect101(x0 + b, W);
-            for (int a0 = t / 64; a0 < ISX; a0 += kRows * kU) {
-                float v[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    const int a = a0 + u * kRows;
-                    v[u] = 0.f;
-                    if (a < ISX) {
-                        const int gy = inside ? y0 + a : reflect101(y0 + a, H);
-                        v[u] = img[(int64_t)gy * ld + gx];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    const int a = a0 + u * kRows;
-                    if (a < ISX) simg[a * IPP + b] = v[u];
-                }
-            }
-        }
-    }
+    // 1. input region (top-left at tile origin - Q - R)
+    load_region(J, ty0 - Q - R, tx0 - Q - R, ISX, simg, IPP);
     __syncthreads();
 
     // 2. basis responses Gx, Gy, Gxx, Gyy, Gxy * I summed over sigma, held in
     //    registers by the thread that owns each vertical run of kRun pixels.
     // runs: (BSP / kRun) vertical runs in each of the BSr = kTS + 2Q columns
-    // that steering reads (the padding columns up to BSP are skipped); BSP =
-    // 40 and BSr = 38 when Q = 3 (the K = 1, rates 1-3 path), BSP at most 48
-    // otherwise.
-    constexpr int kMaxOwn = FAST ? 2 : 3;
+    // that steering reads (the padding columns up to BSP are skipped); BSP at
+    // most 48.
+    constexpr int kMaxOwn = 3;
     float bas[kMaxOwn][5][kRun];
 #pragma unroll
     for (int o = 0; o < kMaxOwn; ++o)
@@ -342,174 +506,89 @@ __global__ __launch_bounds__(kNT, (describe_wpc<Z, FAST, VAR>())) void describe_
             for (int j = 0; j < kRun; ++j) bas[o][m][j] = 0.f;
     const int BSr = kTS + 2 * Q;      // rows / columns of the basis maps that steering reads
     const int ncolrun = nrun * BSr;   // (row-run, column) pairs
-    if constexpr (VAR == 1) {
-        // The basis columns in two halves, [0, 20) and [20, 38): per sigma
-        // and half, a row pass over the half's 20 columns (five runs per
-        // row) into half-width maps, then the column pass of that half.
-        // Thread t owns run t of each half (10 row runs x the half's
-        // columns), so bas[h] holds its half-h run for the whole sigma sum.
-        constexpr int kHW = kFastBSP / 2, kHR = kHW / kRun;
-        static_assert(kMaxOwn == 2 && kFastBSP == 40 && kNT >= kHW * (kFastBSP / kRun), "two halves of 40 columns");
-        for (int s = 0; s < C.nsig; ++s) {
-            const int rho = C.rad[s];
-            const float* tg = C.taps + C.off[s];
-            const float* td = tg + (rho + 1);
-            const float* tdd = td + (rho + 1);
-            const float cn = C.cnorm[s];
-            const int use = C.use[s];
-            const int rows = BSP + 2 * rho;
-            const int ig = ISX * IPP, id = ig + rows * kHalfPitch, idd = ig + 2 * rows * kHalfPitch;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                for (int e = t; e < rows * kHR; e += kNT) {
-                    const int a = e / kHR, b0 = (e - a * kHR) * kRun;
-                    const float* p = simg + (a + R - rho) * IPP + (h * kHW + b0 + R);
-                    float og[kRun], od[kRun], odd[kRun];
+    for (int s = 0; s < C.nsig; ++s) {
+        const int rho = C.rad[s];
+        const float* tg = C.taps + C.off[s];
+        const float* td = tg + (rho + 1);
+        const float* tdd = td + (rho + 1);
+        const float cn = C.cnorm[s];
+        const int rows = BSP + 2 * rho;
+        // row pass on rows [0, rows) x cols [0, BSP): horizontal runs.  Row a
+        // of this pass is image-region row a + R - rho.
+        for (int e = t; e < rows * nrun; e += kNT) {
+            const int a = e / nrun, b0 = (e - a * nrun) * kRun;
+            const float* p = simg + (a + R - rho) * IPP + (b0 + R);
+            float og[kRun], od[kRun], odd[kRun];
 #define ROW_T(RR) row_run<RR>(p, tg, td, tdd, og, od, odd)
-                    SFOC_RADIUS_SWITCH(rho, ROW_T, row_run_any(p, rho, tg, td, tdd, og, od, odd))
+            SFOC_RADIUS_SWITCH(rho, ROW_T, row_run_any(p, rho, tg, td, tdd, og, od, odd))
 #undef ROW_T
-                    float* w = srow + a * kHalfPitch + b0;
+            float* w = srow + a * BPP + b0;
 #pragma unroll
-                    for (int j = 0; j < kRun; ++j) {
-                        w[j] = og[j];
-                        w[rows * kHalfPitch + j] = od[j];
-                        w[2 * rows * kHalfPitch + j] = odd[j];
-                    }
-                }
-                __syncthreads();
-                const int wh = h ? BSr - kHW : kHW;   // basis columns of this half
-                if (t < wh * nrun) {
-                    const int b = t % wh, a0 = (t / wh) * kRun;
-                    float bx[kRun], by[kRun], bxx[kRun], byy[kRun], bxy[kRun], dummy[kRun];
-                    const int c0 = (a0 + rho) * kHalfPitch + b;
-#define COL_T(RR)                                                       \
-    do {                                                                \
-        col_run<RR>(lds, ig + c0, kHalfPitch, tdd, td, byy, by);        \
-        col_run<RR>(lds, id + c0, kHalfPitch, tg, td, bx, bxy);         \
-        col_run<RR>(lds, idd + c0, kHalfPitch, tg, nullptr, bxx, dummy); \
-    } while (0)
-#define COL_ANY                                                         \
-    do {                                                                \
-        col_run_any(lds + ig + c0, kHalfPitch, rho, tdd, td, byy, by);  \
-        col_run_any(lds + id + c0, kHalfPitch, rho, tg, td, bx, bxy);   \
-        col_run_any(lds + idd + c0, kHalfPitch, rho, tg, nullptr, bxx, dummy); \
-    } while (0)
-                    SFOC_RADIUS_SWITCH(rho, COL_T, COL_ANY)
-#undef COL_T
-#undef COL_ANY
-                    (void)dummy;
-#pragma unroll
-                    for (int j = 0; j < kRun; ++j) {
-                        if (use & 1) {
-                            bas[h][0][j] = fmaf(cn, bx[j], bas[h][0][j]);
-                            bas[h][1][j] = fmaf(cn, by[j], bas[h][1][j]);
-                        }
-                        if (use & 2) {
-                            bas[h][2][j] = fmaf(cn, bxx[j], bas[h][2][j]);
-                            bas[h][3][j] = fmaf(cn, byy[j], bas[h][3][j]);
-                            bas[h][4][j] = fmaf(cn, bxy[j], bas[h][4][j]);
-                        }
-                    }
-                }
-                __syncthreads();
+            for (int j = 0; j < kRun; ++j) {
+                w[j] = og[j];
+                w[rows * BPP + j] = od[j];
+                w[2 * rows * BPP + j] = odd[j];
             }
         }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int wh = h ? BSr - kHW : kHW;
-            if (t < wh * nrun) {
-                const int b = h * kHW + t % wh, a0 = (t / wh) * kRun;
-#pragma unroll
-                for (int m = 0; m < 5; ++m)
-#pragma unroll
-                    for (int j = 0; j < kRun; ++j) sbas[m * BB + (a0 + j) * BPP + b] = bas[h][m][j];
-            }
-        }
-    } else {
-        for (int s = 0; s < C.nsig; ++s) {
-            const int rho = C.rad[s];
-            const float* tg = C.taps + C.off[s];
-            const float* td = tg + (rho + 1);
-            const float* tdd = td + (rho + 1);
-            const float cn = C.cnorm[s];
-            const int rows = BSP + 2 * rho;
-            // row pass on rows [0, rows) x cols [0, BSP): horizontal runs.  Row a
-            // of this pass is image-region row a + R - rho.
-            for (int e = t; e < rows * nrun; e += kNT) {
-                const int a = e / nrun, b0 = (e - a * nrun) * kRun;
-                const float* p = simg + (a + R - rho) * IPP + (b0 + R);
-                float og[kRun], od[kRun], odd[kRun];
-#define ROW_T(RR) row_run<RR>(p, tg, td, tdd, og, od, odd)
-                SFOC_RADIUS_SWITCH(rho, ROW_T, row_run_any(p, rho, tg, td, tdd, og, od, odd))
-#undef ROW_T
-                float* w = srow + a * BPP + b0;
-#pragma unroll
-                for (int j = 0; j < kRun; ++j) {
-                    w[j] = og[j];
-                    w[rows * BPP + j] = od[j];
-                    w[2 * rows * BPP + j] = odd[j];
-                }
-            }
-            __syncthreads();
-            // column pass on vertical runs; output row a reads pass rows a + rho + k.
-            const float* rg = srow;
-            const float* rd = srow + rows * BPP;
-            const float* rdd = srow + 2 * rows * BPP;
-            const int ig = ISX * IPP, id = ig + rows * BPP, idd = ig + 2 * rows * BPP;   // the same, as lds indices
-            const int use = C.use[s];
-#pragma unroll
-            for (int o = 0; o < kMaxOwn; ++o) {
-                const int e = t + o * kNT;
-                if (e < ncolrun) {
-                    const int b = e % BSr, a0 = (e / BSr) * kRun;
-                    float bx[kRun], by[kRun], bxx[kRun], byy[kRun], bxy[kRun], dummy[kRun];
-                    const int c0 = (a0 + rho) * BPP + b;
-                    // rg -> By (odd d), Byy (even dd); rd -> Bx (even g), Bxy (odd d);
-                    // rdd -> Bxx (even g).
-#define COL_T(RR)                                                \
-        do {                                                         \
-            col_run<RR>(lds, ig + c0, BPP, tdd, td, byy, by);        \
-            col_run<RR>(lds, id + c0, BPP, tg, td, bx, bxy);         \
-            col_run<RR>(lds, idd + c0, BPP, tg, nullptr, bxx, dummy); \
-        } while (0)
-#define COL_ANY                                                  \
-        do {                                                         \
-            col_run_any(rg + c0, BPP, rho, tdd, td, byy, by);        \
-            col_run_any(rd + c0, BPP, rho, tg, td, bx, bxy);         \
-            col_run_any(rdd + c0, BPP, rho, tg, nullptr, bxx, dummy); \
-        } while (0)
-                    SFOC_RADIUS_SWITCH(rho, COL_T, COL_ANY)
-#undef COL_T
-#undef COL_ANY
-                    (void)dummy;
-#pragma unroll
-                    for (int j = 0; j < kRun; ++j) {
-                        // the 2-D normalisation cn of this sigma, applied as the
-                        // response joins the sum over sigma
-                        if (use & 1) {
-                            bas[o][0][j] = fmaf(cn, bx[j], bas[o][0][j]);
-                            bas[o][1][j] = fmaf(cn, by[j], bas[o][1][j]);
-                        }
-                        if (use & 2) {
-                            bas[o][2][j] = fmaf(cn, bxx[j], bas[o][2][j]);
-                            bas[o][3][j] = fmaf(cn, byy[j], bas[o][3][j]);
-                            bas[o][4][j] = fmaf(cn, bxy[j], bas[o][4][j]);
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-        }
+        __syncthreads();
+        // column pass on vertical runs; output row a reads pass rows a + rho + k.
+        const float* rg = srow;
+        const float* rd = srow + rows * BPP;
+        const float* rdd = srow + 2 * rows * BPP;
+        const int ig = ISX * IPP, id = ig + rows * BPP, idd = ig + 2 * rows * BPP;   // the same, as lds indices
+        const int use = C.use[s];
 #pragma unroll
         for (int o = 0; o < kMaxOwn; ++o) {
             const int e = t + o * kNT;
             if (e < ncolrun) {
                 const int b = e % BSr, a0 = (e / BSr) * kRun;
+                float bx[kRun], by[kRun], bxx[kRun], byy[kRun], bxy[kRun], dummy[kRun];
+                const int c0 = (a0 + rho) * BPP + b;
+                // rg -> By (odd d), Byy (even dd); rd -> Bx (even g), Bxy (odd d);
+                // rdd -> Bxx (even g).
+#define COL_T(RR)                                                \
+    do {                                                         \
+        col_run<RR>(lds, ig + c0, BPP, tdd, td, byy, by);        \
+        col_run<RR>(lds, id + c0, BPP, tg, td, bx, bxy);         \
+        col_run<RR>(lds, idd + c0, BPP, tg, nullptr, bxx, dummy); \
+    } while (0)
+#define COL_ANY                                                  \
+    do {                                                         \
+        col_run_any(rg + c0, BPP, rho, tdd, td, byy, by);        \
+        col_run_any(rd + c0, BPP, rho, tg, td, bx, bxy);         \
+        col_run_any(rdd + c0, BPP, rho, tg, nullptr, bxx, dummy); \
+    } while (0)
+                SFOC_RADIUS_SWITCH(rho, COL_T, COL_ANY)
+#undef COL_T
+#undef COL_ANY
+                (void)dummy;
 #pragma unroll
-                for (int m = 0; m < 5; ++m)
-#pragma unroll
-                    for (int j = 0; j < kRun; ++j) sbas[m * BB + (a0 + j) * BPP + b] = bas[o][m][j];
+                for (int j = 0; j < kRun; ++j) {
+                    // the 2-D normalisation cn of this sigma, applied as the
+                    // response joins the sum over sigma
+                    if (use & 1) {
+                        bas[o][0][j] = fmaf(cn, bx[j], bas[o][0][j]);
+                        bas[o][1][j] = fmaf(cn, by[j], bas[o][1][j]);
+                    }
+                    if (use & 2) {
+                        bas[o][2][j] = fmaf(cn, bxx[j], bas[o][2][j]);
+                        bas[o][3][j] = fmaf(cn, byy[j], bas[o][3][j]);
+                        bas[o][4][j] = fmaf(cn, bxy[j], bas[o][4][j]);
+                    }
+                }
             }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int o = 0; o < kMaxOwn; ++o) {
+        const int e = t + o * kNT;
+        if (e < ncolrun) {
+            const int b = e % BSr, a0 = (e / BSr) * kRun;
+#pragma unroll
+            for (int m = 0; m < 5; ++m)
+#pragma unroll
+                for (int j = 0; j < kRun; ++j) sbas[m * BB + (a0 + j) * BPP + b] = bas[o][m][j];
         }
     }
     __syncthreads();
@@ -518,83 +597,9 @@ __global__ __launch_bounds__(kNT, (describe_wpc<Z, FAST, VAR>())) void describe_
     //    of this thread's horizontal run of kRun outputs.
     float acc[Z][kRun];
     float* schan = sbas + 5 * BB;
-    // The fast path has both orders (N = Z / 2 at compile time).
-    const int N = FAST ? Z / 2 : C.N;
-    const int B = 2 * C.K + 1;
-    const int oy = t / (kTS / kRun), ox0 = (t % (kTS / kRun)) * kRun;
-
-    // 4. (per order block) normalisation, rounding, store, channel sums.
-    //    Each thread stores its run of kRun pixels of a channel as one
-    //    vector (8 threads cover a 128-byte row segment), so every store
-    //    instruction writes whole cache lines; unaligned widths, tiles whose
-    //    column origin is not a multiple of kRun and the right edge fall back
-    //    to scalar stores.  The channel sums for the
-    //    integral images accumulate in channel order.
-    const int64_t plane = (int64_t)H * W;
-    const int gy = ty0 + oy, gx0 = tx0 + ox0;
-    const size_t align = C.dtype == SFOC_DTYPE_F32 ? 15 : 7;
-    const bool full =
-        (W & (kRun - 1)) == 0 && (gx0 & (kRun - 1)) == 0 && ((uintptr_t)desc & align) == 0 && gx0 + kRun <= W;
-    const int64_t off0 = (int64_t)gy * W + gx0;
-    double d1[kRun], d2[kRun];
+    const int N = C.N, B = 2 * C.K + 1;
 #pragma unroll
-    for (int j = 0; j < kRun; ++j) d1[j] = d2[j] = 0.0;
-    auto emit = [&](int lo, int hi) {   // channels [lo, hi): one order block
-        float inv[kRun];
-#pragma unroll
-        for (int j = 0; j < kRun; ++j) {
-            float s2 = 0.f;
-#pragma unroll
-            for (int c = 0; c < Z; ++c)
-                if (c >= lo && c < hi) s2 = fmaf(acc[c][j], acc[c][j], s2);
-            inv[j] = rsqrtf(s2 + C.eps);
-        }
-        if (gy >= H) return;
-#pragma unroll
-        for (int c = 0; c < Z; ++c) {
-            if (c < lo || c >= hi) continue;
-            float v[kRun];
-#pragma unroll
-            for (int j = 0; j < kRun; ++j) v[j] = acc[c][j] * inv[j];
-            if (C.dtype == SFOC_DTYPE_F32) {
-                float* dst = (float*)desc + c * plane + off0;
-                if (full) {
-                    *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < kRun; ++j)
-                        if (gx0 + j < W) dst[j] = v[j];
-                }
-            } else {
-                uint16_t q[kRun];
-#pragma unroll
-                for (int j = 0; j < kRun; ++j) {
-                    q[j] = C.dtype == SFOC_DTYPE_BF16 ? f32_to_bf16_bits(v[j]) : f32_to_f16_bits(v[j]);
-                    v[j] = C.dtype == SFOC_DTYPE_BF16 ? bf16_bits_to_f32(q[j]) : f16_bits_to_f32(q[j]);
-                }
-                uint16_t* dst = (uint16_t*)desc + c * plane + off0;
-                if (full) {
-                    *(ushort4*)dst = make_ushort4(q[0], q[1], q[2], q[3]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < kRun; ++j)
-                        if (gx0 + j < W) dst[j] = q[j];
-                }
-            }
-            if (integ1) {
-#pragma unroll
-                for (int j = 0; j < kRun; ++j) {
-                    const double dv = (double)v[j];
-                    d1[j] += dv;
-                    d2[j] = fma(dv, dv, d2[j]);
-                }
-            }
-        }
-    };
-    // channels [lo, hi) in groups of CG: steer into LDS, then smooth
-    auto steer_smooth = [&](int lo, int hi) {
-#pragma unroll
-    for (int c0 = lo; c0 < hi; c0 += CG) {
+    for (int c0 = 0; c0 < Z; c0 += CG) {
         // thread index laundered per group: keeps the group's LDS addresses
         // from being hoisted (and kept live) across the whole channel loop.
         int tl = t;
@@ -628,107 +633,242 @@ __global__ __launch_bounds__(kNT, (describe_wpc<Z, FAST, VAR>())) void describe_
             if (c < Z) {
                 const float* w = (c < N) ? C.w1 : C.w2;
                 const float* ch = schan + cc * BB + obase;
-                if (FAST) {
-                    smooth_run_k1_123(lds, (5 + cc) * BB + obase, BPP, w[4], w[1], w[0], acc[c]);
-                    // one channel's reads in flight at a time (the scheduler
-                    // would otherwise hoist all of a group's LDS reads)
-                    __builtin_amdgcn_sched_barrier(0);
-                } else {
 #pragma unroll
-                    for (int j = 0; j < kRun; ++j) {
-                        float a = 0.f;
-                        for (int di = 0; di < C.ndil; ++di) {
-                            const int r = C.dil[di];
-                            for (int i = 0; i < B; ++i)
-                                for (int jj = 0; jj < B; ++jj)
-                                    a = fmaf(w[i * B + jj], ch[(i - C.K) * r * BPP + (jj - C.K) * r + j], a);
-                        }
-                        acc[c][j] = a;
+                for (int j = 0; j < kRun; ++j) {
+                    float a = 0.f;
+                    for (int di = 0; di < C.ndil; ++di) {
+                        const int r = C.dil[di];
+                        for (int i = 0; i < B; ++i)
+                            for (int jj = 0; jj < B; ++jj)
+                                a = fmaf(w[i * B + jj], ch[(i - C.K) * r * BPP + (jj - C.K) * r + j], a);
                     }
+                    acc[c][j] = a;
                 }
             }
         }
         __syncthreads();
     }
-    };
-    if constexpr (VAR == 1) {
-        // one order at a time: its accumulators die at its emit
-        steer_smooth(0, Z / 2);
-        emit(0, Z / 2);
-        steer_smooth(Z / 2, Z);
-        emit(Z / 2, Z);
-    } else {
-        steer_smooth(0, Z);
-        emit(0, N);
-        emit(N, Z);
-    }
-    if (integ1) {
-        // Per-pixel channel sums of the stored values (zero outside the
-        // image) into the integral-image buffers, and this tile's aggregates
-        // for the prefix pass: row sums (the 8 lanes of a row, butterfly),
-        // column sums (the 8 rows of a wave, butterfly, then the 4 waves in
-        // order) and the total (the 32 column sums, butterfly).  Every sum is
-        // taken in a fixed order, so the integral images are reproducible.
-#pragma unroll
-        for (int j = 0; j < kRun; ++j)
-            if (gy >= H || gx0 + j >= W) d1[j] = d2[j] = 0.0;
-        if (gy < H) {
-            const int64_t io = (int64_t)(gy + 1) * (W + 1) + gx0 + 1;
-#pragma unroll
-            for (int j = 0; j < kRun; ++j)
-                if (gx0 + j < W) {
-                    integ1[io + j] = d1[j];
-                    integ2[io + j] = d2[j];
-                }
-        }
-        const IntegAgg ag = integ_agg(H, W);
-        double* __restrict__ agg = J.agg;
-        const int tb = tx0 / kTS, ta = ty0 / kTS;
-        double r1 = ((d1[0] + d1[1]) + d1[2]) + d1[3];
-        double r2 = ((d2[0] + d2[1]) + d2[2]) + d2[3];
-#pragma unroll
-        for (int d = 1; d < kTS / kRun; d <<= 1) {
-            r1 += __shfl_xor(r1, d, 64);
-            r2 += __shfl_xor(r2, d, 64);
-        }
-        if ((t & (kTS / kRun - 1)) == 0 && gy < H) {
-            agg[ag.rs1 + tb * (int64_t)H + gy] = r1;
-            agg[ag.rs2 + tb * (int64_t)H + gy] = r2;
-        }
-#pragma unroll
-        for (int j = 0; j < kRun; ++j)
-#pragma unroll
-            for (int d = kTS / kRun; d < 64; d <<= 1) {
-                d1[j] += __shfl_xor(d1[j], d, 64);
-                d2[j] += __shfl_xor(d2[j], d, 64);
-            }
-        double* cs = reinterpret_cast<double*>(lds);   // [map][wave][column], then [map][column]
-        const int lane = t & 63, wv = t >> 6;
-        if (lane < kTS / kRun) {
-#pragma unroll
-            for (int j = 0; j < kRun; ++j) {
-                cs[(0 * (kNT / 64) + wv) * kTS + lane * kRun + j] = d1[j];
-                cs[(1 * (kNT / 64) + wv) * kTS + lane * kRun + j] = d2[j];
-            }
-        }
-        __syncthreads();
-        static_assert(2 * kTS == 64, "the column sums of both maps fill one wave");
-        if (t < 2 * kTS) {
-            // wave 0: lane q * 32 + x sums column x of map q over the four
-            // waves in order, then the 32 columns of each map are summed by
-            // a butterfly within its half-wave (a fixed order)
-            const int q = t / kTS, x = t % kTS;
-            double c = 0.0;
-#pragma unroll
-            for (int w = 0; w < kNT / 64; ++w) c += cs[(q * (kNT / 64) + w) * kTS + x];
-            if (tx0 + x < W) agg[(q ? ag.cs2 : ag.cs1) + ta * (int64_t)W + tx0 + x] = c;
-#pragma unroll
-            for (int d = 1; d < kTS; d <<= 1) c += __shfl_xor(c, d, 64);
-            if (x == 0) agg[(q ? ag.tt2 : ag.tt1) + ta * ag.ntx + tb] = c;
-        }
-    }
+
+    // 4. (per order block) normalisation, rounding, store, channel sums.
+    RunOut O;
+    init_run(O, J, C, ty0, tx0);
+    emit_block<Z>(acc, 0, N, 0, J.desc, J.integ1 != nullptr, C, O);
+    emit_block<Z>(acc, N, Z, 0, J.desc, J.integ1 != nullptr, C, O);
+    if (J.integ1) emit_sums(J, O, ty0, tx0, reinterpret_cast<double*>(lds));
 }
 
+// ---- K = 1, rates 1, 2, 3, both orders ----------------------------------------
+// Row pass, then column pass, of one sigma; the responses join the thread's
+// sums over sigma.  RHO = 0: any radius.  Thread t owns the column runs
+// t + o kNT of three rows: 494 runs of 38 columns, so that every wave has two
+// rounds of three rows (runs of four rows: 380, two rounds for half of the
+// waves).  USE: see row_run; what an order does not read is not computed.
+template <int RHO, int USE>
+__device__ __forceinline__ void sigma_pass(const float* simg, int IPP, float* srow, const DescribeConsts& C, int s,
+                         float (&bas)[kCOwn][5][kCRun]) {
+    // (the index laundered: what is derived from it is not hoisted out of the
+    // sigma loop, for every radius at once)
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    const int rho = RHO ? RHO : C.rad[s], R = C.R;
+    const float* tg = C.taps + C.off[s];
+    const float* td = tg + (rho + 1);
+    const float* tdd = td + (rho + 1);
+    const float cn = C.cnorm[s];
+    const int use = RHO ? USE : C.use[s];
+    const int rows = kB + 2 * rho, map = rows * kRP;
+    // Row a of this pass is image-region row a + R - rho.  The lanes run along
+    // the rows: with odd pitches their accesses fall on different banks.  (The
+    // last run's two columns past the map are never read.)
+    constexpr int kRuns = (kB + kRun - 1) / kRun;
+    for (int e = t; e < rows * kRuns; e += kNT) {
+        const int q = e / rows, a = e - q * rows, b0 = q * kRun;
+        const float* p = simg + (a + R - rho) * IPP + (b0 + R);
+        float og[kRun], od[kRun], odd[kRun];
+        if constexpr (RHO > 0) row_run<RHO, USE>(p, tg, td, tdd, og, od, odd);
+        else row_run_any(p, rho, tg, td, tdd, og, od, odd);
+        float* w = srow + a * kRP + b0;
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) {
+            w[j] = og[j];
+            w[map + j] = od[j];
+            if (USE & 2) w[2 * map + j] = odd[j];
+        }
+    }
+    __syncthreads();
+    // output row a reads pass rows a + rho + k; g -> By (odd d), Byy (even dd);
+    // d -> Bx (even g), Bxy (odd d); dd -> Bxx (even g)
+#pragma unroll
+    for (int o = 0; o < kCOwn; ++o) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int e = t + o * kNT;
+        if (e < kCRuns * kB) {
+            const int c0 = (e / kB * kCRun + rho) * kRP + e % kB;
+            float bx[kCRun], by[kCRun], bxx[kCRun], byy[kCRun], bxy[kCRun], none[kCRun];
+            const float* t1 = USE & 1 ? tg : nullptr;
+            const float* t1d = USE & 1 ? td : nullptr;
+            const float* t2dd = USE & 2 ? tdd : nullptr;
+            const float* t2d = USE & 2 ? td : nullptr;
+            if constexpr (RHO > 0) {
+                col_run<RHO, kCRun>(srow, c0, kRP, t2dd, t1d, byy, by);
+                col_run<RHO, kCRun>(srow, c0 + map, kRP, t1, t2d, bx, bxy);
+                if (USE & 2) col_run<RHO, kCRun>(srow, c0 + 2 * map, kRP, tg, nullptr, bxx, none);
+            } else {
+                col_run_any<kCRun>(srow + c0, kRP, rho, t2dd, t1d, byy, by);
+                col_run_any<kCRun>(srow + c0 + map, kRP, rho, t1, t2d, bx, bxy);
+                if (USE & 2) col_run_any<kCRun>(srow + c0 + 2 * map, kRP, rho, tg, nullptr, bxx, none);
+            }
+            (void)none;
+            // the 2-D normalisation cn of this sigma is applied here
+#pragma unroll
+            for (int j = 0; j < kCRun; ++j) {
+                if (use & 1) {
+                    bas[o][0][j] = fmaf(cn, bx[j], bas[o][0][j]);
+                    bas[o][1][j] = fmaf(cn, by[j], bas[o][1][j]);
+                }
+                if (use & 2) {
+                    bas[o][2][j] = fmaf(cn, bxx[j], bas[o][2][j]);
+                    bas[o][3][j] = fmaf(cn, byy[j], bas[o][3][j]);
+                    bas[o][4][j] = fmaf(cn, bxy[j], bas[o][4][j]);
+                }
+            }
+        }
+    }
+    __syncthreads();
+}
+template <int RHO>
+__device__ __forceinline__ void sigma_pass_use(const float* simg, int IPP, float* srow, const DescribeConsts& C, int s,
+                                               float (&bas)[kCOwn][5][kCRun]) {
+    if (RHO > 0 && C.use[s] == 1) sigma_pass<RHO, RHO ? 1 : 3>(simg, IPP, srow, C, s, bas);
+    else if (RHO > 0 && C.use[s] == 2) sigma_pass<RHO, RHO ? 2 : 3>(simg, IPP, srow, C, s, bas);
+    else sigma_pass<RHO, 3>(simg, IPP, srow, C, s, bas);
+}
+
+// The same method for the parameters in use, z = 2 N channels.  What bounds
+// it is instruction issue, so everything is arranged for few instructions a
+// pixel: the maps are linear with compile-time pitches; a thread holds the
+// basis of its six map elements in registers while an order's channels are
+// steered (a multiply-add or two and a store a channel, no address
+// arithmetic); steered maps alternate between two buffers, the ones the first
+// order's basis came from, with one barrier a channel; and an order is emitted
+// before the next is steered, so four workgroups fit a CU (40 KB of LDS for
+// R = 9, 128 VGPRs for N <= 8).
+// 2048 x 2048, FP32 with integral inputs: 250 us with the basis read from LDS
+// by a loop over map elements (23 issue slots a channel and element), runs of
+// four rows and two or four row-pass phases a sigma; 195 us so (85.8 M wave
+// instructions, 74 % of the issue slots).
+// The arguments are read where the launch put them: as a by-value parameter
+// with this many readers the compiler would copy them to scratch memory.
+struct K1Args {
+    DescribeJob single;
+    const DescribeJob* jobs;
+    const int4* tiles;
+    const uint8_t* tmask;
+    DescribeConsts C;
+};
+template <int N>
+__global__ __launch_bounds__(kNT, N <= 8 ? 4 : 3) void describe_k1_kernel(const K1Args by_value) {
+    extern __shared__ float lds[];
+    const K1Args& A = *(const K1Args*)__builtin_amdgcn_kernarg_segment_ptr();
+    const DescribeConsts& C = A.C;
+    DescribeJob J;
+    int ty0, tx0;
+    if (!describe_tile(A.single, A.jobs, A.tiles, A.tmask, J, ty0, tx0)) return;
+    const int t = threadIdx.x, R = C.R, side = kB + 2 * R, IPP = side | 1;
+    float* srow = lds + side * IPP;
+    load_region(J, ty0 - 3 - R, tx0 - 3 - R, side, lds, IPP);
+    __syncthreads();
+
+    // Gx, Gy, Gxx, Gyy, Gxy * I summed over sigma, held by the threads of the
+    // column runs, then laid out as maps over the dead image region
+    {
+        float bas[kCOwn][5][kCRun];
+#pragma unroll
+        for (int o = 0; o < kCOwn; ++o)
+#pragma unroll
+            for (int m = 0; m < 5; ++m)
+#pragma unroll
+                for (int j = 0; j < kCRun; ++j) bas[o][m][j] = 0.f;
+        for (int s = 0; s < C.nsig; ++s) {
+#define PASS(RR) sigma_pass_use<RR>(lds, IPP, srow, C, s, bas)
+            SFOC_RADIUS_SWITCH(C.rad[s], PASS, PASS(0))
+#undef PASS
+        }
+#pragma unroll
+        for (int o = 0; o < kCOwn; ++o) {
+            const int e = t + o * kNT;
+            if (e < kCRuns * kB) {
+                float* d = lds + e / kB * kCRun * kCP + e % kB;
+#pragma unroll
+                for (int m = 0; m < 5; ++m)
+#pragma unroll
+                    for (int j = 0; j < kCRun; ++j) d[m * kCM + j * kCP] = bas[o][m][j];
+            }
+        }
+    }
+    __syncthreads();
+
+    RunOut O;
+    init_run(O, J, C, ty0, tx0);
+    const bool sums = J.integ1 != nullptr;
+    const int rect = C.rectify;
+    // the top-left element of the neighbourhood of the thread's output run
+    const int nb = (t / (kTS / kRun)) * kCP + (t % (kTS / kRun)) * kRun + 3 * kCP + 3;
+    float acc[N][kRun];
+    // Channels of one order: steer(c, k) is channel c at the thread's map
+    // element k.  Map elements past the 38 x 38 pixels hold values that no
+    // output reads.  A buffer is written again two channels later, when every
+    // thread has passed the barrier after it last read it.
+    auto channels = [&](auto steer, const float* w) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            float* buf = lds + (c & 1) * kCM;
+            if (rect == SFOC_RECTIFY_ABS) {
+#pragma unroll
+                for (int k = 0; k < kPix; ++k) buf[t + k * kNT] = fabsf(steer(c, k));
+            } else if (rect == SFOC_RECTIFY_RELU) {
+#pragma unroll
+                for (int k = 0; k < kPix; ++k) buf[t + k * kNT] = fmaxf(steer(c, k), 0.f);
+            } else {
+#pragma unroll
+                for (int k = 0; k < kPix; ++k) buf[t + k * kNT] = steer(c, k);
+            }
+            __syncthreads();
+            smooth_run_k1_123(lds, (c & 1) * kCM + nb, kCP, w[4], w[1], w[0], acc[c]);
+            // computed here, with one channel's reads in flight at a time
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) asm volatile("" : "+v"(acc[c][j]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    {
+        float b0[kPix], b1[kPix];
+#pragma unroll
+        for (int k = 0; k < kPix; ++k) {
+            b0[k] = lds[t + k * kNT];
+            b1[k] = lds[kCM + t + k * kNT];
+        }
+        __syncthreads();   // the maps become the channel buffers
+        channels([&](int c, int k) { return fmaf(C.c1[c], b0[k], C.s1[c] * b1[k]); }, C.w1);
+    }
+    emit_block<N>(acc, 0, N, 0, J.desc, sums, C, O);
+    {
+        float b2[kPix], b3[kPix], b4[kPix];
+#pragma unroll
+        for (int k = 0; k < kPix; ++k) {
+            b2[k] = lds[2 * kCM + t + k * kNT];
+            b3[k] = lds[3 * kCM + t + k * kNT];
+            b4[k] = lds[4 * kCM + t + k * kNT];
+        }
+        if (N & 1) __syncthreads();   // buffer 0 again, read by the last channel
+        channels([&](int c, int k) { return fmaf(C.sc2[c], b4[k], fmaf(C.cc[c], b2[k], C.ss[c] * b3[k])); }, C.w2);
+    }
+    emit_block<N>(acc, 0, N, N, J.desc, sums, C, O);
+    if (sums) {
+        // the column sums go where nobody reads any more (map 2)
+        emit_sums(J, O, ty0, tx0, reinterpret_cast<double*>(lds + 2 * kCM));
+    }
+}
 
 // ---- integral images (Eq. 14-16) ------------------------------------------
 // The inclusive 2-D prefix sum (Eq. 15) of a per-pixel map s, at a pixel
@@ -956,14 +1096,33 @@ __global__ __launch_bounds__(kScanNT) void integral_tiles(const IntegJob single,
 }
 
 // ---- launch -------------------------------------------------------------
-template <int Z, bool FAST, int VAR>
-static hipError_t launch_describe_zf(const DescribeJob& job, const DescribeJob* jobs, const int4* tiles, int ntiles,
-                                     const uint8_t* tmask, const DescribeConsts& c, hipStream_t st) {
-    constexpr int CG = describe_cg<Z, FAST, VAR>();
-    const DescribeGeom g = describe_geom(c, CG, VAR == 1);
-    dim3 grid = tiles ? dim3(ntiles) : dim3((job.W + kTS - 1) / kTS, (job.H + kTS - 1) / kTS);
+// K = 1 at rates 1, 2, 3 with both orders: compile-time geometry.
+static bool describe_k1(const DescribeConsts& c) {
+    return c.K == 1 && c.ndil == 3 && c.dil[0] == 1 && c.dil[1] == 2 && c.dil[2] == 3 && c.second &&
+           c.N * 2 == c.z;
+}
+
+int describe_configs(const DescribeConsts& c) { return describe_k1(c) && c.z <= 16 ? 2 : 1; }
+
+template <int Z>
+static hipError_t launch_describe_z(const DescribeJob& job, const DescribeJob* jobs, const int4* tiles, int ntiles,
+                                    const uint8_t* tmask, const DescribeConsts& c, hipStream_t st) {
+    const dim3 grid = tiles ? dim3(ntiles) : dim3((job.W + kTS - 1) / kTS, (job.H + kTS - 1) / kTS);
     if (grid.x == 0) return hipSuccess;
-    auto kern = describe_kernel<Z, CG, FAST, VAR>;
+    if constexpr (Z % 2 == 0)
+        if (describe_k1(c)) {
+            auto kern = describe_k1_kernel<Z / 2>;
+            const size_t bytes = describe_k1_lds(c.R);
+            hipError_t e = ensure_dynamic_lds((const void*)kern, (int)bytes);
+            if (e != hipSuccess) return e;
+            trace_begin(st, SFOC_K_DESCRIBE);
+            hipLaunchKernelGGL(kern, grid, dim3(kNT), bytes, st, K1Args{job, jobs, tiles, tmask, c});
+            trace_end(st, SFOC_K_DESCRIBE);
+            return hipGetLastError();
+        }
+    constexpr int CG = Z >= 4 ? 4 : Z;
+    const DescribeGeom g = describe_geom(c, CG);
+    auto kern = describe_kernel<Z, CG>;
     hipError_t e = ensure_dynamic_lds((const void*)kern, (int)g.bytes);
     if (e != hipSuccess) return e;
     trace_begin(st, SFOC_K_DESCRIBE);
@@ -972,57 +1131,40 @@ static hipError_t launch_describe_zf(const DescribeJob& job, const DescribeJob* 
     return hipGetLastError();
 }
 
-// The K = 1, rates 1-3 path with both orders: compile-time geometry.
-static bool describe_fast(const DescribeConsts& c) {
-    return c.K == 1 && c.ndil == 3 && c.dil[0] == 1 && c.dil[1] == 2 && c.dil[2] == 3 && c.second &&
-           c.N * 2 == c.z;
-}
-
-int describe_configs(const DescribeConsts& c) { return describe_fast(c) && c.z <= 16 && c.z % 2 == 0 ? 2 : 1; }
-
-template <int Z>
-static hipError_t launch_describe_z(const DescribeJob& job, const DescribeJob* jobs, const int4* tiles, int ntiles,
-                                    const uint8_t* tmask, const DescribeConsts& c, hipStream_t st, int var) {
-    if (!describe_fast(c)) return launch_describe_zf<Z, false, 0>(job, jobs, tiles, ntiles, tmask, c, st);
-    if constexpr (Z <= 16 && Z % 2 == 0)
-        if (var == 1) return launch_describe_zf<Z, true, 1>(job, jobs, tiles, ntiles, tmask, c, st);
-    return launch_describe_zf<Z, true, 0>(job, jobs, tiles, ntiles, tmask, c, st);
-}
-
 static hipError_t launch_describe_any(const DescribeJob& job, const DescribeJob* jobs, const int4* tiles, int ntiles,
-                                      const uint8_t* tmask, const DescribeConsts& c, hipStream_t st, int var) {
+                                      const uint8_t* tmask, const DescribeConsts& c, hipStream_t st) {
     switch (c.z) {
-        case 2: return launch_describe_z<2>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 3: return launch_describe_z<3>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 4: return launch_describe_z<4>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 6: return launch_describe_z<6>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 8: return launch_describe_z<8>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 12: return launch_describe_z<12>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 16: return launch_describe_z<16>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 24: return launch_describe_z<24>(job, jobs, tiles, ntiles, tmask, c, st, var);
-        case 32: return launch_describe_z<32>(job, jobs, tiles, ntiles, tmask, c, st, var);
+        case 2: return launch_describe_z<2>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 3: return launch_describe_z<3>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 4: return launch_describe_z<4>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 6: return launch_describe_z<6>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 8: return launch_describe_z<8>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 12: return launch_describe_z<12>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 16: return launch_describe_z<16>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 24: return launch_describe_z<24>(job, jobs, tiles, ntiles, tmask, c, st);
+        case 32: return launch_describe_z<32>(job, jobs, tiles, ntiles, tmask, c, st);
         default: return hipErrorInvalidValue;
     }
 }
 
 // Several images in one launch: jobs and tiles are device tables.
 hipError_t launch_describe_batched(const DescribeJob* jobs, const int4* tiles, int ntiles, const DescribeConsts& c,
-                                   hipStream_t st, int var) {
+                                   hipStream_t st) {
     DescribeJob none{};
-    return launch_describe_any(none, jobs, tiles, ntiles, nullptr, c, st, var);
+    return launch_describe_any(none, jobs, tiles, ntiles, nullptr, c, st);
 }
 
 hipError_t launch_describe(const float* img, int H, int W, int64_t ld, void* desc, double* i1, double* i2,
                            double* agg, const DescribeConsts& c, hipStream_t st, const uint8_t* tmask) {
     DescribeJob job{img, desc, i1, i2, agg, ld, H, W};
-    return launch_describe_any(job, nullptr, nullptr, 0, tmask, c, st, 0);
+    return launch_describe_any(job, nullptr, nullptr, 0, tmask, c, st);
 }
 
 hipError_t launch_describe_tiles(const float* img, int H, int W, int64_t ld, void* desc, const int4* tiles,
                                  int ntiles, const DescribeConsts& c, hipStream_t st) {
     if (ntiles == 0) return hipSuccess;
     DescribeJob job{img, desc, nullptr, nullptr, nullptr, ld, H, W};
-    return launch_describe_any(job, nullptr, tiles, ntiles, nullptr, c, st, 0);
+    return launch_describe_any(job, nullptr, tiles, ntiles, nullptr, c, st);
 }
 
 // ---- the pair call's describe table ---------------------------------------
@@ -1092,9 +1234,8 @@ hipError_t launch_describe_pair(const float* ref, int Hr, int Wr, int64_t ldr, v
                        Hs, Ws, Hr, Wr, jref, jsen, jobs, tiles, mask);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // configuration 1 (four workgroups per CU) where the parameters have it
     DescribeJob none{};
-    return launch_describe_any(none, jobs, tiles, (int)cnt, mask, c, st, 1);
+    return launch_describe_any(none, jobs, tiles, (int)cnt, mask, c, st);
 }
 
 hipError_t launch_integral(double* i1, double* i2, int H, int W, double* agg, hipStream_t st, uint8_t* tmask) {

@@ -130,12 +130,10 @@ hipError_t launch_cp_row_shift(sfoc_cp* cps, int n, int dy, hipStream_t st);
 void match_args_layout(MatchArgs& a, const MatchPlan& mp, void* ws);
 
 // ---- tables (device pointers) --------------------------------------------
-// tiles[k] = {job, tile row origin, tile column origin, 0}; var picks the
-// launch configuration (0, or 1 where describe_configs() is 2): the same
-// descriptors either way.
+// tiles[k] = {job, tile row origin, tile column origin, 0}.
 hipError_t launch_describe_batched(const DescribeJob* jobs, const int4* tiles, int ntiles, const DescribeConsts& c,
-                                   hipStream_t st, int var = 0);
-// Launch configurations of the describe kernel for these constants (1 or 2).
+                                   hipStream_t st);
+// Configuration numbers that a plan takes for these constants (1 or 2).
 int describe_configs(const DescribeConsts& c);
 // pre[k] = {job, kind, block, 0}: kind 0 a block of kScanNT rows of the
 // row sums, 1 a block of kScanNT columns of the column sums, 2 the tile
