@@ -252,7 +252,10 @@ int sfoc_fastncc_match(const void* desc_sen, int64_t Hs, int64_t Ws,
  * on `stream` is ordered after the call.  Arguments as above; the
  * descriptors, integral images, the describe table of both images' tiles,
  * the match's R_ST surfaces and the reference tile mask live inside ws (see
- * sfoc_register_workspace).  The CPs equal
+ * sfoc_register_workspace).  For few IPs (up to 512 at 64 x 64 windows, 96 to
+ * 128 at larger ones) the queried size includes up to 160 MB with which the
+ * channels are matched side by side; a call with a workspace short of only
+ * that takes the channels in turn, with the same result.  The CPs equal
  * those of sfoc_describe of both whole images followed by sfoc_fastncc_match
  * up to the float64 rounding of those box sums (bit for bit in every test).
  */

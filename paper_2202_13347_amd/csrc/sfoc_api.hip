@@ -61,12 +61,22 @@ static hipError_t side_stream(SideStream** out) {
     return hipSuccess;
 }
 
+// Scratch of the match's spread form, after what a call cannot do without: it
+// is taken where the caller's workspace has it.
+struct SpreadRegion {
+    size_t off, bytes;
+    size_t end() const { return off + bytes; }
+    void* in(void* ws, size_t ws_bytes) const { return bytes && ws_bytes >= end() ? (char*)ws + off : nullptr; }
+};
+
 struct RegisterLayout {
     size_t desc_ref, desc_sen, integ1, integ2, scan, jobs, tiles, rmask, split, match, total;
+    SpreadRegion spread;
 };
 
 static RegisterLayout register_layout(int64_t Hr, int64_t Wr, int64_t Hs, int64_t Ws, int32_t n, int32_t m,
-                                      int32_t r, int32_t z, size_t es, size_t match_ws) {
+                                      int32_t r, int32_t z, int32_t dtype, size_t match_ws) {
+    const size_t es = dtype_size(dtype);
     RegisterLayout L;
     size_t off = 0;
     L.desc_ref = off;
@@ -90,15 +100,18 @@ static RegisterLayout register_layout(int64_t Hr, int64_t Wr, int64_t Hs, int64_
     L.match = off;
     off = align_up(off + match_ws, 256);
     L.total = off;
+    L.spread = {off, match_spread_bytes(n, m, r, z, dtype)};
     return L;
 }
 
 // The pair call's launches for sizes already checked and a workspace laid
-// out by register_layout (consistency = false leaves out the median check).
+// out by register_layout (consistency = false leaves out the median check);
+// spread: match_spread_bytes for the call's n, or null.
 static hipError_t register_core(const float* ref, int64_t Hr, int64_t Wr, int64_t ldr, const float* sen, int64_t Hs,
                                 int64_t Ws, int64_t lds, const int32_t* ips, const int32_t* prior, int32_t n,
                                 int32_t m, int32_t r, const DescribeConsts& c, int32_t z, int32_t dtype, float* ncc,
-                                sfoc_cp* cps, const RegisterLayout& L, void* ws, hipStream_t st, bool consistency) {
+                                sfoc_cp* cps, const RegisterLayout& L, void* ws, void* spread, hipStream_t st,
+                                bool consistency) {
     char* base = (char*)ws;
     void* dref = base + L.desc_ref;
     void* dsen = base + L.desc_sen;
@@ -135,7 +148,7 @@ static hipError_t register_core(const float* ref, int64_t Hr, int64_t Wr, int64_
     if (e == hipSuccess) e = hipEventRecord(side->join, side->s);
     if (e == hipSuccess)
         e = launch_match_fft(dsen, Hs, Ws, dref, Hr, Wr, z, dtype, ips, prior, n, m, r, ncc, cps, base + L.match,
-                             split, st);
+                             split, spread, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, side->join, 0);
     if (e != hipSuccess) return e;
     return launch_match_finish(dsen, Hs, Ws, dref, Hr, Wr, i1, i2, z, dtype, ips, prior, n, m, r, ncc, cps,
@@ -199,17 +212,19 @@ static void band_bounds(int64_t Hr, int64_t Hs, int32_t m, int32_t r, int32_t ba
 struct StreamLayout {
     RegisterLayout band;   // one band's register workspace
     size_t ips, prior, total;
+    SpreadRegion spread;
 };
 
 static StreamLayout stream_layout(int64_t Hr, int64_t Wr, int64_t Hs, int64_t Ws, int32_t n, int32_t m, int32_t r,
-                                  int32_t band_rows, int32_t max_prior, int32_t z, size_t es, int halo) {
+                                  int32_t band_rows, int32_t max_prior, int32_t z, int32_t dtype, int halo) {
     StreamLayout S;
     int64_t hs = 0, hr = 0;
     band_bounds(Hr, Hs, m, r, band_rows, max_prior, halo, &hs, &hr);
-    S.band = register_layout(hr, Wr, hs, Ws, n, m, r, z, es, match_plan(n, m, r).ws_bytes);
+    S.band = register_layout(hr, Wr, hs, Ws, n, m, r, z, dtype, match_plan(n, m, r).ws_bytes);
     S.ips = S.band.total;
     S.prior = align_up(S.ips + (size_t)n * 2 * sizeof(int32_t), 256);
     S.total = align_up(S.prior + (size_t)n * 2 * sizeof(int32_t), 256);
+    S.spread = {S.total, match_spread_bytes(n, m, r, z, dtype)};   // (a band has n IPs at most)
     return S;
 }
 
@@ -338,7 +353,7 @@ int sfoc_register_workspace(int64_t Hr, int64_t Wr, int64_t Hs, int64_t Ws, int3
     if (rc) return rc;
     rc = check_match_shape(n, m, r);
     if (rc) return rc;
-    *bytes = register_layout(Hr, Wr, Hs, Ws, n, m, r, z, dtype_size(p->desc_dtype), match_plan(n, m, r).ws_bytes).total;
+    *bytes = register_layout(Hr, Wr, Hs, Ws, n, m, r, z, p->desc_dtype, match_plan(n, m, r).ws_bytes).spread.end();
     return SFOC_OK;
 }
 
@@ -360,12 +375,13 @@ int sfoc_register_cps(const float* ref, int64_t Hr, int64_t Wr, int64_t ldr, con
     const int64_t ntiles = (int64_t)n * template_tile_slots(m, kDescribeTile);
     if (ntiles > INT32_MAX) return SFOC_E_UNSUPPORTED;
     const RegisterLayout L =
-        register_layout(Hr, Wr, Hs, Ws, n, m, r, z, dtype_size(p->desc_dtype), match_plan(n, m, r).ws_bytes);
+        register_layout(Hr, Wr, Hs, Ws, n, m, r, z, p->desc_dtype, match_plan(n, m, r).ws_bytes);
     if (!ws || ws_bytes < L.total) return SFOC_E_WORKSPACE;
     DescribeConsts c;
     build_describe_consts(p, &c);
     return hip_status(register_core(ref, Hr, Wr, ldr, sen, Hs, Ws, lds, ips, prior, n, m, r, c, z, p->desc_dtype, ncc,
-                                    cps, L, ws, (hipStream_t)stream, true));
+                                    cps, L, ws, L.spread.in(ws, ws_bytes),
+                                    (hipStream_t)stream, true));
 }
 
 int sfoc_register_streamed_workspace(int64_t Hr, int64_t Wr, int64_t Hs, int64_t Ws, int32_t n, int32_t m,
@@ -379,8 +395,8 @@ int sfoc_register_streamed_workspace(int64_t Hr, int64_t Wr, int64_t Hs, int64_t
     if (rc) return rc;
     DescribeConsts c;
     build_describe_consts(p, &c);
-    *bytes = stream_layout(Hr, Wr, Hs, Ws, n, m, r, band_rows, max_prior, z, dtype_size(p->desc_dtype), c.Q + c.R)
-                 .total;
+    *bytes = stream_layout(Hr, Wr, Hs, Ws, n, m, r, band_rows, max_prior, z, p->desc_dtype, c.Q + c.R)
+                 .spread.end();
     return SFOC_OK;
 }
 
@@ -405,7 +421,7 @@ int sfoc_register_cps_streamed(const float* ref, int64_t Hr, int64_t Wr, int64_t
     build_describe_consts(p, &c);
     const int halo = c.Q + c.R;
     const StreamLayout S =
-        stream_layout(Hr, Wr, Hs, Ws, n, m, r, band_rows, max_prior, z, dtype_size(p->desc_dtype), halo);
+        stream_layout(Hr, Wr, Hs, Ws, n, m, r, band_rows, max_prior, z, p->desc_dtype, halo);
     if (!ws || ws_bytes < S.total) return SFOC_E_WORKSPACE;
     if (n == 0) return SFOC_OK;
     hipStream_t st = (hipStream_t)stream;
@@ -448,7 +464,8 @@ int sfoc_register_cps_streamed(const float* ref, int64_t Hr, int64_t Wr, int64_t
         const int nb = b.i1 - b.i0;
         e = register_core(ref + b.r0 * ldr, b.r1 - b.r0, Wr, ldr, sen + b.s0 * lds, b.s1 - b.s0, Ws, lds,
                           d_ips + 2 * b.i0, d_prior + 2 * b.i0, nb, m, r, c, z, p->desc_dtype,
-                          ncc ? ncc + b.i0 * V * V : nullptr, cps + b.i0, S.band, ws, st, false);
+                          ncc ? ncc + b.i0 * V * V : nullptr, cps + b.i0, S.band, ws,
+                          S.spread.in(ws, ws_bytes), st, false);
         if (e == hipSuccess) e = launch_cp_row_shift(cps + b.i0, nb, (int)b.s0, st);
     }
     if (e == hipSuccess) e = launch_consistency(cps, prior, n, st);

@@ -57,6 +57,11 @@ struct MatchArgs {
     // and the peaks from them and the integral images.
     float* rst = nullptr;
     double* tsum = nullptr;
+    // Spread form of the split form (spec set): per (IP, channel) the spectrum
+    // product, the factors of its two packed self bins, and the template sums.
+    float2* spec = nullptr;
+    float2* spec_self = nullptr;
+    double* spec_sum = nullptr;
 };
 
 // SFOC_OK for hipSuccess, else SFOC_E_HIP (the HIP error is kept for
@@ -107,16 +112,20 @@ hipError_t launch_match(const void* desc_sen, int64_t Hs, int64_t Ws, const void
                         hipStream_t st, bool consistency = true);
 // The same match in two launches, so that the integral images need not
 // exist before the second: launch_match_fft runs the transforms and leaves
-// R_ST and the template sums in `split` (match_split_bytes(n, r) bytes);
+// R_ST and the template sums in `split` (match_split_bytes bytes), with
+// `spread` (match_spread_bytes, or null) in the spread form where it is taken;
 // launch_match_finish assembles the NCC surfaces (ncc, if set) and the
 // peaks into cps from them and the integral images, then (consistency) the
 // median check.  Only where match_split_ok: an FFT side without offset
 // blocks.  ws is launch_match's workspace.
 bool match_split_ok(int n, int m, int r, int dtype);
 size_t match_split_bytes(int n, int r);
+// Scratch of the transforms' spread form (a workgroup per IP and channel), 0
+// where it is not taken; taken for n IPs, it is for fewer.
+size_t match_spread_bytes(int n, int m, int r, int z, int dtype);
 hipError_t launch_match_fft(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
                             int64_t Wr, int z, int dtype, const int32_t* ips, const int32_t* prior, int n, int m,
-                            int r, float* ncc, sfoc_cp* cps, void* ws, void* split, hipStream_t st);
+                            int r, float* ncc, sfoc_cp* cps, void* ws, void* split, void* spread, hipStream_t st);
 hipError_t launch_match_finish(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
                                int64_t Wr, const double* i1, const double* i2, int z, int dtype, const int32_t* ips,
                                const int32_t* prior, int n, int m, int r, float* ncc, sfoc_cp* cps, void* ws,

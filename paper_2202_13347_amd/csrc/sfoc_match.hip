@@ -910,91 +910,39 @@ SFOC_DEV void ncc_peak(const MatchArgs& A, int i, int slot, int u0, int v0, int 
     }
 }
 
-// One work item: interest point i, offset block bq (record slot `slot`).
-// With M <= L there is one block and this workgroup finishes the CP;
-// otherwise each block covers offsets [u0, u0 + Vu) x [v0, v0 + Vv) with a
-// search window of (m + Vu - 1) x (m + Vv - 1) <= L x L, writes its part of
-// the surface and its best score, and peak_kernel combines the blocks.
-// Every thread of the workgroup calls it with the same item; it returns
-// with the workgroup synchronised.
-template <int L, int DT, bool SPLIT = false>
-SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const float2* tw, float2* buf, double* red) {
+// The spectra of channel h: the search window's (rows sy.., columns sx.., Mu x
+// Mv) into xsp, then the template's into yt; the template's sums join s1, s2.
+// The search window comes first (only the running sum is live during its
+// larger row stage), its spectrum kept in registers.
+template <int L, int DT>
+SFOC_DEV void channel_spectra(const MatchArgs& A, int h, int64_t sy, int64_t sx, int Mu, int Mv, int64_t ty,
+                              int64_t tx, const float2* tw, float2* buf, double& s1, double& s2,
+                              float2 (&xsp)[MatchCfg<L>::BINS], float2 (&u)[MatchCfg<L>::NB],
+                              float2 (&v)[MatchCfg<L>::NB]) {
     using C = MatchCfg<L>;
-    const int nblk = A.nbu * A.nbv;
-    const int bu = bq / A.nbv, bv = bq - bu * A.nbv;
-    const int t = threadIdx.x;
-    const int m = A.m, r = A.r, M = m + 2 * r, V = 2 * r + 1;
-    const int u0 = bu * A.Vb, v0 = bv * A.Vb;
-    const int Vu = min(A.Vb, V - u0), Vv = min(A.Vb, V - v0);
-    const int Mu = m + Vu - 1, Mv = m + Vv - 1;
-    const int py = A.ips[2 * i], px = A.ips[2 * i + 1];
-    const int pry = A.prior ? A.prior[2 * i] : 0, prx = A.prior ? A.prior[2 * i + 1] : 0;
-    const int64_t ty = (int64_t)py - m / 2, tx = (int64_t)px - m / 2;
-    const int64_t sy = ty - r + pry, sx = tx - r + prx;
-    float* nout = A.ncc ? A.ncc + (int64_t)i * V * V : (nblk > 1 ? A.surf + (int64_t)i * V * V : nullptr);
-    sfoc_cp out;
-    out.sen_row = py;
-    out.sen_col = px;
-    out.dy = out.dx = 0;
-    out.sub_dy = out.sub_dx = 0.f;
-    out.score = 0.f;
-    out.flags = 0;
-    if (!in_image(ty, tx, m, m, A.Hs, A.Ws) || !in_image(sy, sx, M, M, A.Hr, A.Wr)) {
-        if (t == 0) {
-            if (nblk == 1) {
-                out.flags = SFOC_CP_OOB;
-                A.cps[i] = out;
-            } else {
-                A.blk[slot] = make_float4(0.f, __int_as_float(0), __int_as_float(kBlkOOB), 0.f);
-            }
-        }
-        if (nout)
-            for (int e = t; e < Vu * Vv; e += C::NT) {
-                const int u = e / Vv, v = e - u * Vv;
-                nout[(u0 + u) * V + v0 + v] = 0.f;
-            }
-        return;
-    }
-
-    float2 acc[C::BINS];   // sum over channels of F(S_h) conj(F(T_h))
-#pragma unroll
-    for (int q = 0; q < C::BINS; ++q) acc[q] = make_float2(0.f, 0.f);
-    double s1 = 0.0, s2 = 0.0;
     const int64_t plane_s = A.Hs * A.Ws, plane_r = A.Hr * A.Wr;
-    // Per channel: the search window first (only the running sum is live
-    // during its larger row stage), its spectrum kept in registers, then the
-    // template, whose column stage accumulates F(S_h) conj(F(T_h)).
-    float2 xsp[C::BINS];   // search-window spectrum of the current channel
-    for (int h = 0; h < A.z; ++h) {
-        float2 u[C::NB], v[C::NB];
-        forward_2d<L, DT, false, false>(elem_ptr<DT>(A.desc_ref, h * plane_r), (int)A.Wr, (int)(sy + u0),
-                                        (int)(sx + v0), Mu, Mv, buf, tw, s1, s2, u, v);
-        const int tl = tid_local(), cc = tl / C::HA, j = tl - cc * C::HA;
-        if (cc == 0) separate_packed<C::NB>(u, v, j);
+    const int m = A.m;
+    forward_2d<L, DT, false, false>(elem_ptr<DT>(A.desc_ref, h * plane_r), (int)A.Wr, (int)sy, (int)sx, Mu, Mv, buf,
+                                    tw, s1, s2, u, v);
+    const int tl = tid_local(), cc = tl / C::HA, j = tl - cc * C::HA;
+    if (cc == 0) separate_packed<C::NB>(u, v, j);
 #pragma unroll
-        for (int q = 0; q < C::NB; ++q) {
-            xsp[q] = u[q];
-            xsp[C::NB + q] = v[q];
-        }
-        __syncthreads();
-        forward_2d<L, DT, true, true>(elem_ptr<DT>(A.desc_sen, h * plane_s), (int)A.Ws, (int)ty, (int)tx, m, m, buf,
-                                      tw, s1, s2, u, v);
-        if (cc == 0) separate_packed<C::NB>(u, v, j);
-        const bool self = tl == 0;   // cc = j = 0: slots 0 and NB/2 hold (F_dc, F_nyq) as reals
-#pragma unroll
-        for (int q = 0; q < C::BINS; ++q) {
-            const float2 xs = xsp[q];
-            const float2 yt = q < C::NB ? u[q] : v[q - C::NB];
-            const float2 a = acc[q];
-            acc[q] = cadd(a, cmulc(xs, yt));
-            if (q == 0 || q == C::NB / 2)
-                acc[q] = pick(self, make_float2(fmaf(xs.x, yt.x, a.x), fmaf(xs.y, yt.y, a.y)), acc[q]);
-        }
-        __syncthreads();
+    for (int q = 0; q < C::NB; ++q) {
+        xsp[q] = u[q];
+        xsp[C::NB + q] = v[q];
     }
+    __syncthreads();
+    forward_2d<L, DT, true, true>(elem_ptr<DT>(A.desc_sen, h * plane_s), (int)A.Ws, (int)ty, (int)tx, m, m, buf, tw,
+                                  s1, s2, u, v);
+    if (cc == 0) separate_packed<C::NB>(u, v, j);
+}
 
-    block_sum2<C::NT>(s1, s2, red);
-
+// R_ST of rows u < Vu from the summed spectrum: real rows in buf, row pair
+// (u, u + 1) at C::row(u).
+template <int L>
+SFOC_DEV void inverse_2d(const float2 (&acc)[MatchCfg<L>::BINS], int Vu, const float2* tw, float2* buf) {
+    using C = MatchCfg<L>;
+    const int t = threadIdx.x;
     // inverse, columns first: spectrum bins back to LDS (natural order), then
     // column transforms k1 -> u.
     {
@@ -1112,6 +1060,81 @@ SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const floa
         }
         __syncthreads();
     }
+}
+
+// The record of an IP whose template or search window leaves its image.
+SFOC_DEV sfoc_cp oob_record(int py, int px) {
+    sfoc_cp out;
+    out.sen_row = py;
+    out.sen_col = px;
+    out.dy = out.dx = 0;
+    out.sub_dy = out.sub_dx = 0.f;
+    out.score = 0.f;
+    out.flags = SFOC_CP_OOB;
+    return out;
+}
+
+// One work item: interest point i, offset block bq (record slot `slot`).
+// With M <= L there is one block and this workgroup finishes the CP;
+// otherwise each block covers offsets [u0, u0 + Vu) x [v0, v0 + Vv) with a
+// search window of (m + Vu - 1) x (m + Vv - 1) <= L x L, writes its part of
+// the surface and its best score, and peak_kernel combines the blocks.
+// Every thread of the workgroup calls it with the same item; it returns
+// with the workgroup synchronised.
+template <int L, int DT, bool SPLIT = false>
+SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const float2* tw, float2* buf, double* red) {
+    using C = MatchCfg<L>;
+    const int nblk = A.nbu * A.nbv;
+    const int bu = bq / A.nbv, bv = bq - bu * A.nbv;
+    const int t = threadIdx.x;
+    const int m = A.m, r = A.r, M = m + 2 * r, V = 2 * r + 1;
+    const int u0 = bu * A.Vb, v0 = bv * A.Vb;
+    const int Vu = min(A.Vb, V - u0), Vv = min(A.Vb, V - v0);
+    const int Mu = m + Vu - 1, Mv = m + Vv - 1;
+    const int py = A.ips[2 * i], px = A.ips[2 * i + 1];
+    const int pry = A.prior ? A.prior[2 * i] : 0, prx = A.prior ? A.prior[2 * i + 1] : 0;
+    const int64_t ty = (int64_t)py - m / 2, tx = (int64_t)px - m / 2;
+    const int64_t sy = ty - r + pry, sx = tx - r + prx;
+    float* nout = A.ncc ? A.ncc + (int64_t)i * V * V : (nblk > 1 ? A.surf + (int64_t)i * V * V : nullptr);
+    if (!in_image(ty, tx, m, m, A.Hs, A.Ws) || !in_image(sy, sx, M, M, A.Hr, A.Wr)) {
+        if (t == 0) {
+            if (nblk == 1) {
+                A.cps[i] = oob_record(py, px);
+            } else {
+                A.blk[slot] = make_float4(0.f, __int_as_float(0), __int_as_float(kBlkOOB), 0.f);
+            }
+        }
+        if (nout)
+            for (int e = t; e < Vu * Vv; e += C::NT) {
+                const int u = e / Vv, v = e - u * Vv;
+                nout[(u0 + u) * V + v0 + v] = 0.f;
+            }
+        return;
+    }
+
+    float2 acc[C::BINS];   // sum over channels of F(S_h) conj(F(T_h))
+#pragma unroll
+    for (int q = 0; q < C::BINS; ++q) acc[q] = make_float2(0.f, 0.f);
+    double s1 = 0.0, s2 = 0.0;
+    float2 xsp[C::BINS];   // search-window spectrum of the current channel
+    for (int h = 0; h < A.z; ++h) {
+        float2 u[C::NB], v[C::NB];
+        channel_spectra<L, DT>(A, h, sy + u0, sx + v0, Mu, Mv, ty, tx, tw, buf, s1, s2, xsp, u, v);
+        const bool self = tid_local() == 0;   // cc = j = 0: slots 0 and NB/2 hold (F_dc, F_nyq) as reals
+#pragma unroll
+        for (int q = 0; q < C::BINS; ++q) {
+            const float2 xs = xsp[q];
+            const float2 yt = q < C::NB ? u[q] : v[q - C::NB];
+            const float2 a = acc[q];
+            acc[q] = cadd(a, cmulc(xs, yt));
+            if (q == 0 || q == C::NB / 2)
+                acc[q] = pick(self, make_float2(fmaf(xs.x, yt.x, a.x), fmaf(xs.y, yt.y, a.y)), acc[q]);
+        }
+        __syncthreads();
+    }
+
+    block_sum2<C::NT>(s1, s2, red);
+    inverse_2d<L>(acc, Vu, tw, buf);
 
     if constexpr (SPLIT) {   // split form: R_ST and the template sums for ncc_finish_kernel
         float* __restrict__ o = A.rst + (int64_t)i * V * V;
@@ -1129,6 +1152,108 @@ SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const floa
             const float* rr = reinterpret_cast<const float*>(buf + C::row((u >> 1) * 2));
             return rr[(u & 1) * L + v];
         });
+    }
+}
+
+// Few interest points leave most CUs idle while a workgroup takes a point's
+// channels one after the other.  Spread form: a workgroup per (point, channel)
+// leaves the spectrum product, and a second launch sums the products in
+// channel order, as the fused form does, and transforms back.  The products of
+// the two packed self bins are fused into that sum, so their factors are left
+// instead.
+template <int L>
+struct Spread {
+    using C = MatchCfg<L>;
+    static constexpr size_t bins = (size_t)C::BINS * C::NT;   // complex values of a product
+    static constexpr size_t item_bytes = bins * sizeof(float2) + 4 * sizeof(float2) + 2 * sizeof(double);
+};
+template <int L, int DT>
+__global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void match_spectra_kernel(const MatchArgs A) {
+    using C = MatchCfg<L>;
+    extern __shared__ float4 lds_raw[];
+    float2* tw = reinterpret_cast<float2*>(lds_raw);
+    float2* buf = tw + L;
+    double* red = reinterpret_cast<double*>(buf + C::buf_elems);
+    // each XCD takes a contiguous run of points (see match_kernel)
+    const int items = (int)gridDim.x, q8 = items / 8 * 8, id = (int)blockIdx.x;
+    const int k = id < q8 ? (id % 8) * (q8 / 8) + id / 8 : id;
+    const int i = k / A.z, h = k - i * A.z, m = A.m, r = A.r, M = m + 2 * r, t = threadIdx.x;
+    const int64_t ty = (int64_t)A.ips[2 * i] - m / 2, tx = (int64_t)A.ips[2 * i + 1] - m / 2;
+    const int64_t sy = ty - r + (A.prior ? A.prior[2 * i] : 0), sx = tx - r + (A.prior ? A.prior[2 * i + 1] : 0);
+    if (!in_image(ty, tx, m, m, A.Hs, A.Ws) || !in_image(sy, sx, M, M, A.Hr, A.Wr)) return;
+    init_twiddles<L>(tw);
+    __syncthreads();
+    double s1 = 0.0, s2 = 0.0;
+    float2 xsp[C::BINS], u[C::NB], v[C::NB];
+    channel_spectra<L, DT>(A, h, sy, sx, M, M, ty, tx, tw, buf, s1, s2, xsp, u, v);
+    float2* __restrict__ o = A.spec + (size_t)k * Spread<L>::bins + t;
+    float2* __restrict__ f = A.spec_self + (size_t)k * 4;
+#pragma unroll
+    for (int q = 0; q < C::BINS; ++q) {
+        const float2 yt = q < C::NB ? u[q] : v[q - C::NB];
+        o[q * C::NT] = cmulc(xsp[q], yt);
+        if ((q == 0 || q == C::NB / 2) && t == 0) {
+            f[q ? 2 : 0] = xsp[q];
+            f[q ? 3 : 1] = yt;
+        }
+    }
+    block_sum2<C::NT>(s1, s2, red);
+    if (t == 0) {
+        A.spec_sum[2 * k] = red[64];
+        A.spec_sum[2 * k + 1] = red[65];
+    }
+}
+
+// The second launch: a workgroup per point.
+template <int L>
+__global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void match_combine_kernel(const MatchArgs A) {
+    using C = MatchCfg<L>;
+    extern __shared__ float4 lds_raw[];
+    float2* tw = reinterpret_cast<float2*>(lds_raw);
+    float2* buf = tw + L;
+    const int i = (int)blockIdx.x, m = A.m, r = A.r, M = m + 2 * r, V = 2 * r + 1, t = threadIdx.x;
+    const int py = A.ips[2 * i], px = A.ips[2 * i + 1];
+    const int64_t ty = (int64_t)py - m / 2, tx = (int64_t)px - m / 2;
+    const int64_t sy = ty - r + (A.prior ? A.prior[2 * i] : 0), sx = tx - r + (A.prior ? A.prior[2 * i + 1] : 0);
+    if (!in_image(ty, tx, m, m, A.Hs, A.Ws) || !in_image(sy, sx, M, M, A.Hr, A.Wr)) {
+        if (t == 0) A.cps[i] = oob_record(py, px);
+        if (A.ncc)
+            for (int e = t; e < V * V; e += C::NT) A.ncc[(int64_t)i * V * V + e] = 0.f;
+        return;
+    }
+    init_twiddles<L>(tw);
+    float2 acc[C::BINS];
+#pragma unroll
+    for (int q = 0; q < C::BINS; ++q) acc[q] = make_float2(0.f, 0.f);
+    const float2* __restrict__ o = A.spec + (size_t)i * A.z * Spread<L>::bins + t;
+    const float2* __restrict__ f = A.spec_self + (size_t)i * A.z * 4;
+#pragma unroll 2
+    for (int h = 0; h < A.z; ++h) {
+        float2 p[C::BINS];
+#pragma unroll
+        for (int q = 0; q < C::BINS; ++q) p[q] = o[h * Spread<L>::bins + q * C::NT];
+#pragma unroll
+        for (int q = 0; q < C::BINS; ++q) {
+            const float2 a = acc[q];
+            acc[q] = cadd(a, p[q]);
+            if (q == 0 || q == C::NB / 2) {
+                const float2 xs = f[4 * h + (q ? 2 : 0)], yt = f[4 * h + (q ? 3 : 1)];
+                acc[q] = pick(t == 0, make_float2(fmaf(xs.x, yt.x, a.x), fmaf(xs.y, yt.y, a.y)), acc[q]);
+            }
+        }
+    }
+    __syncthreads();
+    inverse_2d<L>(acc, V, tw, buf);
+    float* __restrict__ R = A.rst + (int64_t)i * V * V;
+    for (int e = t; e < V * V; e += C::NT) {
+        const int u = e / V, v = e - u * V;
+        const float* rr = reinterpret_cast<const float*>(buf + C::row((u >> 1) * 2));
+        R[e] = rr[(u & 1) * L + v];
+    }
+    if (t < 2) {
+        double s = 0.0;
+        for (int h = 0; h < A.z; ++h) s += A.spec_sum[2 * ((size_t)i * A.z + h) + t];
+        A.tsum[2 * i + t] = s;
     }
 }
 
@@ -1851,6 +1976,34 @@ static size_t split_rst_bytes(int n, int r) {
 
 size_t match_split_bytes(int n, int r) { return split_rst_bytes(n, r) + (size_t)n * 2 * sizeof(double); }
 
+// Where the spread form is taken.  It costs a second launch and a pass of the
+// products through memory (4 L^2 bytes an IP and channel), and pays while the
+// fused form's workgroups, one an IP, leave CUs idle.  Times of a pair call of
+// 700 x 700 pixels, z = 16 (us, fused and spread):
+//   L =  64:  n = 16  191   99;  256  210  144;  512  222  191;  640  261  230
+//   L = 128:  n = 16  228  130;   64  230  158;  128  243  204;  192  265  282
+//   L = 160:  n = 16  367  171;   64  365  236;   96  371  280;  128  372  350
+//   L = 192:  n = 16  418  187;   64  439  287;   96  451  394;  128  459  459
+// and at n = 16, L = 64: z = 4  106  86;  z = 2  84  92.  The products are held
+// to 160 MB (a scene's descriptors at 2048 x 2048 are 540).
+constexpr size_t kSpreadBytes = 160000000;
+constexpr int kSpreadMinZ = 4;
+static size_t spread_item_bytes(int L) {
+    return L == 64 ? Spread<64>::item_bytes : L == 128 ? Spread<128>::item_bytes
+                   : L == 160 ? Spread<160>::item_bytes : Spread<192>::item_bytes;
+}
+static int spread_most(int L, int z) {   // IPs
+    const int cap = L == 64 ? 512 : L == 128 ? 128 : 96;
+    const size_t fit = kSpreadBytes / (spread_item_bytes(L) * (size_t)z);
+    return z < kSpreadMinZ ? 0 : fit < (size_t)cap ? (int)fit : cap;
+}
+
+size_t match_spread_bytes(int n, int m, int r, int z, int dtype) {
+    if (!match_split_ok(n, m, r, dtype)) return 0;
+    const int L = match_plan_dt(n, m, r, dtype).L;
+    return n <= spread_most(L, z) ? (size_t)n * z * spread_item_bytes(L) : 0;
+}
+
 static MatchArgs split_args(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
                             int64_t Wr, const double* i1, const double* i2, int z, int dtype, const int32_t* ips,
                             const int32_t* prior, int n, int m, int r, float* ncc, sfoc_cp* cps, void* ws,
@@ -1880,19 +2033,54 @@ static MatchArgs split_args(const void* desc_sen, int64_t Hs, int64_t Ws, const 
     return a;
 }
 
+template <int L, int DT>
+static hipError_t launch_spectra(const MatchArgs& a, hipStream_t st) {
+    using C = MatchCfg<L>;
+    auto kern = match_spectra_kernel<L, DT>;
+    hipError_t e = ensure_dynamic_lds((const void*)kern, (int)C::lds_bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.n * a.z), dim3(C::NT), C::lds_bytes, st, a);
+    return hipGetLastError();
+}
+template <int L>
+static hipError_t launch_spread(MatchArgs a, void* scratch, hipStream_t st) {
+    using C = MatchCfg<L>;
+    const size_t items = (size_t)a.n * a.z;
+    a.spec = (float2*)scratch;
+    a.spec_self = a.spec + items * Spread<L>::bins;
+    a.spec_sum = (double*)(a.spec_self + items * 4);
+    auto kern = match_combine_kernel<L>;
+    hipError_t e = ensure_dynamic_lds((const void*)kern, (int)C::lds_bytes);
+    if (e != hipSuccess) return e;
+    trace_begin(st, SFOC_K_MATCH);
+    e = a.dtype == 0 ? launch_spectra<L, 0>(a, st) : a.dtype == 1 ? launch_spectra<L, 1>(a, st) : launch_spectra<L, 2>(a, st);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(kern, dim3(a.n), dim3(C::NT), C::lds_bytes, st, a);
+        e = hipGetLastError();
+    }
+    trace_end(st, SFOC_K_MATCH);
+    return e;
+}
+// The transforms of the split form; spread: match_spread_bytes of scratch, or
+// null for the fused form.
+static hipError_t launch_split(const MatchArgs& a, int L, void* spread, hipStream_t st) {
+    switch (L) {
+        case 64: return spread ? launch_spread<64>(a, spread, st) : launch_match_side<64, true>(a, a.dtype, st);
+        case 128: return spread ? launch_spread<128>(a, spread, st) : launch_match_side<128, true>(a, a.dtype, st);
+        case 160: return spread ? launch_spread<160>(a, spread, st) : launch_match_side<160, true>(a, a.dtype, st);
+        case 192: return spread ? launch_spread<192>(a, spread, st) : launch_match_side<192, true>(a, a.dtype, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_match_fft(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
                             int64_t Wr, int z, int dtype, const int32_t* ips, const int32_t* prior, int n, int m,
-                            int r, float* ncc, sfoc_cp* cps, void* ws, void* split, hipStream_t st) {
+                            int r, float* ncc, sfoc_cp* cps, void* ws, void* split, void* spread, hipStream_t st) {
     if (!match_split_ok(n, m, r, dtype)) return hipErrorInvalidValue;
     const MatchArgs a = split_args(desc_sen, Hs, Ws, desc_ref, Hr, Wr, nullptr, nullptr, z, dtype, ips, prior, n, m,
                                    r, ncc, cps, ws, split);
-    switch (match_plan_dt(n, m, r, dtype).L) {
-        case 64: return launch_match_side<64, true>(a, dtype, st);
-        case 128: return launch_match_side<128, true>(a, dtype, st);
-        case 160: return launch_match_side<160, true>(a, dtype, st);
-        case 192: return launch_match_side<192, true>(a, dtype, st);
-        default: return hipErrorInvalidValue;
-    }
+    return launch_split(a, match_plan_dt(n, m, r, dtype).L, match_spread_bytes(n, m, r, z, dtype) ? spread : nullptr,
+                        st);
 }
 
 hipError_t launch_match_finish(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
