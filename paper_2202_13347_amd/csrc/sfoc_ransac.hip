@@ -37,7 +37,7 @@ namespace ransac {
 constexpr uint32_t kBad = SFOC_CP_OOB | SFOC_CP_FLAT_T | SFOC_CP_FLAT_S | SFOC_CP_EDGE_PEAK | SFOC_CP_NONFINITE;
 constexpr double kCollinearEps = 1e-9;   // |cross| in normalised units
 constexpr double kSingular = 1e-12;      // relative pivot of a refit system
-constexpr int kPrepNT = 1024, kHypNT = 256, kTile = 1024, kFinNT = 256;
+constexpr int kPrepNT = 1024, kHypNT = 256, kTile = 1024, kFinNT = 512;
 constexpr int kScoreBlocks = 1024, kMinChunk = 32;   // target grid of the score launch
 constexpr int kMaxN = 1 << 22, kMaxHyp = 1 << 20, kMaxRefine = 16;
 
@@ -320,43 +320,82 @@ SFOC_DEV bool cholesky_solve(double (&A)[N][N], double (&b)[NR][N]) {
     return ok;
 }
 
-constexpr int kSumsAff = 12, kSumsProj = 44;
+constexpr int kSumsAff = 12, kSumsProj = 29;
 
-// Normal-equation terms of one inlier: affine: the six distinct entries of
-// sum [x y 1]^T [x y 1], then sum X [x y 1] and sum Y [x y 1]; projective:
-// the 36 distinct entries of A^T A and the 8 of A^T b for the two rows of
-// the h22 = 1 system (u = (h0 x + h1 y + h2) - x u h6 - y u h7, same for v).
+// Normal-equation terms of one inlier.  Affine: the six distinct entries of
+// sum [x y 1]^T [x y 1], then sum X [x y 1] and sum Y [x y 1].  Projective, for
+// the two rows [v 0 -X x -X y] and [0 v -Y x -Y y], v = [x y 1], of the h22 = 1
+// system with right-hand sides X and Y: the same six entries (of both diagonal
+// blocks; the block between them is zero), the columns of h6 and h7 against
+// v (from X, then from Y) and each other, then A^T b.
 template <bool PROJ>
 SFOC_DEV void terms(double4 c, double* s) {
     const double x = c.x, y = c.y, X = c.z, Y = c.w;
-    if (!PROJ) {
-        const double v[3] = {x, y, 1.0};
-        int o = 0;
+    const double v[3] = {x, y, 1.0};
+    int o = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = i; j < 3; ++j) s[o++] += v[i] * v[j];
+    if (PROJ) {
+        const double p[2] = {-x * X, -y * X}, q[2] = {-x * Y, -y * Y};
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = i; j < 3; ++j) s[o++] += v[i] * v[j];
+            for (int j = 0; j < 2; ++j) {
+                s[6 + 2 * i + j] += v[i] * p[j];
+                s[12 + 2 * i + j] += v[i] * q[j];
+            }
+        s[18] += p[0] * p[0] + q[0] * q[0];
+        s[19] += p[0] * p[1] + q[0] * q[1];
+        s[20] += p[1] * p[1] + q[1] * q[1];
+        o = 21;
+    }
 #pragma unroll
-        for (int i = 0; i < 3; ++i) s[6 + i] += X * v[i];
+    for (int i = 0; i < 3; ++i) s[o + i] += X * v[i];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) s[9 + i] += Y * v[i];
-    } else {
-        const double r1[8] = {x, y, 1.0, 0.0, 0.0, 0.0, -x * X, -y * X};
-        const double r2[8] = {0.0, 0.0, 0.0, x, y, 1.0, -x * Y, -y * Y};
-        int o = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int j = i; j < 8; ++j) s[o++] += r1[i] * r1[j] + r2[i] * r2[j];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s[36 + i] += r1[i] * X + r2[i] * Y;
+    for (int i = 0; i < 3; ++i) s[o + 3 + i] += Y * v[i];
+    if (PROJ) {
+        s[27] += (-x * X) * X + (-x * Y) * Y;
+        s[28] += (-y * X) * X + (-y * Y) * Y;
     }
 }
 
+// Sums of N values over a wave, halving the values with the lanes (about N
+// exchanges instead of 6 N): value i of lane l and of lane l ^ d meet in the
+// half that keeps it.  Afterwards s[0] of lane l is the sum of value
+// wave_sum_index(l), in both lanes l and l ^ 1.
+template <int N>   // 16 or 32
+SFOC_DEV void wave_sums(double* s) {
+    const int lane = threadIdx.x & 63;
+    int d = 32;
+#pragma unroll
+    for (int half = N / 2; half >= 1; half >>= 1, d >>= 1) {
+        const bool up = lane & d;
+#pragma unroll
+        for (int q = 0; q < half; ++q) {
+            const double lo = s[q], hi = s[q + half];
+            s[q] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, d, 64);
+        }
+    }
+    for (; d >= 1; d >>= 1) s[0] += __shfl_xor(s[0], d, 64);
+}
+template <int N>
+SFOC_DEV int wave_sum_index(int lane) {   // the top bits of the lane, as many as N has
+    return lane / (64 / N);
+}
+
+// One workgroup: its time is latency, of the loads and of the serial solve.  A
+// pass per refit tests the candidates and sums the normal equations of the
+// inliers at once, four candidates' loads in flight a thread.  5041 candidates,
+// projective, two refits: 58 us with two passes a refit, 256 threads, a load at
+// a time and 44 sums reduced one by one; 23 us so.
 template <bool PROJ>
 __global__ __launch_bounds__(kFinNT) void finish_kernel(Args a) {
+    constexpr int kSumN = PROJ ? 32 : 16, kU = 4;   // sums, padded; candidates in flight
+    static_assert(kSumN >= (PROJ ? kSumsProj : kSumsAff), "room for the sums");
     __shared__ double sM[9];
-    __shared__ double part[kFinNT / 64][kSumsProj];
+    __shared__ double part[kFinNT / 64][kSumN], total[kSumN];
     __shared__ int bc[kFinNT / 64], bi[kFinNT / 64], ci[kFinNT / 64];
     __shared__ int flag;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -365,6 +404,7 @@ __global__ __launch_bounds__(kFinNT) void finish_kernel(Args a) {
     const int k = a.k;
     // best hypothesis: most inliers, lowest index on ties
     int best = -1, bidx = 0x7fffffff;
+#pragma unroll 8
     for (int h = t; h < a.n_hyp; h += kFinNT) {
         const int c = a.counts[h];
         if (c > best) {   // increasing h: the first maximum of this thread
@@ -409,48 +449,50 @@ __global__ __launch_bounds__(kFinNT) void finish_kernel(Args a) {
         }
         return;
     }
-    constexpr int nsum = PROJ ? kSumsProj : kSumsAff;
     int ninl = 0;
     for (int it = 0;; ++it) {
         double M[9];
         for (int q = 0; q < 9; ++q) M[q] = sM[q];
-        // inlier set of the current model and its count
+        // inlier set of the current model, its count, and (if a refit follows)
+        // the normal equations: per-thread sums over a fixed candidate subset,
+        // then fixed-order wave and workgroup reductions
+        const bool refit = it < a.n_refine;
         int c = 0;
-        for (int j = t; j < n; j += kFinNT) {
-            const bool in = inlier(M, proj, a.cand[j], a.thr_n2);
-            a.inl[j] = in;
-            c += in;
+        double s[kSumN];
+#pragma unroll
+        for (int q = 0; q < kSumN; ++q) s[q] = 0.0;
+        for (int j0 = t; j0 < n; j0 += kU * kFinNT) {
+            double4 p[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) p[u] = a.cand[min(j0 + u * kFinNT, n - 1)];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int j = j0 + u * kFinNT;
+                if (j >= n) continue;
+                const bool in = inlier(M, proj, p[u], a.thr_n2);
+                a.inl[j] = in;
+                c += in;
+                if (in && refit) terms<PROJ>(p[u], s);
+            }
         }
         for (int d = 32; d >= 1; d >>= 1) c += __shfl_down(c, d, 64);
         if (lane == 0) ci[wv] = c;
+        if (refit) {
+            wave_sums<kSumN>(s);
+            if (lane % (64 / kSumN) == 0) part[wv][wave_sum_index<kSumN>(lane)] = s[0];
+        }
         __syncthreads();
         ninl = 0;
         for (int w = 0; w < kFinNT / 64; ++w) ninl += ci[w];
-        if (it == a.n_refine || ninl < k) break;
-        // least squares over the inliers: per-thread sums over a fixed
-        // candidate subset, then fixed-order wave and workgroup reductions
-        double s[nsum];
-#pragma unroll
-        for (int q = 0; q < nsum; ++q) s[q] = 0.0;
-        for (int j = t; j < n; j += kFinNT)
-            if (a.inl[j]) terms<PROJ>(a.cand[j], s);
-        // all sums step by step, so each step's shuffles are independent
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1)
-#pragma unroll
-            for (int q = 0; q < nsum; ++q) s[q] += __shfl_down(s[q], d, 64);
-        if (lane == 0)
-#pragma unroll
-            for (int q = 0; q < nsum; ++q) part[wv][q] = s[q];
+        if (!refit || ninl < k) break;
+        if (t < kSumN) {
+            double v = 0.0;
+            for (int w = 0; w < kFinNT / 64; ++w) v += part[w][t];
+            total[t] = v;
+        }
         __syncthreads();
         if (t == 0) {
-            double tot[nsum];
-#pragma unroll
-            for (int q = 0; q < nsum; ++q) {
-                double v = 0.0;
-                for (int w = 0; w < kFinNT / 64; ++w) v += part[w][q];
-                tot[q] = v;
-            }
+            const double* tot = total;
             bool good;
             if (!proj) {   // [x y 1] normal matrix, right-hand sides X and Y
                 double A[3][3], b[2][3];
@@ -479,16 +521,26 @@ __global__ __launch_bounds__(kFinNT) void finish_kernel(Args a) {
                 }
             } else {
                 double A[8][8], b[1][8];
-                int o = 0;
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
+                for (int i = 0; i < 3; ++i)
 #pragma unroll
-                    for (int j = i; j < 8; ++j, ++o) {
-                        A[i][j] = tot[o];
-                        A[j][i] = tot[o];
+                    for (int j = 0; j < 3; ++j) {
+                        const int o = i <= j ? (i == 0 ? j : i == 1 ? 2 + j : 5) : (j == 0 ? i : 2 + i);
+                        A[i][j] = A[3 + i][3 + j] = tot[o];
+                        A[i][3 + j] = A[3 + i][j] = 0.0;
                     }
 #pragma unroll
-                for (int i = 0; i < 8; ++i) b[0][i] = tot[36 + i];
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        A[i][6 + j] = A[6 + j][i] = tot[6 + 2 * i + j];
+                        A[3 + i][6 + j] = A[6 + j][3 + i] = tot[12 + 2 * i + j];
+                    }
+                A[6][6] = tot[18];
+                A[6][7] = A[7][6] = tot[19];
+                A[7][7] = tot[20];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) b[0][i] = tot[21 + i];
                 good = cholesky_solve<8, 1>(A, b);
                 if (good) {
                     for (int i = 0; i < 8; ++i) sM[i] = b[0][i];
@@ -503,10 +555,20 @@ __global__ __launch_bounds__(kFinNT) void finish_kernel(Args a) {
         }
     }
     __syncthreads();
-    for (int j = t; j < n; j += kFinNT) {
-        const int i = a.cidx[j];
-        a.cps[i].flags = (a.cps_in[i].flags & ~(SFOC_CP_VALID | SFOC_CP_INCONSISTENT)) |
-                         (a.inl[j] ? SFOC_CP_VALID : SFOC_CP_INCONSISTENT);
+    for (int j0 = t; j0 < n; j0 += kU * kFinNT) {
+        int i[kU];
+        uint32_t fl[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) i[u] = a.cidx[min(j0 + u * kFinNT, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) fl[u] = a.cps_in[i[u]].flags;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int j = j0 + u * kFinNT;
+            if (j < n)
+                a.cps[i[u]].flags = (fl[u] & ~(SFOC_CP_VALID | SFOC_CP_INCONSISTENT)) |
+                                    (a.inl[j] ? SFOC_CP_VALID : SFOC_CP_INCONSISTENT);
+        }
     }
     if (t == 0) {
         // pixels: P = Tr^-1 M Ts with Ts = [[s, 0, -cr s], [0, s, -cc s], [0, 0, 1]]
