@@ -12,8 +12,8 @@
 //     to a list per tile in raster order; with its bits a mask word holds the
 //     place in that list of its first corner.  (A map of the image, written
 //     and read at the corners alone, moved a cache line per corner.)
-//     Bound by the three-operand minima and maxima, about 80 a pixel and
-//     13 % of ring pixels (min / max do not fuse: one a lane and cycle).
+//     Bound by the minima and maxima, 72 a pixel and 13 % of ring pixels
+//     (they do not fuse: one a lane and cycle).
 //     Only float32 subtractions and min / max are involved, so V is exact.
 //  2. selection, one workgroup per block: the threads walk the block's mask
 //     words, read the strengths of the set bits from the tiles' lists, and
@@ -21,9 +21,9 @@
 //     (strength descending, raster index within the block ascending) in
 //     registers; a bitonic sort of all threads' lists in LDS (K = 1: a
 //     minimum) gives the block's first per_block.
-// 10000 x 10000 pixels, 71 x 71 blocks of one point: strength 580 -> 385 us
-// (149 -> 96 VALU instructions a pixel, four pixels a tile load, branch-free
-// suppression), selection 98 -> 40 us (lists instead of the map).
+// 10000 x 10000 pixels, 71 x 71 blocks of one point: strength 580 -> 345 us
+// (149 -> 84 VALU instructions a strength, four pixels a tile load, no region
+// test inside it, branch-free suppression), selection 98 -> 40 us (lists instead of the map).
 //  3. compaction (one workgroup): block counts prefix-summed, each block's
 //     interest points copied to its place in one list.
 #include <hip/hip_runtime.h>
@@ -68,36 +68,45 @@ constexpr int kCx[16] = {0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3, -3, -3, -2, -1};
 SFOC_DEV float min3(float a, float b, float c) { return fminf(fminf(a, b), c); }
 SFOC_DEV float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// Largest of the 16 values (eight instructions).
-template <typename F>
-SFOC_DEV float fold16(const float (&x)[16], F&& f) {
-    return f(f(f(x[0], x[1], x[2]), f(x[3], x[4], x[5]), f(x[6], x[7], x[8])), f(x[9], x[10], x[11]),
-             f(x[12], f(x[13], x[14], x[15]), x[15]));
+// The same of two loaded values, by the instruction itself: before fminf and
+// fmaxf the compiler would quiet each of the 16 loads (an instruction each).
+SFOC_DEV float min2(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+SFOC_DEV float max2(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
 // V from the circle's raw values: subtraction rounds monotonically, so the
 // minimum (maximum) over an arc of the rounded differences is the rounded
 // difference of the arc's minimum (maximum), and the maximum over the arcs of
-// those likewise.  The arcs of nine are three arcs of three: 32 three-operand
-// minima and 32 maxima for the 16 arcs, then 16 to fold them.
+// those likewise.  The arcs from k and k + 1, k even, share the eight pixels
+// k + 1 .. k + 8, four pairs: the larger of their two minima is
+// min(pairs, max(p[k], p[k + 9])), 36 instructions a polarity with the pairs
+// and the fold (16 arcs by three arcs of three: 40).
 SFOC_DEV float strength(const float* tile, int ty, int tx) {
     const float* nb = tile + (ty - 3) * kIS + (tx - 3);
     const float c = nb[3 * kIS + 3];
-    float p[16], mn[16], mx[16], lo[16], hi[16];
+    float p[16], mn[8], mx[8], lo[8], hi[8];
 #pragma unroll
     for (int i = 0; i < 16; ++i) p[i] = nb[(kCy[i] + 3) * kIS + kCx[i] + 3];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        mn[i] = min3(p[i], p[(i + 1) & 15], p[(i + 2) & 15]);
-        mx[i] = max3(p[i], p[(i + 1) & 15], p[(i + 2) & 15]);
+    for (int j = 0; j < 8; ++j) {
+        mn[j] = min2(p[2 * j + 1], p[(2 * j + 2) & 15]);
+        mx[j] = max2(p[2 * j + 1], p[(2 * j + 2) & 15]);
     }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        lo[k] = min3(mn[k], mn[(k + 3) & 15], mn[(k + 6) & 15]);
-        hi[k] = max3(mx[k], mx[(k + 3) & 15], mx[(k + 6) & 15]);
+    for (int j = 0; j < 8; ++j) {
+        const float a = p[2 * j], b = p[(2 * j + 9) & 15];
+        lo[j] = min3(min3(mn[j], mn[(j + 1) & 7], mn[(j + 2) & 7]), mn[(j + 3) & 7], max2(a, b));
+        hi[j] = max3(max3(mx[j], mx[(j + 1) & 7], mx[(j + 2) & 7]), mx[(j + 3) & 7], min2(a, b));
     }
-    const float bright = fold16(lo, [](float a, float b, float d) { return max3(a, b, d); });
-    const float dark = fold16(hi, [](float a, float b, float d) { return min3(a, b, d); });
+    const float bright = max3(max3(lo[0], lo[1], lo[2]), max3(lo[3], lo[4], lo[5]), fmaxf(lo[6], lo[7]));
+    const float dark = min3(min3(hi[0], hi[1], hi[2]), min3(hi[3], hi[4], hi[5]), fminf(hi[6], hi[7]));
     return fmaxf(bright - c, c - dark);
 }
 
@@ -139,12 +148,20 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
         }
     }
     __syncthreads();
-    // strengths of the tile and a 1-pixel ring; -inf outside the region
-    for (int e = t; e < kVS * kVS; e += kNT) {
-        const int a = e / kVS, c = e - a * kVS;
-        const int y = ty0 - 1 + a, x = tx0 - 1 + c;
-        const bool in = y >= R.b && y < R.H - R.b && x >= R.b && x < R.W - R.b;
-        vs[e] = in ? strength(tile, a + kHalo - 1, c + kHalo - 1) : -INFINITY;
+    // strengths of the tile and a 1-pixel ring; -inf outside the region (which
+    // only tiles at its border reach)
+    if (ty0 - 1 >= R.b && tx0 - 1 >= R.b && ty0 + kTS < R.H - R.b && tx0 + kTS < R.W - R.b) {
+        for (int e = t; e < kVS * kVS; e += kNT) {
+            const int a = e / kVS, c = e - a * kVS;
+            vs[e] = strength(tile, a + kHalo - 1, c + kHalo - 1);
+        }
+    } else {
+        for (int e = t; e < kVS * kVS; e += kNT) {
+            const int a = e / kVS, c = e - a * kVS;
+            const int y = ty0 - 1 + a, x = tx0 - 1 + c;
+            const bool in = y >= R.b && y < R.H - R.b && x >= R.b && x < R.W - R.b;
+            vs[e] = in ? strength(tile, a + kHalo - 1, c + kHalo - 1) : -INFINITY;
+        }
     }
     __syncthreads();
     // Thread t suppresses column t % 32 of rows 4 (t / 32) .. + 3, so a wave
@@ -167,8 +184,8 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
             const float v = m[k + 1];
-            const float before = fmaxf(max3(l[k], m[k], r[k]), l[k + 1]);
-            const float after = fmaxf(max3(l[k + 2], m[k + 2], r[k + 2]), r[k + 1]);
+            const float before = max2(max3(l[k], m[k], r[k]), l[k + 1]);
+            const float after = max2(max3(l[k + 2], m[k + 2], r[k + 2]), r[k + 1]);
             // (a strength outside the region is -inf, below any threshold)
             keep[k] = v > thr && v > before && v >= after;
             bal[k] = __ballot(keep[k]);
