@@ -1204,9 +1204,10 @@ __global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void 
     }
 }
 
-// The second launch: a workgroup per point.
+// The second launch: a workgroup per point, for its latency: registers for four
+// channels' loads in flight rather than for several workgroups a CU.
 template <int L>
-__global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void match_combine_kernel(const MatchArgs A) {
+__global__ __launch_bounds__(MatchCfg<L>::NT, (MatchCfg<L>::NT + 255) / 256) void match_combine_kernel(const MatchArgs A) {
     using C = MatchCfg<L>;
     extern __shared__ float4 lds_raw[];
     float2* tw = reinterpret_cast<float2*>(lds_raw);
@@ -1227,18 +1228,29 @@ __global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void 
     for (int q = 0; q < C::BINS; ++q) acc[q] = make_float2(0.f, 0.f);
     const float2* __restrict__ o = A.spec + (size_t)i * A.z * Spread<L>::bins + t;
     const float2* __restrict__ f = A.spec_self + (size_t)i * A.z * 4;
-#pragma unroll 2
-    for (int h = 0; h < A.z; ++h) {
-        float2 p[C::BINS];
+    constexpr int kU = L <= 64 ? 4 : L <= 128 ? 3 : 2;
+    for (int h0 = 0; h0 < A.z; h0 += kU) {
+        float2 p[kU][C::BINS], fs[kU][4];
 #pragma unroll
-        for (int q = 0; q < C::BINS; ++q) p[q] = o[h * Spread<L>::bins + q * C::NT];
+        for (int k = 0; k < kU; ++k) {
+            const int h = min(h0 + k, A.z - 1);
 #pragma unroll
-        for (int q = 0; q < C::BINS; ++q) {
-            const float2 a = acc[q];
-            acc[q] = cadd(a, p[q]);
-            if (q == 0 || q == C::NB / 2) {
-                const float2 xs = f[4 * h + (q ? 2 : 0)], yt = f[4 * h + (q ? 3 : 1)];
-                acc[q] = pick(t == 0, make_float2(fmaf(xs.x, yt.x, a.x), fmaf(xs.y, yt.y, a.y)), acc[q]);
+            for (int q = 0; q < C::BINS; ++q) p[k][q] = o[h * Spread<L>::bins + q * C::NT];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) fs[k][q] = f[4 * h + q];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            if (h0 + k >= A.z) break;
+#pragma unroll
+            for (int q = 0; q < C::BINS; ++q) {
+                const float2 a = acc[q];
+                acc[q] = cadd(a, p[k][q]);
+                if (q == 0 || q == C::NB / 2) {
+                    const float2 xs = fs[k][q ? 2 : 0], yt = fs[k][q ? 3 : 1];
+                    acc[q] = pick(t == 0, make_float2(fmaf(xs.x, yt.x, a.x), fmaf(xs.y, yt.y, a.y)), acc[q]);
+                }
             }
         }
     }
