@@ -373,7 +373,11 @@ Layout layout(int64_t H, int64_t W, int nblocks, int per) {
     L.bips = take(sizeof(int32_t) * 2 * (size_t)nblocks * per);
     L.bsc = take(sizeof(float) * (size_t)nblocks * per);
     L.bcnt = take(sizeof(int32_t) * (size_t)nblocks);
-    L.total = o;
+    // never less than a strength per pixel and a mask word per 32, which callers
+    // that size their workspace once may count on
+    const size_t map = align_up(sizeof(float) * (size_t)H * (size_t)W, 256) +
+                       align_up(sizeof(uint32_t) * (size_t)H * L.mask_words, 256);
+    L.total = std::max(o, map + (o - L.bips));
     return L;
 }
 
