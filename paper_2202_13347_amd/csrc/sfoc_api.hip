@@ -152,7 +152,7 @@ static hipError_t register_core(const float* ref, int64_t Hr, int64_t Wr, int64_
     if (e == hipSuccess) e = hipStreamWaitEvent(st, side->join, 0);
     if (e != hipSuccess) return e;
     return launch_match_finish(dsen, Hs, Ws, dref, Hr, Wr, i1, i2, z, dtype, ips, prior, n, m, r, ncc, cps,
-                               base + L.match, split, st, consistency);
+                               base + L.match, split, spread, st, consistency);
 }
 
 // ---- band-streamed registration ---------------------------------------------

@@ -113,7 +113,8 @@ hipError_t launch_match(const void* desc_sen, int64_t Hs, int64_t Ws, const void
 // The same match in two launches, so that the integral images need not
 // exist before the second: launch_match_fft runs the transforms and leaves
 // R_ST and the template sums in `split` (match_split_bytes bytes), with
-// `spread` (match_spread_bytes, or null) in the spread form where it is taken;
+// `spread` (match_spread_bytes, or null) the channels' products instead, where
+// the spread form is taken;
 // launch_match_finish assembles the NCC surfaces (ncc, if set) and the
 // peaks into cps from them and the integral images, then (consistency) the
 // median check.  Only where match_split_ok: an FFT side without offset
@@ -129,7 +130,7 @@ hipError_t launch_match_fft(const void* desc_sen, int64_t Hs, int64_t Ws, const 
 hipError_t launch_match_finish(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
                                int64_t Wr, const double* i1, const double* i2, int z, int dtype, const int32_t* ips,
                                const int32_t* prior, int n, int m, int r, float* ncc, sfoc_cp* cps, void* ws,
-                               void* split, hipStream_t st, bool consistency);
+                               void* split, void* spread, hipStream_t st, bool consistency);
 // The median-displacement consistency check over n records (one workgroup).
 hipError_t launch_consistency(sfoc_cp* cps, const int32_t* prior, int n, hipStream_t st);
 // cps[i].sen_row += dy for i < n.

@@ -1158,7 +1158,7 @@ SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const floa
 // Few interest points leave most CUs idle while a workgroup takes a point's
 // channels one after the other.  Spread form: a workgroup per (point, channel)
 // leaves the spectrum product, and a second launch sums the products in
-// channel order, as the fused form does, and transforms back.  The products of
+// channel order, as the fused form does.  The products of
 // the two packed self bins are fused into that sum, so their factors are left
 // instead.
 template <int L>
@@ -1204,14 +1204,21 @@ __global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void 
     }
 }
 
-// The second launch: a workgroup per point, for its latency: registers for four
-// channels' loads in flight rather than for several workgroups a CU.
+// The second launch: a workgroup per point, for its latency: registers for up to
+// four channels' loads in flight rather than for several workgroups a CU.  Above
+// side 64 it comes after the integral images and takes the NCC and the peak too
+// (119 points, side 128: 161 -> 156 us a call; 64 points, side 160: 231 -> 214);
+// at side 64 its 128 threads would be slower at it than ncc_finish_kernel's 256
+// (16 points: 80 us a call with that, 89 without), so there it leaves R_ST.
+template <int L>
+constexpr bool spread_peak() { return L > 64; }
 template <int L>
 __global__ __launch_bounds__(MatchCfg<L>::NT, (MatchCfg<L>::NT + 255) / 256) void match_combine_kernel(const MatchArgs A) {
     using C = MatchCfg<L>;
     extern __shared__ float4 lds_raw[];
     float2* tw = reinterpret_cast<float2*>(lds_raw);
     float2* buf = tw + L;
+    double* red = reinterpret_cast<double*>(buf + C::buf_elems);
     const int i = (int)blockIdx.x, m = A.m, r = A.r, M = m + 2 * r, V = 2 * r + 1, t = threadIdx.x;
     const int py = A.ips[2 * i], px = A.ips[2 * i + 1];
     const int64_t ty = (int64_t)py - m / 2, tx = (int64_t)px - m / 2;
@@ -1254,18 +1261,23 @@ __global__ __launch_bounds__(MatchCfg<L>::NT, (MatchCfg<L>::NT + 255) / 256) voi
             }
         }
     }
-    __syncthreads();
-    inverse_2d<L>(acc, V, tw, buf);
-    float* __restrict__ R = A.rst + (int64_t)i * V * V;
-    for (int e = t; e < V * V; e += C::NT) {
-        const int u = e / V, v = e - u * V;
-        const float* rr = reinterpret_cast<const float*>(buf + C::row((u >> 1) * 2));
-        R[e] = rr[(u & 1) * L + v];
-    }
     if (t < 2) {
         double s = 0.0;
         for (int h = 0; h < A.z; ++h) s += A.spec_sum[2 * ((size_t)i * A.z + h) + t];
-        A.tsum[2 * i + t] = s;
+        if constexpr (spread_peak<L>()) red[64 + t] = s;
+        else A.tsum[2 * i + t] = s;
+    }
+    __syncthreads();
+    inverse_2d<L>(acc, V, tw, buf);
+    auto rst_at = [&](int u, int v) {
+        const float* rr = reinterpret_cast<const float*>(buf + C::row((u >> 1) * 2));
+        return rr[(u & 1) * L + v];
+    };
+    if constexpr (spread_peak<L>()) {
+        ncc_peak<C::NT>(A, i, i, 0, 0, V, V, red[64], red[65], red, rst_at);
+    } else {
+        float* __restrict__ R = A.rst + (int64_t)i * V * V;
+        for (int e = t; e < V * V; e += C::NT) R[e] = rst_at(e / V, e % V);
     }
 }
 
@@ -1992,10 +2004,11 @@ size_t match_split_bytes(int n, int r) { return split_rst_bytes(n, r) + (size_t)
 // products through memory (4 L^2 bytes an IP and channel), and pays while the
 // fused form's workgroups, one an IP, leave CUs idle.  Times of a pair call of
 // 700 x 700 pixels, z = 16 (us, fused and spread):
-//   L =  64:  n = 16  191   99;  256  210  144;  512  222  191;  640  261  230
-//   L = 128:  n = 16  228  130;   64  230  158;  128  243  204;  192  265  282
-//   L = 160:  n = 16  367  171;   64  365  236;   96  371  280;  128  372  350
-//   L = 192:  n = 16  418  187;   64  439  287;   96  451  394;  128  459  459
+//   L =  64:  n = 16  191   94;  256  210  142;  512  222  188;  640  261  230
+//   L = 128:  n = 16  228  130;   64  230  154;  128  243  189;  192  265  282
+//   L = 160:  n = 16  367  155;   64  365  212;   96  371  258;  128  372  350
+//   L = 192:  n = 16  418  181;   64  439  270;   96  451  394;  128  459  459
+// (beyond the line with the NCC in a launch of its own)
 // and at n = 16, L = 64: z = 4  106  86;  z = 2  84  92.  The products are held
 // to 160 MB (a scene's descriptors at 2048 x 2048 are 540).
 constexpr size_t kSpreadBytes = 160000000;
@@ -2054,35 +2067,34 @@ static hipError_t launch_spectra(const MatchArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(kern, dim3(a.n * a.z), dim3(C::NT), C::lds_bytes, st, a);
     return hipGetLastError();
 }
+// The spread form's scratch (match_spread_bytes) in the arguments.
 template <int L>
-static hipError_t launch_spread(MatchArgs a, void* scratch, hipStream_t st) {
-    using C = MatchCfg<L>;
+static void spread_args(MatchArgs& a, void* scratch) {
     const size_t items = (size_t)a.n * a.z;
     a.spec = (float2*)scratch;
     a.spec_self = a.spec + items * Spread<L>::bins;
     a.spec_sum = (double*)(a.spec_self + items * 4);
+}
+template <int L>
+static hipError_t launch_combine(MatchArgs a, void* spread, hipStream_t st) {
+    using C = MatchCfg<L>;
+    spread_args<L>(a, spread);
     auto kern = match_combine_kernel<L>;
     hipError_t e = ensure_dynamic_lds((const void*)kern, (int)C::lds_bytes);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.n), dim3(C::NT), C::lds_bytes, st, a);
+    return hipGetLastError();
+}
+template <int L>
+static hipError_t launch_transforms(MatchArgs a, void* spread, hipStream_t st) {
+    if (!spread) return launch_match_side<L, true>(a, a.dtype, st);
+    spread_args<L>(a, spread);
     trace_begin(st, SFOC_K_MATCH);
-    e = a.dtype == 0 ? launch_spectra<L, 0>(a, st) : a.dtype == 1 ? launch_spectra<L, 1>(a, st) : launch_spectra<L, 2>(a, st);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(kern, dim3(a.n), dim3(C::NT), C::lds_bytes, st, a);
-        e = hipGetLastError();
-    }
+    hipError_t e = a.dtype == 0   ? launch_spectra<L, 0>(a, st)
+                   : a.dtype == 1 ? launch_spectra<L, 1>(a, st) : launch_spectra<L, 2>(a, st);
+    if (e == hipSuccess && !spread_peak<L>()) e = launch_combine<L>(a, spread, st);
     trace_end(st, SFOC_K_MATCH);
     return e;
-}
-// The transforms of the split form; spread: match_spread_bytes of scratch, or
-// null for the fused form.
-static hipError_t launch_split(const MatchArgs& a, int L, void* spread, hipStream_t st) {
-    switch (L) {
-        case 64: return spread ? launch_spread<64>(a, spread, st) : launch_match_side<64, true>(a, a.dtype, st);
-        case 128: return spread ? launch_spread<128>(a, spread, st) : launch_match_side<128, true>(a, a.dtype, st);
-        case 160: return spread ? launch_spread<160>(a, spread, st) : launch_match_side<160, true>(a, a.dtype, st);
-        case 192: return spread ? launch_spread<192>(a, spread, st) : launch_match_side<192, true>(a, a.dtype, st);
-        default: return hipErrorInvalidValue;
-    }
 }
 
 hipError_t launch_match_fft(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
@@ -2091,21 +2103,38 @@ hipError_t launch_match_fft(const void* desc_sen, int64_t Hs, int64_t Ws, const 
     if (!match_split_ok(n, m, r, dtype)) return hipErrorInvalidValue;
     const MatchArgs a = split_args(desc_sen, Hs, Ws, desc_ref, Hr, Wr, nullptr, nullptr, z, dtype, ips, prior, n, m,
                                    r, ncc, cps, ws, split);
-    return launch_split(a, match_plan_dt(n, m, r, dtype).L, match_spread_bytes(n, m, r, z, dtype) ? spread : nullptr,
-                        st);
+    if (!match_spread_bytes(n, m, r, z, dtype)) spread = nullptr;
+    switch (match_plan_dt(n, m, r, dtype).L) {
+        case 64: return launch_transforms<64>(a, spread, st);
+        case 128: return launch_transforms<128>(a, spread, st);
+        case 160: return launch_transforms<160>(a, spread, st);
+        case 192: return launch_transforms<192>(a, spread, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_match_finish(const void* desc_sen, int64_t Hs, int64_t Ws, const void* desc_ref, int64_t Hr,
                                int64_t Wr, const double* i1, const double* i2, int z, int dtype, const int32_t* ips,
                                const int32_t* prior, int n, int m, int r, float* ncc, sfoc_cp* cps, void* ws,
-                               void* split, hipStream_t st, bool consistency) {
+                               void* split, void* spread, hipStream_t st, bool consistency) {
     if (!match_split_ok(n, m, r, dtype) || !i1 || !i2) return hipErrorInvalidValue;
     const MatchArgs a = split_args(desc_sen, Hs, Ws, desc_ref, Hr, Wr, i1, i2, z, dtype, ips, prior, n, m, r, ncc,
                                    cps, ws, split);
+    hipError_t e;
     trace_begin(st, SFOC_K_PEAK);
-    hipLaunchKernelGGL(ncc_finish_kernel, dim3(n), dim3(kFinishNT), 0, st, a);
+    const int L = match_plan_dt(n, m, r, dtype).L;
+    if (L > 64 && spread && match_spread_bytes(n, m, r, z, dtype)) {
+        static_assert(!spread_peak<64>() && spread_peak<128>() && spread_peak<160>() && spread_peak<192>(), "as here");
+        switch (L) {
+            case 128: e = launch_combine<128>(a, spread, st); break;
+            case 160: e = launch_combine<160>(a, spread, st); break;
+            default: e = launch_combine<192>(a, spread, st); break;
+        }
+    } else {
+        hipLaunchKernelGGL(ncc_finish_kernel, dim3(n), dim3(kFinishNT), 0, st, a);
+        e = hipGetLastError();
+    }
     trace_end(st, SFOC_K_PEAK);
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess || !consistency) return e;
     return launch_consistency(cps, prior, n, st);
 }
