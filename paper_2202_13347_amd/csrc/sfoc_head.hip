@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "sfoc_dev.h"
 #include "sfoc_launch.h"
 #include "sfoc_trace.h"
@@ -33,6 +35,12 @@ constexpr int kMaxN = 65536;
 
 // To bfloat16 (nearest even) and back, by the conversion instruction.
 SFOC_DEV float bf16_round(float w) { return static_cast<float>(static_cast<__bf16>(w)); }
+// Orders a wave's LDS writes before its following reads.
+SFOC_DEV void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 // The thread index laundered through an empty asm: what a phase derives from
 // it is recomputed there instead of being hoisted out of the sample loop and
 // kept in registers across the other phases.
@@ -48,21 +56,26 @@ SFOC_DEV int tid_here() {
 // partials and the small vectors of the fully connected layers is written.
 // The convolutions, their data gradients and their weight gradients are
 // products on the FP32 matrix cores (16 x 16 x 4: FP32 operands and sums):
-//   forward        D[o][pos]  = sum over (tap, c) of W[o][c][tap] in[c][S pos + tap]
-//   data gradient  D[c][pos]  = sum over (tap, o) of W[o][c][tap] g[o][(pos - tap) / S],
+//   forward        D[o][pos]  = sum over (c, tap) of W[o][c][tap] in[c][S pos + tap]
+//   data gradient  D[c][pos]  = sum over (o, tap) of W[o][c][tap] g[o][(pos - tap) / S],
 //                  one product per parity class of the position (its taps)
 //   weight grad.   D[o][c]    = sum over pos of g[o][pos] in[c][S pos + tap], per tap
 // The input of conv2 (32 x 33 x 33 floats) would fill the LDS, so conv2 works
 // in three bands of output rows and conv1 is computed per band, again in the
 // backward pass (9 of 290 multiply-adds a sample).  Every sum has a fixed
 // order: results are bit-reproducible.
+// A 16 x 16 x 4 product adds its four terms to the sum one after the other,
+// each as fmaf does.  So a convolution's sum is the plain loop's, from the bias
+// over channels and then taps in one chain of fmaf, and fc1's and fc2's are
+// such chains: every activation, and with it what the ReLUs let through of a
+// gradient, is defined by that loop and does not depend on the tiling.
 // What bounds it: with one workgroup a CU, the LDS reads and the barriers
 // between phases; the matrix-core instructions alone (10.8 k of 32 cycles a
 // sample in training, a quarter of them on each SIMD) are 36 us.  A training
 // step of 256 samples took 2043 us with a thread per output pixel (or weight)
-// and every activation in HBM, 166 us now (this launch 155 us of it, the update
-// 10 us); the forward pass of 400 samples 153 us and 81 us (two rounds of 256
-// CUs; without conv2 46 us, without the other phases 67 to 78 us each).
+// and every activation in HBM, 138 us now (in a kernel trace this launch 134 us
+// and the update 10); the forward pass of 400 samples 153 us and 77 us (two
+// rounds of 256 CUs; fc1's chain of 808 is 4 us of each).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kNetNT = 512, kWaves = kNetNT / 64;
 constexpr int kWP = 40;                          // LDS pitch of W[(tap, c)][o] (four rows on 32 banks)
@@ -75,42 +88,61 @@ constexpr int kP1 = kS1 + 2, kL1 = kBR * kP1;    // a1 band: columns -1 .. 33
 constexpr int kP2 = kS2 + 2, kL2 = kP2 * kP2;    // a2 (later its gradient), rows and columns -1 .. 17
 constexpr int kP3 = kS3 + 2, kL3 = kP3 * kP3;
 constexpr int kL4 = kS4 * kS4;
+// Weights of 32 outputs are loaded by 16 lanes an output: no division for an
+// element's place (256 samples forward: 47 us with one for each and the registers
+// it spilled, 38 us so).
+constexpr int kLanes = kNetNT / kCh;
+// fc1 in three chunks of inputs: a chunk's weights as float4 [k / 4][o], at a
+// pitch that spreads the stores of 16 inputs and 4 outputs over all banks.
+constexpr int kFcRows = 288, kFcChunks = 3, kFcPitch = kCh + 2, kFcPad = kFcRows * kFcChunks;
+constexpr int kFcRegs = kFcRows / kLanes;
+static_assert(kFcPad >= kFcIn && kFcRegs * kLanes == kFcRows && kFcRows % 4 == 0, "fc1 chunks");
 constexpr int kPC = kS0 + 2;                     // crop, rows and columns -1 .. 33
 static_assert(kL1 % 2 == 1 && kL2 % 2 == 1 && kL3 % 2 == 1 && kL4 % 2 == 1, "odd planes");
 constexpr int kConvParams = kF1;                 // conv1..conv4 weights and biases: a prefix of the vector
 struct NetLds {
-    float w[9 * kCh * kWP];     // the layer's rounded weights [(tap, c)][o]
+    float w[9 * kCh * kWP];     // the layer's rounded weights [(c, tap)][o], o at weight_col
     float a2[kCh * kL2];
     union {
         float a1[kCh * kL1];
         struct {
             float a3[kCh * kL3];
-            float a4[kFlat];
+            float a4[kFcPad];   // then the statistics: fc1's input, zeros to the end
+            float4 fw[kFcRows / 4 * kFcPitch];
         };
     };
     float crop[kPC * kPC + 3];
     float w1[9 * kCh];          // conv1 weights [tap][o]
-    float h1[kCh], dh1[kCh], out[4], dout[4], stats[kNStat];
+    float bias[3 * kCh];        // of conv2, conv3, conv4
+    float f2[3 * kCh];          // fc2 weights [q][o]
+    float h1[kCh], dh1[kCh], dout[4];
     int job;
 };
 static_assert(sizeof(NetLds) <= 160 * 1024 && kWaves * kCh * 16 <= kCh * kL1, "LDS of a CU; the wave sums fit a1");
+static_assert(kCh * kL3 + kFcPad + kFcRows * kFcPitch <= kCh * kL1 && kCh * kL3 % 4 == 0, "fc1 in the place of a1");
 
 SFOC_DEV f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // One layer's weights (32 x 32 x 9): loaded into registers ahead of the phase
-// before, then rounded to bfloat16 into w[(tap, c)][o].
-constexpr int kWRegs = kCh * kCh * 9 / kNetNT;
-static_assert(kWRegs * kNetNT == kCh * kCh * 9, "whole rounds");
+// before, then rounded to bfloat16 into w[(c, tap)][o].  Within its row an
+// output's place is exchanged by channel, so that the data gradient, whose lanes
+// run over the channels, reads from sixteen banks and not from four.
+SFOC_DEV int weight_swap(int c) { return 2 * ((c >> 2) & 3); }
+SFOC_DEV int weight_col(int o, int c) { return o ^ weight_swap(c); }
+constexpr int kWRegs = kCh * 9 / kLanes;
+static_assert(kWRegs * kLanes == kCh * 9, "whole rounds");
 SFOC_DEV void load_weights(const float* __restrict__ th, float (&v)[kWRegs]) {
+    const int t = tid_here();
+    const float* p = th + t / kLanes * (kCh * 9) + t % kLanes;
 #pragma unroll
-    for (int k = 0; k < kWRegs; ++k) v[k] = th[threadIdx.x + k * kNetNT];
+    for (int k = 0; k < kWRegs; ++k) v[k] = p[k * kLanes];
 }
 SFOC_DEV void stage_weights(const float (&v)[kWRegs], float* w) {
-    const int t = tid_here();
+    const int t = tid_here(), o = t / kLanes;
 #pragma unroll
     for (int k = 0; k < kWRegs; ++k) {
-        const int e = t + k * kNetNT, o = e / (kCh * 9), rem = e - o * kCh * 9, c = rem / 9, tap = rem - c * 9;
-        w[(tap * kCh + c) * kWP + o] = bf16_round(v[k]);
+        const int ct = t % kLanes + k * kLanes;
+        w[ct * kWP + weight_col(o, ct / 9)] = bf16_round(v[k]);
     }
 }
 
@@ -155,51 +187,59 @@ SFOC_DEV void conv1_band(NetLds& S, const float* __restrict__ th, int r0) {
 // Stride-2 convolution + bias + ReLU of `rows` output rows from a zero-bordered
 // LDS map `in` (plane LI, pitch PI; its first row is the row above output row
 // 0's centre) into `out` (plane LO, pitch PO, first pixel at OO).  A wave takes
-// tiles of 16 positions and 16 HALVES channels; a tap's operands are read
-// while the matrix instructions of the tap before run.  Two sums a tile, each
-// over half of the channels: shorter chains round less.
+// tiles of 16 positions and 16 HALVES channels, one chain of products each.
+// Product k = 9 c + tap: lane group g holds k = 4 s + g at step s, so that nine
+// steps (four channels) on, its operands lie four planes further: nine offsets a
+// lane.  The operands are read as many steps ahead as keep the reads under way
+// within the fifteen that a wave can count (256 samples forward: 51 us with nine
+// steps' reads at once, 46 us so).
 template <int HOUT, int LI, int PI, int LO, int PO, int OO, int HALVES>
-SFOC_DEV void conv_tiles(const float* in, const float* w, const float* __restrict__ bias, float* out, int rows) {
+SFOC_DEV void conv_tiles(const float* in, const float* w, const float* bias, float* out, int rows) {
     const int t = tid_here(), lane = t & 63, wv = t >> 6, n = lane & 15, g = lane >> 4;
-    constexpr int kSplit = 2 / HALVES, kS = kCh / 4;
+    constexpr int kSplit = 2 / HALVES, kS = 9, kGroups = kCh / 4, kAhead = HALVES == 2 ? 4 : 6;
     const int npos = rows * HOUT, jobs = kSplit * ((npos + 15) / 16);
+    int off[kS];
+#pragma unroll
+    for (int r = 0; r < kS; ++r) {
+        const int k = 4 * r + g, c = k / 9, tap = k - c * 9;
+        off[r] = c * LI + (tap / 3) * PI + tap % 3;
+    }
     for (int job = wv; job < jobs; job += kWaves) {
         const int h0 = job % kSplit, p = (job / kSplit) * 16 + n, pc = min(p, npos - 1);
         const int y = pc / HOUT, x = pc - y * HOUT;
-        const float* b0 = in + g * LI + 2 * y * PI + 2 * x;
-        const float* a0 = w + g * kWP + h0 * 16 + n;
-        f32x4 acc[2][HALVES];
+        const float* b0 = in + 2 * y * PI + 2 * x;
+        const float* a0 = w + g * kWP + h0 * 16;
+        f32x4 acc[HALVES];
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) acc[0][h] = acc[1][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float av[2][HALVES][kS], bv[2][kS];
-        auto read = [&](int tap, int buf) {
+        for (int h = 0; h < HALVES; ++h)
 #pragma unroll
-            for (int cs = 0; cs < kS; ++cs) {
-                bv[buf][cs] = b0[(tap / 3) * PI + tap % 3 + 4 * cs * LI];
+            for (int r = 0; r < 4; ++r) acc[h][r] = bias[(h0 + h) * 16 + 4 * g + r];
+        const float* ax[4];   // the lane's output in the rows of channels 4 q .. 4 q + 3, by q mod 4
 #pragma unroll
-                for (int h = 0; h < HALVES; ++h) av[buf][h][cs] = a0[(tap * kCh + 4 * cs) * kWP + 16 * h];
-            }
+        for (int q = 0; q < 4; ++q) ax[q] = a0 + (n ^ weight_swap(4 * q));
+        float av[kAhead + 1][HALVES], bv[kAhead + 1];
+        auto read = [&](int s) {
+            const int q = s / kS, r = s % kS, buf = s % (kAhead + 1);
+            bv[buf] = b0[off[r] + 4 * q * LI];
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h) av[buf][h] = ax[q % 4][4 * s * kWP + 16 * h];
         };
-        read(0, 0);
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            if (tap + 1 < 9) read(tap + 1, (tap + 1) & 1);
+        for (int s = 0; s < kAhead; ++s) read(s);
+#pragma unroll
+        for (int s = 0; s < kS * kGroups; ++s) {
+            if (s + kAhead < kS * kGroups) read(s + kAhead);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int cs = 0; cs < kS; ++cs)
-#pragma unroll
-                for (int h = 0; h < HALVES; ++h)
-                    acc[cs & 1][h] = mfma4(av[tap & 1][h][cs], bv[tap & 1][cs], acc[cs & 1][h]);
+            for (int h = 0; h < HALVES; ++h) acc[h] = mfma4(av[s % (kAhead + 1)][h], bv[s % (kAhead + 1)], acc[h]);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (p < npos) {
 #pragma unroll
             for (int h = 0; h < HALVES; ++h)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int o = (h0 + h) * 16 + 4 * g + r;
-                    out[o * LO + OO + y * PO + x] = fmaxf(acc[0][h][r] + acc[1][h][r] + bias[o], 0.f);
-                }
+                for (int r = 0; r < 4; ++r)
+                    out[((h0 + h) * 16 + 4 * g + r) * LO + OO + y * PO + x] = fmaxf(acc[h][r], 0.f);
         }
     }
 }
@@ -208,8 +248,9 @@ SFOC_DEV void conv_tiles(const float* in, const float* w, const float* __restric
 // `act` (plane LI, pitch PI; pixel (y, x) at OI + (y - y0) PI + x), masked by
 // act > 0 and written over it; g is the output gradient (plane LG, pitch PG,
 // first pixel at OG).  Position (2a + cy, 2b + cx) gets the taps i = 1 - cy (of
-// output row a + cy) and, for cy = 1, i = 2 (of row a); columns likewise.  The
-// waves draw (class, 16 positions, 16 channels) tiles from a counter, longest
+// output row a + cy) and, for cy = 1, i = 2 (of row a); columns likewise: T = 1,
+// 2 or 4 taps.  Product k = T o + tap: lane group q holds tap q mod T of outputs
+// q / T, q / T + 4 / T, ...  The waves draw (class, 16 positions, 16 channels) tiles from a counter, longest
 // first; what a tile computes does not depend on who draws it.
 template <int HOUT, int LG, int PG, int OG, int LI, int PI, int OI>
 SFOC_DEV void dgrad_tiles(const float* g, const float* w, float* act, int y0, int ya, int R1, int* counter) {
@@ -232,37 +273,37 @@ SFOC_DEV void dgrad_tiles(const float* g, const float* w, float* act, int y0, in
         const int cy = k < 2, cx = !(k & 1), jk = job - first[k], half = jk & 1;
         const int ny = (R1 - 2 * ya - cy + 1) / 2, nx = HOUT - cx, np = ny * nx;
         const int p = (jk >> 1) * 16 + n, pc = min(p, np - 1), a = pc / nx, b = pc - a * nx;
-        const float* gp = g + q * LG + OG + (ya + a) * PG + b;
-        const float* wp = w + (half * 16 + n) * kWP + q;
+        const int c = half * 16 + n;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        constexpr int kS = kCh / 4;
-        const int taps = (1 + cy) * (1 + cx);
-        float av[kS], bv[kS], an[kS], bn[kS];
-        auto read = [&](int k, float(&a_)[kS], float(&b_)[kS]) {
-            // cy = 0: tap 1, row a; cy = 1: tap 0, row a + 1, then tap 2, row a
-            const int iy = k >> cx, ix = cx ? k & 1 : 0;
+        auto run = [&](auto taps) {
+            constexpr int T = decltype(taps)::value, kO = 4 / T, kAhead = 6;   // (see conv_tiles)
+            const int o0 = q / T, ti = q % T;
+            // cy = 0: tap row 1 on row a; cy = 1: 0 on row a + 1, then 2 on row a
+            const int iy = T == 4 ? ti >> 1 : cy ? ti : 0, ix = T == 4 ? ti & 1 : cx ? ti : 0;
             const int i = cy ? 2 * iy : 1, j = cx ? 2 * ix : 1;
-            const float* gg = gp + (cy && !iy ? PG : 0) + (cx && !ix ? 1 : 0);
-            const float* ww = wp + (i * 3 + j) * kCh * kWP;
+            const float* gp = g + o0 * LG + OG + (ya + a + (cy && !iy)) * PG + b + (cx && !ix);
+            const float* wp = w + (c * 9 + i * 3 + j) * kWP;
+            const float* wo[2 * T];   // outputs below 8 of this lane
 #pragma unroll
-            for (int os = 0; os < kS; ++os) {
-                a_[os] = ww[4 * os];
-                b_[os] = gg[4 * os * LG];
+            for (int v = 0; v < 2 * T; ++v) wo[v] = wp + weight_col(o0 + kO * v, c);
+            float av[kAhead + 1], bv[kAhead + 1];
+            auto read = [&](int os) {
+                av[os % (kAhead + 1)] = wo[os % (2 * T)][8 * (os / (2 * T))];
+                bv[os % (kAhead + 1)] = gp[kO * os * LG];
+            };
+#pragma unroll
+            for (int os = 0; os < kAhead; ++os) read(os);
+#pragma unroll
+            for (int os = 0; os < 8 * T; ++os) {
+                if (os + kAhead < 8 * T) read(os + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
+                acc = mfma4(av[os % (kAhead + 1)], bv[os % (kAhead + 1)], acc);
+                __builtin_amdgcn_sched_barrier(0);
             }
         };
-        read(0, av, bv);
-        for (int k = 0; k < taps; ++k) {   // the next tap's operands are read ahead
-            read(min(k + 1, taps - 1), an, bn);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int os = 0; os < kS; ++os) acc = mfma4(av[os], bv[os], acc);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int os = 0; os < kS; ++os) {
-                av[os] = an[os];
-                bv[os] = bn[os];
-            }
-        }
+        if (k == 0) run(std::integral_constant<int, 4>{});
+        else if (k == 3) run(std::integral_constant<int, 1>{});
+        else run(std::integral_constant<int, 2>{});
         if (p < np) {
             const int y = 2 * (ya + a) + cy - y0, x = 2 * b + cx;
 #pragma unroll
@@ -359,6 +400,63 @@ SFOC_DEV void store_bgrad(const float* g, int rows, int cols, float* __restrict_
     if (k == 0) part[o] = add ? part[o] + s : s;
 }
 
+// A chunk of fc1's weights: loaded along the inputs into registers, then rounded
+// into fw (zero past the last input).
+SFOC_DEV void load_fc(const float* __restrict__ th, int chunk, float (&v)[kFcRegs]) {
+    const int t = tid_here(), k0 = chunk * kFcRows + t % kLanes;
+    const float* p = th + kF1 + t / kLanes * kFcIn;
+#pragma unroll
+    for (int i = 0; i < kFcRegs; ++i) {
+        const int k = k0 + i * kLanes;
+        v[i] = p[min(k, kFcIn - 1)];
+        v[i] = k < kFcIn ? v[i] : 0.f;
+    }
+}
+SFOC_DEV void stage_fc(const float (&v)[kFcRegs], float4* fw) {
+    const int t = tid_here(), k0 = t % kLanes;
+    float* p = reinterpret_cast<float*>(fw + k0 / 4 * kFcPitch + t / kLanes) + k0 % 4;
+#pragma unroll
+    for (int i = 0; i < kFcRegs; ++i) p[i * (kLanes / 4) * (kFcPitch * 4)] = bf16_round(v[i]);
+}
+// The chunk's inputs x added to h, output o's sum, in order; the operands are read
+// as far ahead as a wave can count (see conv_tiles).  The first operands' places
+// in LDS are opaque to the compiler, so that the reads of a round share a base
+// register each instead of costing an address add.
+SFOC_DEV float fc_chunk(const float4* lds, const float4* fw, const float* x, int o, float h) {
+    constexpr int kQuads = kFcRows / 4, kSlots = 8;
+    static_assert(kQuads % kSlots == 0, "whole rounds");
+    int wi = (int)(fw - lds) + o, xi = (int)(reinterpret_cast<const float4*>(x) - lds);
+    asm volatile("" : "+v"(wi), "+v"(xi));
+    const float4* wq = lds + wi;
+    const float4* xq = lds + xi;
+    float4 w[kSlots], v[kSlots];
+    auto read = [&](int q, int slot) {
+        w[slot] = wq[q * kFcPitch];
+        v[slot] = xq[q];
+    };
+    auto add = [&](int slot) {
+        __builtin_amdgcn_sched_barrier(0);
+        h = fmaf(w[slot].x, v[slot].x, h);
+        h = fmaf(w[slot].y, v[slot].y, h);
+        h = fmaf(w[slot].z, v[slot].z, h);
+        h = fmaf(w[slot].w, v[slot].w, h);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int u = 0; u + 1 < kSlots; ++u) read(u, u);
+#pragma unroll 1
+    for (int q = 0; q + kSlots < kQuads; q += kSlots)
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u) {
+            read(q + u + kSlots - 1, (u + kSlots - 1) % kSlots);
+            add(u);
+        }
+    read(kQuads - 1, kSlots - 1);
+#pragma unroll
+    for (int u = 0; u < kSlots; ++u) add(u);
+    return h;
+}
+
 // ---- loss and its gradient w.r.t. the outputs -------------------------------
 SFOC_DEV float sigmoidf_(float l) {
     const float e = __expf(-fabsf(l));
@@ -408,6 +506,12 @@ __global__ __launch_bounds__(kNetNT, 2) void net_kernel(const NetArgs A) {
     const int t = threadIdx.x, lane = t & 63;
     const float* __restrict__ th = A.th;
     if (t < 9 * kCh) S.w1[(t % 9) * kCh + t / 9] = bf16_round(th[kW1 + t]);
+    if (t < kCh) {
+        S.bias[t] = th[kB2 + t];
+        S.bias[kCh + t] = th[kB3 + t];
+        S.bias[2 * kCh + t] = th[kB4 + t];
+    }
+    if (t < 3 * kCh) S.f2[t] = bf16_round(th[kF2 + t]);
     for (int b = blockIdx.x; b < A.n; b += gridDim.x) {
         const bool add = b != (int)blockIdx.x;   // later samples add to the partials
         __syncthreads();
@@ -418,8 +522,8 @@ __global__ __launch_bounds__(kNetNT, 2) void net_kernel(const NetArgs A) {
             S.crop[e] = y >= 0 && y < kS0 && x >= 0 && x < kS0 ? crop[y * kS0 + x] : 0.f;
         }
         for (int e = t; e < kCh * kL2; e += kNetNT) S.a2[e] = 0.f;
-        if (t < kNStat) S.stats[t] = A.stats[(size_t)b * kNStat + t];
-        float wr[kWRegs];
+        const float stat = A.stats[(size_t)b * kNStat + min(t, kNStat - 1)];
+        float wr[kWRegs], fr[kFcRegs];
         load_weights(th + kW2, wr);
         stage_weights(wr, S.w);
         load_weights(th + kW3, wr);
@@ -429,46 +533,52 @@ __global__ __launch_bounds__(kNetNT, 2) void net_kernel(const NetArgs A) {
             const int r0 = band * kBandRows, rows = min(kBandRows, kS2 - r0);
             conv1_band(S, th, 2 * r0 - 1);
             __syncthreads();
-            conv_tiles<kS2, kL1, kP1, kL2, kP2, kP2 + 1, 2>(S.a1, S.w, th + kB2, S.a2 + r0 * kP2, rows);
+            conv_tiles<kS2, kL1, kP1, kL2, kP2, kP2 + 1, 2>(S.a1, S.w, S.bias, S.a2 + r0 * kP2, rows);
             __syncthreads();
         }
         for (int e = t; e < kCh * kL3; e += kNetNT) S.a3[e] = 0.f;
+        if (t < kFcPad - kFlat) S.a4[kFlat + t] = t < kNStat ? stat : 0.f;
         stage_weights(wr, S.w);
         load_weights(th + kW4, wr);
+        load_fc(th, 0, fr);
         __syncthreads();
-        conv_tiles<kS3, kL2, kP2, kL3, kP3, kP3 + 1, 1>(S.a2, S.w, th + kB3, S.a3, kS3);
+        conv_tiles<kS3, kL2, kP2, kL3, kP3, kP3 + 1, 1>(S.a2, S.w, S.bias + kCh, S.a3, kS3);
         __syncthreads();
         stage_weights(wr, S.w);
+        stage_fc(fr, S.fw);
         if (TRAIN) load_weights(th + kW3, wr);
+        load_fc(th, 1, fr);
         __syncthreads();
-        conv_tiles<kS4, kL3, kP3, kL4, kS4, 0, 1>(S.a3, S.w, th + kB4, S.a4, kS4);
+        conv_tiles<kS4, kL3, kP3, kL4, kS4, 0, 1>(S.a3, S.w, S.bias + 2 * kCh, S.a4, kS4);
         __syncthreads();
-        // fc1: 16 lanes an output, then fc2
+        // fc1 (lane o of the first wave output o), then fc2 (lane q output q)
         {
-            const int o = t / 16, k0 = t % 16;
-            const float* w = th + kF1 + o * kFcIn;
-            float s = 0.f;
-#pragma unroll 10
-            for (int k = k0; k < kFlat; k += 16) s = fmaf(bf16_round(w[k]), S.a4[k], s);
-            if (k0 < kNStat) s = fmaf(bf16_round(w[kFlat + k0]), S.stats[k0], s);
-#pragma unroll
-            for (int d = 1; d < 16; d <<= 1) s += __shfl_xor(s, d, 64);
-            if (k0 == 0) S.h1[o] = fmaxf(s + th[kC1 + o], 0.f);
+            float h = t < kCh ? th[kC1 + t] : 0.f;
+            for (int chunk = 0; chunk < kFcChunks; ++chunk) {
+                if (chunk) {
+                    stage_fc(fr, S.fw);
+                    if (chunk + 1 < kFcChunks) load_fc(th, chunk + 1, fr);
+                    __syncthreads();
+                }
+                if (t < kCh) h = fc_chunk(lds_raw, S.fw, S.a4 + chunk * kFcRows, t, h);
+                if (chunk + 1 < kFcChunks) __syncthreads();
+            }
+            if (t < kCh) S.h1[t] = fmaxf(h, 0.f);
         }
-        __syncthreads();
-        if (t < 64) {   // fc2 in the first wave
+        wave_order();   // fc2 reads what lanes of its own wave wrote
+        if (t < 64) {
+            const int ql = min(lane, 2);
+            float v = th[kC2 + ql];
+#pragma unroll
+            for (int o = 0; o < kCh; ++o) v = fmaf(S.f2[ql * kCh + o], S.h1[o], v);
             float s[3];
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                s[q] = lane < kCh ? bf16_round(th[kF2 + q * kCh + lane]) * S.h1[lane] : 0.f;
-#pragma unroll
-                for (int d = 1; d < 32; d <<= 1) s[q] += __shfl_xor(s[q], d, 64);
-            }
+            for (int q = 0; q < 3; ++q) s[q] = __shfl(v, q, 64);
             if (lane == 0) {
                 float o[3];
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
-                    o[q] = s[q] + th[kC2 + q];
+                    o[q] = s[q];
                     if (A.out) A.out[(size_t)b * 3 + q] = o[q];
                 }
                 if constexpr (!TRAIN) {
@@ -494,7 +604,7 @@ __global__ __launch_bounds__(kNetNT, 2) void net_kernel(const NetArgs A) {
             if (t < kCh) {
                 float g = 0.f;
 #pragma unroll
-                for (int q = 0; q < 3; ++q) g = fmaf(bf16_round(th[kF2 + q * kCh + t]), S.dout[q], g);
+                for (int q = 0; q < 3; ++q) g = fmaf(S.f2[q * kCh + t], S.dout[q], g);
                 const float h = S.h1[t], d = h > 0.f ? g : 0.f;
                 S.dh1[t] = d;
                 A.h1[(size_t)b * kCh + t] = h;
