@@ -58,7 +58,7 @@ struct MatchArgs {
     float* rst = nullptr;
     double* tsum = nullptr;
     // Spread form of the split form (spec set): per (IP, channel) the spectrum
-    // product, the factors of its two packed self bins, and the template sums.
+    // product and the factors of its two packed self bins; per IP the template sums.
     float2* spec = nullptr;
     float2* spec_self = nullptr;
     double* spec_sum = nullptr;

@@ -470,6 +470,58 @@ SFOC_DEV void join_packed(float2 (&u)[NB], float2 (&v)[NB], int j) {
 }
 
 // ---- row stage: real rows -> half spectra -------------------------------
+// Samples n1 + NB n2, n2 < NV, of row pair p, taken as one complex row, of an
+// nrows x ncols window of one descriptor plane.  Loads at 32-bit byte offsets
+// from the plane (a plane holds < 2^30 elements); sample n2 lies NB * n2
+// elements further on, a constant offset the load instruction encodes.  The
+// window lies inside the image; a missing second row re-reads the first (then
+// zeroed).  Where the samples end inside the NV blocks, columns are clamped into
+// the window and the samples beyond it zeroed.
+template <int L, int DT, int NV>
+SFOC_DEV void load_pair(const void* __restrict__ plane, int pitch, int y0, int x0, int nrows, int ncols, int p, int n1,
+                        float2 (&x)[MatchCfg<L>::NA]) {
+    using C = MatchCfg<L>;
+    constexpr int ES = DT == 0 ? 4 : 2;
+    const bool full = ncols == NV * C::NB, odd = nrows & 1;
+    const char* base = static_cast<const char*>(plane);
+    const bool two = 2 * p + 1 < nrows;
+    const uint32_t oa = (uint32_t)((y0 + 2 * p) * pitch + x0);
+    const uint32_t ob = oa + (two ? (uint32_t)pitch : 0u);
+    if (full) {
+        const char* ra = base + (size_t)(oa + n1) * ES;
+        const char* rb = base + (size_t)(ob + n1) * ES;
+#pragma unroll
+        for (int n2 = 0; n2 < NV; ++n2) x[n2] = make_float2(ldd<DT>(ra, C::NB * n2), ldd<DT>(rb, C::NB * n2));
+    } else {
+#pragma unroll
+        for (int n2 = 0; n2 < NV; ++n2) {
+            const uint32_t c = (uint32_t)min(n1 + C::NB * n2, ncols - 1);
+            x[n2] = make_float2(ldd<DT>(base + (size_t)(oa + c) * ES, 0), ldd<DT>(base + (size_t)(ob + c) * ES, 0));
+        }
+#pragma unroll
+        for (int n2 = 0; n2 < NV; ++n2)
+            if (n1 + C::NB * n2 >= ncols) x[n2] = make_float2(0.f, 0.f);
+    }
+    if (odd) {
+#pragma unroll
+        for (int n2 = 0; n2 < NV; ++n2) x[n2].y = two ? x[n2].y : 0.f;
+    }
+}
+
+// The sum and sum of squares of a pair's samples join s1, s2.
+template <int NV, int NA>
+SFOC_DEV void add_pair(const float2 (&x)[NA], double& s1, double& s2) {
+    double a = 0.0, q = 0.0;
+#pragma unroll
+    for (int n2 = 0; n2 < NV; ++n2) {
+        const double dr = x[n2].x, di = x[n2].y;
+        a += dr + di;
+        q += dr * dr + di * di;
+    }
+    s1 += a;
+    s2 += q;
+}
+
 // Pass A of rows [0, nrows) x columns [0, ncols) of one descriptor plane,
 // zero padded to L: of each row pair, taken as one complex row, element n1's
 // samples n1 + NB n2, n2 < NV, are transformed (ncols <= NV * NB; the others
@@ -479,53 +531,13 @@ template <int L, int DT, int NV, bool SUMS>
 SFOC_DEV void row_pass_a(const void* __restrict__ plane, int pitch, int y0, int x0, int nrows, int ncols,
                          float2* buf, const float2* tw, double& s1, double& s2) {
     using C = MatchCfg<L>;
-    constexpr int ES = DT == 0 ? 4 : 2;
     const int tid = tid_local();
     const int npair = (nrows + 1) / 2;
-    // Loads at 32-bit byte offsets from the plane (a plane holds < 2^30
-    // elements); sample n2 lies NB * n2 elements further on, a constant
-    // offset the load instruction encodes.  The window lies inside the image;
-    // a missing second row re-reads the first (then zeroed).  Where the
-    // samples end inside the NV blocks, columns are clamped into the window
-    // and the samples beyond it zeroed.
-    const bool full = ncols == NV * C::NB, odd = nrows & 1;
     auto load = [&](int p, int n1, float2(&x)[C::NA]) {
-        const char* base = static_cast<const char*>(plane);
-        const bool two = 2 * p + 1 < nrows;
-        const uint32_t oa = (uint32_t)((y0 + 2 * p) * pitch + x0);
-        const uint32_t ob = oa + (two ? (uint32_t)pitch : 0u);
-        if (full) {
-            const char* ra = base + (size_t)(oa + n1) * ES;
-            const char* rb = base + (size_t)(ob + n1) * ES;
-#pragma unroll
-            for (int n2 = 0; n2 < NV; ++n2) x[n2] = make_float2(ldd<DT>(ra, C::NB * n2), ldd<DT>(rb, C::NB * n2));
-        } else {
-#pragma unroll
-            for (int n2 = 0; n2 < NV; ++n2) {
-                const uint32_t c = (uint32_t)min(n1 + C::NB * n2, ncols - 1);
-                x[n2] = make_float2(ldd<DT>(base + (size_t)(oa + c) * ES, 0), ldd<DT>(base + (size_t)(ob + c) * ES, 0));
-            }
-#pragma unroll
-            for (int n2 = 0; n2 < NV; ++n2)
-                if (n1 + C::NB * n2 >= ncols) x[n2] = make_float2(0.f, 0.f);
-        }
-        if (odd) {
-#pragma unroll
-            for (int n2 = 0; n2 < NV; ++n2) x[n2].y = two ? x[n2].y : 0.f;
-        }
+        load_pair<L, DT, NV>(plane, pitch, y0, x0, nrows, ncols, p, n1, x);
     };
     auto finish = [&](int p, int n1, float2(&x)[C::NA]) {
-        if constexpr (SUMS) {
-            double a = 0.0, q = 0.0;
-#pragma unroll
-            for (int n2 = 0; n2 < NV; ++n2) {
-                const double dr = x[n2].x, di = x[n2].y;
-                a += dr + di;
-                q += dr * dr + di * di;
-            }
-            s1 += a;
-            s2 += q;
-        }
+        if constexpr (SUMS) add_pair<NV>(x, s1, s2);
         dftn<C::NA, DT == 2 ? kFwdF16 : kFwd, NV>(x);
         float2* reg = buf + C::row(2 * p);
         const float2* w = tw + n1;
@@ -684,34 +696,40 @@ SFOC_DEV void col_pass_b(const float2* buf, float2 (&u)[MatchCfg<L>::NB], float2
     dftn<C::NB, INV ? kInvCol : kFwd>(v);
 }
 
+// f(integral_constant NV) for the blocks of NB samples that a window of `side`
+// rows or columns has: half, three quarters or all of the NA (HALF: half is one
+// of the choices).
+template <int L, bool HALF, typename F>
+SFOC_DEV void by_extent(int side, F f) {
+    using C = MatchCfg<L>;
+    constexpr std::integral_constant<int, C::NA / 2> half{};
+    constexpr std::integral_constant<int, C::NA * 3 / 4> most{};
+    constexpr std::integral_constant<int, C::NA> all{};
+    if (HALF && side <= half.value * C::NB) f(half);
+    else if (side <= most.value * C::NB) f(most);
+    else f(all);
+}
+
 // Forward 2-D transform of an nrows x ncols window of one plane into buf and
 // this thread's bins (u, v).  Windows of at most half or three quarters of
-// the side skip the samples that are zero by their extent (HALF: half is one
-// of the choices).
+// the side skip the samples that are zero by their extent.
 template <int L, int DT, bool HALF, bool SUMS>
 SFOC_DEV void forward_2d(const void* plane, int pitch, int y0, int x0, int nrows, int ncols, float2* buf,
                          const float2* tw, double& s1, double& s2, float2 (&u)[MatchCfg<L>::NB],
                          float2 (&v)[MatchCfg<L>::NB]) {
     using C = MatchCfg<L>;
-    const int side = max(nrows, ncols), nvalid = 2 * ((nrows + 1) / 2);
+    const int nvalid = 2 * ((nrows + 1) / 2);
     auto stages = [&](auto nv) {
         constexpr int NV = decltype(nv)::value;
         row_pass_a<L, DT, NV, SUMS>(plane, pitch, y0, x0, nrows, ncols, buf, tw, s1, s2);
     };
     auto columns = [&](auto nv) { col_pass_a<L, false, decltype(nv)::value>(buf, tw, nvalid); };
-    constexpr std::integral_constant<int, C::NA / 2> half{};
-    constexpr std::integral_constant<int, C::NA * 3 / 4> most{};
-    constexpr std::integral_constant<int, C::NA> all{};
     stage_fence();
-    if (HALF && side <= half.value * C::NB) stages(half);
-    else if (side <= most.value * C::NB) stages(most);
-    else stages(all);
+    by_extent<L, HALF>(max(nrows, ncols), stages);
     stage_fence();
     row_pass_b<L>(nrows, buf);
     stage_fence();
-    if (HALF && side <= half.value * C::NB) columns(half);
-    else if (side <= most.value * C::NB) columns(most);
-    else columns(all);
+    by_extent<L, HALF>(max(nrows, ncols), columns);
     col_pass_b<L, false>(buf, u, v);
 }
 
@@ -911,10 +929,11 @@ SFOC_DEV void ncc_peak(const MatchArgs& A, int i, int slot, int u0, int v0, int 
 }
 
 // The spectra of channel h: the search window's (rows sy.., columns sx.., Mu x
-// Mv) into xsp, then the template's into yt; the template's sums join s1, s2.
+// Mv) into xsp, then the template's into yt; the template's sums join s1, s2
+// (SUMS).
 // The search window comes first (only the running sum is live during its
 // larger row stage), its spectrum kept in registers.
-template <int L, int DT>
+template <int L, int DT, bool SUMS>
 SFOC_DEV void channel_spectra(const MatchArgs& A, int h, int64_t sy, int64_t sx, int Mu, int Mv, int64_t ty,
                               int64_t tx, const float2* tw, float2* buf, double& s1, double& s2,
                               float2 (&xsp)[MatchCfg<L>::BINS], float2 (&u)[MatchCfg<L>::NB],
@@ -932,7 +951,7 @@ SFOC_DEV void channel_spectra(const MatchArgs& A, int h, int64_t sy, int64_t sx,
         xsp[C::NB + q] = v[q];
     }
     __syncthreads();
-    forward_2d<L, DT, true, true>(elem_ptr<DT>(A.desc_sen, h * plane_s), (int)A.Ws, (int)ty, (int)tx, m, m, buf, tw,
+    forward_2d<L, DT, true, SUMS>(elem_ptr<DT>(A.desc_sen, h * plane_s), (int)A.Ws, (int)ty, (int)tx, m, m, buf, tw,
                                   s1, s2, u, v);
     if (cc == 0) separate_packed<C::NB>(u, v, j);
 }
@@ -1119,7 +1138,7 @@ SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const floa
     float2 xsp[C::BINS];   // search-window spectrum of the current channel
     for (int h = 0; h < A.z; ++h) {
         float2 u[C::NB], v[C::NB];
-        channel_spectra<L, DT>(A, h, sy + u0, sx + v0, Mu, Mv, ty, tx, tw, buf, s1, s2, xsp, u, v);
+        channel_spectra<L, DT, true>(A, h, sy + u0, sx + v0, Mu, Mv, ty, tx, tw, buf, s1, s2, xsp, u, v);
         const bool self = tid_local() == 0;   // cc = j = 0: slots 0 and NB/2 hold (F_dc, F_nyq) as reals
 #pragma unroll
         for (int q = 0; q < C::BINS; ++q) {
@@ -1158,15 +1177,55 @@ SFOC_DEV void match_item(const MatchArgs& A, int i, int bq, int slot, const floa
 // Few interest points leave most CUs idle while a workgroup takes a point's
 // channels one after the other.  Spread form: a workgroup per (point, channel)
 // leaves the spectrum product, and a second launch sums the products in
-// channel order, as the fused form does.  The products of
-// the two packed self bins are fused into that sum, so their factors are left
-// instead.
+// channel order, as the fused form does.  The products of the two packed self
+// bins are fused into that sum, so their factors are left instead.  A further
+// workgroup per point takes the template sums, as the fused form's threads do
+// over all channels: both forms give the same bits.
 template <int L>
 struct Spread {
     using C = MatchCfg<L>;
     static constexpr size_t bins = (size_t)C::BINS * C::NT;   // complex values of a product
+    // (two sums an item are more than the two a point that are used)
     static constexpr size_t item_bytes = bins * sizeof(float2) + 4 * sizeof(float2) + 2 * sizeof(double);
 };
+
+constexpr int kTemplateRegs = 64;   // registers of loads in flight
+// This thread's part of the template sums over all channels, in the order of
+// the row passes of match_item: steps of a channel's rounds.  Several steps' loads
+// are issued first.
+template <int L, int DT>
+SFOC_DEV void template_sums(const MatchArgs& A, int64_t ty, int64_t tx, double& s1, double& s2) {
+    using C = MatchCfg<L>;
+    const int m = A.m, npair = (m + 1) / 2, steps = A.z * C::AR;
+    by_extent<L, true>(m, [&](auto nv) {
+        constexpr int NV = decltype(nv)::value, kU = kTemplateRegs / (2 * NV) > 1 ? kTemplateRegs / (2 * NV) : 1;
+        auto pair = [&](int e, int& n1) {   // the row pair and element of a step, as in row_pass_a
+            const int tid = tid_local(), rd = e % C::AR, q = C::WL ? rd * 64 + (tid & 63) : rd * C::NT + tid;
+            n1 = q % C::NB;
+            return C::WL ? (tid >> 6) * C::PW + C::pm_a(q / C::NB) : q / C::NB;
+        };
+#pragma unroll 1
+        for (int e0 = 0; e0 < steps; e0 += kU) {
+            float2 x[kU][C::NA];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int e = min(e0 + u, steps - 1);
+                int n1;
+                const int p = pair(e, n1);
+                if (p < npair)
+                    load_pair<L, DT, NV>(elem_ptr<DT>(A.desc_sen, e / C::AR * (A.Hs * A.Ws)), (int)A.Ws, (int)ty,
+                                         (int)tx, m, m, p, n1, x[u]);
+            }
+            stage_fence();
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                int n1;
+                if (e0 + u < steps && pair(e0 + u, n1) < npair) add_pair<NV>(x[u], s1, s2);
+            }
+        }
+    });
+}
+
 template <int L, int DT>
 __global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void match_spectra_kernel(const MatchArgs A) {
     using C = MatchCfg<L>;
@@ -1174,18 +1233,27 @@ __global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void 
     float2* tw = reinterpret_cast<float2*>(lds_raw);
     float2* buf = tw + L;
     double* red = reinterpret_cast<double*>(buf + C::buf_elems);
-    // each XCD takes a contiguous run of points (see match_kernel)
-    const int items = (int)gridDim.x, q8 = items / 8 * 8, id = (int)blockIdx.x;
-    const int k = id < q8 ? (id % 8) * (q8 / 8) + id / 8 : id;
-    const int i = k / A.z, h = k - i * A.z, m = A.m, r = A.r, M = m + 2 * r, t = threadIdx.x;
+    // the template sums' workgroups come first; of the others each XCD takes a
+    // contiguous run of points (see match_kernel)
+    const int items = A.n * A.z, q8 = items / 8 * 8, id = (int)blockIdx.x - A.n;
+    const bool sums = id < 0;
+    const int k = sums ? -1 : id < q8 ? (id % 8) * (q8 / 8) + id / 8 : id;
+    const int i = sums ? (int)blockIdx.x : k / A.z, h = k - i * A.z;
+    const int m = A.m, r = A.r, M = m + 2 * r, t = threadIdx.x;
     const int64_t ty = (int64_t)A.ips[2 * i] - m / 2, tx = (int64_t)A.ips[2 * i + 1] - m / 2;
     const int64_t sy = ty - r + (A.prior ? A.prior[2 * i] : 0), sx = tx - r + (A.prior ? A.prior[2 * i + 1] : 0);
     if (!in_image(ty, tx, m, m, A.Hs, A.Ws) || !in_image(sy, sx, M, M, A.Hr, A.Wr)) return;
+    double s1 = 0.0, s2 = 0.0;
+    if (sums) {
+        template_sums<L, DT>(A, ty, tx, s1, s2);
+        block_sum2<C::NT>(s1, s2, red);
+        if (t < 2) A.spec_sum[2 * i + t] = red[64 + t];
+        return;
+    }
     init_twiddles<L>(tw);
     __syncthreads();
-    double s1 = 0.0, s2 = 0.0;
     float2 xsp[C::BINS], u[C::NB], v[C::NB];
-    channel_spectra<L, DT>(A, h, sy, sx, M, M, ty, tx, tw, buf, s1, s2, xsp, u, v);
+    channel_spectra<L, DT, false>(A, h, sy, sx, M, M, ty, tx, tw, buf, s1, s2, xsp, u, v);
     float2* __restrict__ o = A.spec + (size_t)k * Spread<L>::bins + t;
     float2* __restrict__ f = A.spec_self + (size_t)k * 4;
 #pragma unroll
@@ -1196,11 +1264,6 @@ __global__ __launch_bounds__(MatchCfg<L>::NT, MatchCfg<L>::WAVES_PER_SIMD) void 
             f[q ? 2 : 0] = xsp[q];
             f[q ? 3 : 1] = yt;
         }
-    }
-    block_sum2<C::NT>(s1, s2, red);
-    if (t == 0) {
-        A.spec_sum[2 * k] = red[64];
-        A.spec_sum[2 * k + 1] = red[65];
     }
 }
 
@@ -1262,8 +1325,7 @@ __global__ __launch_bounds__(MatchCfg<L>::NT, (MatchCfg<L>::NT + 255) / 256) voi
         }
     }
     if (t < 2) {
-        double s = 0.0;
-        for (int h = 0; h < A.z; ++h) s += A.spec_sum[2 * ((size_t)i * A.z + h) + t];
+        const double s = A.spec_sum[2 * i + t];
         if constexpr (spread_peak<L>()) red[64 + t] = s;
         else A.tsum[2 * i + t] = s;
     }
@@ -2064,7 +2126,7 @@ static hipError_t launch_spectra(const MatchArgs& a, hipStream_t st) {
     auto kern = match_spectra_kernel<L, DT>;
     hipError_t e = ensure_dynamic_lds((const void*)kern, (int)C::lds_bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(a.n * a.z), dim3(C::NT), C::lds_bytes, st, a);
+    hipLaunchKernelGGL(kern, dim3(a.n * a.z + a.n), dim3(C::NT), C::lds_bytes, st, a);
     return hipGetLastError();
 }
 // The spread form's scratch (match_spread_bytes) in the arguments.
