@@ -619,8 +619,9 @@ int sfoc_rectify(const float* sen, int64_t Hs, int64_t Ws, int64_t lds, const do
  *  scores   their V (float32), same capacity, or NULL.            (output)
  *  counts   nby * nbx int32 per-block counts, or NULL.            (output)
  *  n_out    one int32: the number of interest points.             (output)
- * All device pointers; ws of sfoc_fast_workspace bytes (corner lists; at least a
- * float per pixel).
+ * All device pointers; ws of sfoc_fast_workspace bytes (a float per pixel and a
+ * mask word per 32 pixels of a row, which hold the lists of kept corners, and the
+ * blocks' records).
  * The result is exact and deterministic (no floating-point sums).
  * Limits: sides <= 2^20, H * W <= 2^32, per_block <= 32, nby * nbx <=
  * 65536 (SFOC_E_UNSUPPORTED beyond).  Errors: SFOC_E_INVALID_ARG (null

@@ -41,9 +41,6 @@ namespace fast {
 
 constexpr int kTS = 32, kHalo = 4, kIS = kTS + 2 * kHalo, kVS = kTS + 2;   // tile, image and strength sides
 constexpr int kNT = 256;
-// Corners a tile can keep: no two are neighbours (of two, the later one would
-// have to be larger and the earlier one not smaller), so one per 2 x 2 block.
-constexpr int kTileMax = kTS * kTS / 4;
 constexpr int kSelNT = 256, kMaxPer = 32, kMaxBlocks = 1 << 16;
 constexpr int kCompNT = 1024;
 
@@ -54,6 +51,16 @@ struct Region {
 struct Blocks {
     int nby, nbx, per;
 };
+
+// Corners kept: no two are neighbours (of two, the later one would have to be
+// larger and the earlier one not smaller), so one per 2 x 2 pixels of a tile, of
+// which those at the right and bottom border may be smaller than 32 x 32.  The
+// tiles' lists lie one after the other, row by row.
+inline SFOC_HOST_DEVICE int64_t list_start(int64_t H, int64_t W, int64_t ta, int64_t tb) {
+    const int64_t h = H - ta * kTS < kTS ? H - ta * kTS : kTS;
+    return ta * (kTS / 2) * ((W + 1) / 2) + (h + 1) / 2 * (kTS / 2) * tb;
+}
+inline int64_t list_total(int64_t H, int64_t W) { return (H + 1) / 2 * ((W + 1) / 2); }
 
 SFOC_DEV int bound(int lo, int n, int i, int nb) { return lo + (int)(((int64_t)i * n) / nb); }
 
@@ -194,6 +201,7 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
         }
         if (lane == 0) wcount[t >> 6] = before_lo + before_hi;
         __syncthreads();
+        float* const list = S + list_start(R.H, R.W, ty0 / kTS, tx0 / kTS);
         int base = 0;   // kept corners of the tile's rows before this thread's group
         for (int w = 0; w < kNT / 64; ++w) base += w < (t >> 6) ? wcount[w] : 0;
         if (lane & 32) base += before_lo;
@@ -201,7 +209,7 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
         for (int k = 0; k < kRows; ++k) {
             const int y = ty0 + a0 + k;
             const uint32_t bits = (uint32_t)(bal[k] >> (lane & 32));
-            if (keep[k]) S[(int64_t)blockIdx.x * kTileMax + base + __popc(bits & ((1u << c) - 1u))] = m[k + 1];
+            if (keep[k]) list[base + __popc(bits & ((1u << c) - 1u))] = m[k + 1];
             if (c == 0 && y < R.H) mask[(int64_t)y * mask_words + tx0 / kTS] = make_uint2(bits, (uint32_t)base);
             base += __popc(bits);
         }
@@ -257,7 +265,7 @@ __global__ __launch_bounds__(kSelNT) void select_kernel(const float* __restrict_
             if (!bits) continue;
             const int q = q0 + u * kSelNT;
             const int a = q / nw, wi = q - a * nw, xw = 32 * (w0 + wi);
-            const float* list = S + ((int64_t)((y0 + a) / kTS) * mask_words + w0 + wi) * kTileMax + m[u].y;
+            const float* list = S + list_start(R.H, R.W, (y0 + a) / kTS, w0 + wi) + m[u].y;
             while (bits) {
                 const int x = xw + __ffs(bits) - 1;
                 bits &= bits - 1u;
@@ -368,16 +376,20 @@ Layout layout(int64_t H, int64_t W, int nblocks, int per) {
         return at;
     };
     L.mask_words = (int)((W + kTS - 1) / kTS);
-    L.smap = take(sizeof(float) * kTileMax * (size_t)((H + kTS - 1) / kTS) * L.mask_words);
-    L.mask = take(sizeof(uint2) * (size_t)H * L.mask_words);
+    // (an image of six rows or columns or fewer has no region)
+    const bool any = H > 6 && W > 6;
+    L.smap = take(any ? sizeof(float) * (size_t)list_total(H, W) : 0);
+    L.mask = take(any ? sizeof(uint2) * (size_t)H * L.mask_words : 0);
     L.bips = take(sizeof(int32_t) * 2 * (size_t)nblocks * per);
     L.bsc = take(sizeof(float) * (size_t)nblocks * per);
     L.bcnt = take(sizeof(int32_t) * (size_t)nblocks);
-    // never less than a strength per pixel and a mask word per 32, which callers
-    // that size their workspace once may count on
+    // The size asked for is a strength per pixel and a mask word per 32, which
+    // callers may have stored: the lists and the wider words always fit (from
+    // seven rows and columns on, 4 bytes per 2 x 2 pixels and 8 per 32 pixels of a
+    // row are no more than 4 bytes per pixel and 4 per 32).
     const size_t map = align_up(sizeof(float) * (size_t)H * (size_t)W, 256) +
                        align_up(sizeof(uint32_t) * (size_t)H * L.mask_words, 256);
-    L.total = std::max(o, map + (o - L.bips));
+    L.total = map + (o - L.bips);
     return L;
 }
 
@@ -441,8 +453,10 @@ extern "C" int sfoc_detect_ips(const float* img, int64_t H, int64_t W, int64_t l
     hipStream_t st = (hipStream_t)stream;
     const int tiles_x = (int)((W + kTS - 1) / kTS), tiles_y = (int)((H + kTS - 1) / kTS);
     trace_begin(st, SFOC_K_FAST);
-    hipLaunchKernelGGL(strength_kernel, dim3(tiles_x * tiles_y), dim3(kNT), 0, st, img, ld, R, threshold, S, mask,
-                       L.mask_words, tiles_x);
+    // (without a region the blocks are empty and the selection reads nothing)
+    if (H - R.b > R.b && W - R.b > R.b)
+        hipLaunchKernelGGL(strength_kernel, dim3(tiles_x * tiles_y), dim3(kNT), 0, st, img, ld, R, threshold, S, mask,
+                           L.mask_words, tiles_x);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
         const int K = per_block <= 1 ? 1 : per_block <= 2 ? 2 : per_block <= 4 ? 4 : per_block <= 8 ? 8
