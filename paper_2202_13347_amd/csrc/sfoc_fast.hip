@@ -94,7 +94,7 @@ SFOC_DEV float max2(float a, float b) {
 // those likewise.  The arcs from k and k + 1, k even, share the eight pixels
 // k + 1 .. k + 8, four pairs: the larger of their two minima is
 // min(pairs, max(p[k], p[k + 9])), 36 instructions a polarity with the pairs
-// and the fold (16 arcs by three arcs of three: 40).
+// and the fold (16 arcs by three arcs of three: 40).  Finite pixels.
 SFOC_DEV float strength(const float* tile, int ty, int tx) {
     const float* nb = tile + (ty - 3) * kIS + (tx - 3);
     const float c = nb[3 * kIS + 3];
@@ -117,6 +117,29 @@ SFOC_DEV float strength(const float* tile, int ty, int tx) {
     return fmaxf(bright - c, c - dark);
 }
 
+// The same where a pixel of the tile is not finite: arc by arc, from the
+// differences, of which minima and maxima ignore a NaN.  (A NaN pixel, or inf -
+// inf, then counts neither for nor against an arc; in the form above it would be
+// ignored by a maximum of two arcs' ends and leave the smaller one.)
+SFOC_DEV float strength_any(const float* tile, int ty, int tx) {
+    const float* nb = tile + (ty - 3) * kIS + (tx - 3);
+    const float c = nb[3 * kIS + 3];
+    float u[16], v = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) u[i] = nb[(kCy[i] + 3) * kIS + kCx[i] + 3] - c;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        float lo = u[k], hi = u[k];
+#pragma unroll
+        for (int j = 1; j < 9; ++j) {
+            lo = fminf(lo, u[(k + j) & 15]);
+            hi = fmaxf(hi, u[(k + j) & 15]);
+        }
+        v = fmaxf(v, fmaxf(lo, -hi));
+    }
+    return v;
+}
+
 __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__ img, int64_t ld, Region R,
                                                        float thr, float* __restrict__ S,
                                                        uint2* __restrict__ mask, int mask_words, int tiles_x) {
@@ -124,6 +147,8 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
     __shared__ __align__(16) float tile[kIS * kIS];
     __shared__ float vs[kVS * kVS];
     __shared__ int wcount[kNT / 64];
+    __shared__ int wodd[kNT / 64];   // a wave loaded a pixel that is not finite
+    float zero = 0.f;                // the sum of the loaded pixels times zero
     const int t = threadIdx.x, lane = t & 63;
     const int ty0 = (blockIdx.x / tiles_x) * kTS, tx0 = (blockIdx.x % tiles_x) * kTS;
     {   // every load of the tile first, then the stores; pixels outside the
@@ -139,6 +164,8 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
             const int e1 = min(t + kNT, kQuads - 1);
             const float4 v0 = *reinterpret_cast<const float4*>(src + (int64_t)(t / kQ) * ld + 4 * (t % kQ));
             const float4 v1 = *reinterpret_cast<const float4*>(src + (int64_t)(e1 / kQ) * ld + 4 * (e1 % kQ));
+            zero = fmaf(v0.x, 0.f, fmaf(v0.y, 0.f, fmaf(v0.z, 0.f, v0.w * 0.f))) +
+                   fmaf(v1.x, 0.f, fmaf(v1.y, 0.f, fmaf(v1.z, 0.f, v1.w * 0.f)));
             reinterpret_cast<float4*>(tile)[t] = v0;
             if (t + kNT < kQuads) reinterpret_cast<float4*>(tile)[t + kNT] = v1;
         } else {
@@ -150,14 +177,22 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
                 v[k] = (y >= 0 && y < R.H && x >= 0 && x < R.W) ? img[(int64_t)y * ld + x] : 0.f;
             }
 #pragma unroll
-            for (int k = 0; k < kLoads; ++k)
+            for (int k = 0; k < kLoads; ++k) {
+                zero = fmaf(v[k], 0.f, zero);
                 if (t + k * kNT < kIS * kIS) tile[t + k * kNT] = v[k];
+            }
         }
     }
+    const uint64_t odd = __ballot(!(zero == 0.f));
+    if (lane == 0) wodd[t >> 6] = odd != 0;
     __syncthreads();
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < kNT / 64; ++w) any |= wodd[w];
+    const bool finite = __builtin_amdgcn_readfirstlane(any) == 0;
     // strengths of the tile and a 1-pixel ring; -inf outside the region (which
     // only tiles at its border reach)
-    if (ty0 - 1 >= R.b && tx0 - 1 >= R.b && ty0 + kTS < R.H - R.b && tx0 + kTS < R.W - R.b) {
+    if (finite && ty0 - 1 >= R.b && tx0 - 1 >= R.b && ty0 + kTS < R.H - R.b && tx0 + kTS < R.W - R.b) {
         for (int e = t; e < kVS * kVS; e += kNT) {
             const int a = e / kVS, c = e - a * kVS;
             vs[e] = strength(tile, a + kHalo - 1, c + kHalo - 1);
@@ -167,7 +202,9 @@ __global__ __launch_bounds__(kNT) void strength_kernel(const float* __restrict__
             const int a = e / kVS, c = e - a * kVS;
             const int y = ty0 - 1 + a, x = tx0 - 1 + c;
             const bool in = y >= R.b && y < R.H - R.b && x >= R.b && x < R.W - R.b;
-            vs[e] = in ? strength(tile, a + kHalo - 1, c + kHalo - 1) : -INFINITY;
+            vs[e] = !in ? -INFINITY
+                        : finite ? strength(tile, a + kHalo - 1, c + kHalo - 1)
+                                 : strength_any(tile, a + kHalo - 1, c + kHalo - 1);
         }
     }
     __syncthreads();
