@@ -243,55 +243,36 @@ SFOC_DEV void zero_tile_aggregates(const DescribeJob& J, int ty0, int tx0) {
     }
 }
 
-// The workgroup's job and tile; false where there is nothing to describe.
-// Workgroups are dealt to the eight XCDs in turn; renumbered so that each XCD
-// takes a contiguous run of tiles, whose overlapping input halos then meet in
-// one L2.
-__device__ __forceinline__ bool describe_tile(const DescribeJob& single, const DescribeJob* __restrict__ jobs,
-                            const int4* __restrict__ tiles, const uint8_t* __restrict__ tmask, DescribeJob& J, int& ty0,
-                            int& tx0) {
+// The workgroup's entry {job, tile row origin, tile column origin, what} of the
+// table, or of the image's tiles where there is none.  Workgroups are dealt to the
+// eight XCDs in turn; renumbered so that each XCD takes a contiguous run of tiles,
+// whose overlapping input halos then meet in one L2.
+__device__ __forceinline__ int4 tile_entry(const int4* __restrict__ tiles, const uint8_t* __restrict__ tmask) {
     const int nblk = (int)(gridDim.x * gridDim.y), q8 = nblk / 8 * 8;
     const int id = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     const int k = id < q8 ? (id % 8) * (q8 / 8) + id / 8 : id;
-    if (tiles) {
-        // entries: {job, tile row origin, tile column origin, what}; without
-        // a job table every entry is of `single`, and a negative job is an
-        // empty slot that the whole workgroup skips.  what = 1: a grid tile
-        // that nothing reads, whose integral-image aggregates are set to
-        // zero (the box sums over the tiles that are described stay exact);
-        // what = 2: a grid tile that is described if the mask marks it
-        const int4 e = tiles[k];
-        if (e.x < 0) return false;
-        J = jobs ? load_table(jobs, e.x) : single;
-        ty0 = e.y;
-        tx0 = e.z;
-        if (e.w == 1 || (e.w == 2 && !tmask[(ty0 / kTS) * ((J.W + kTS - 1) / kTS) + tx0 / kTS])) {
-            if (J.agg) zero_tile_aggregates(J, ty0, tx0);
-            return false;
-        }
-    } else {
-        J = single;
-        ty0 = (k / gridDim.x) * kTS;
-        tx0 = (k % gridDim.x) * kTS;
-        // a grid tile outside the mask is not described; with integral
-        // inputs its aggregates are set to zero
-        if (tmask && !tmask[(ty0 / kTS) * gridDim.x + tx0 / kTS]) {
-            if (J.agg) zero_tile_aggregates(J, ty0, tx0);
-            return false;
-        }
-    }
-    return true;
+    if (tiles) return tiles[k];
+    return make_int4(0, (int)(k / gridDim.x) * kTS, (int)(k % gridDim.x) * kTS, tmask ? 2 : 0);
+}
+// Without a job table every entry is of `single`, and a negative job is an empty
+// slot that the whole workgroup skips.  what = 1: a grid tile that nothing reads,
+// whose integral-image aggregates are set to zero (the box sums over the tiles that
+// are described stay exact); what = 2: a grid tile that is described if the mask
+// marks it.
+__device__ __forceinline__ bool tile_unread(const DescribeJob& J, const int4& e, const uint8_t* __restrict__ tmask) {
+    return e.w == 1 || (e.w == 2 && !tmask[(e.y / kTS) * ((J.W + kTS - 1) / kTS) + e.z / kTS]);
 }
 
 // The square input region of a tile (side `side`, top-left pixel (y0, x0),
-// reflect-101 borders) into simg (pitch P): eight rows' loads are issued
-// before any of their LDS stores.
+// reflect-101 borders) into simg (pitch P): kU rows' loads are issued before any
+// of their LDS stores.
+template <int kU>
 __device__ __forceinline__ void load_region(const DescribeJob& J, int y0, int x0, int side, float* simg, int P) {
     const float* __restrict__ img = J.img;
     const int t = threadIdx.x, H = J.H, W = J.W;
     const int64_t ld = J.ld;
     const bool inside = y0 >= 0 && x0 >= 0 && y0 + side <= H && x0 + side <= W;
-    constexpr int kRows = kNT / 64, kU = 8;
+    constexpr int kRows = kNT / 64;
     for (int b = t % 64; b < side; b += 64) {
         const int gx = inside ? x0 + b : reflect101(x0 + b, W);
         for (int a0 = t / 64; a0 < side; a0 += kRows * kU) {
@@ -477,9 +458,14 @@ __global__ __launch_bounds__(kNT, Z >= 32 ? 2 : 3) void describe_kernel(const De
                                                           int BSP, int ISX, int BPP, int IPP) {
     extern __shared__ float lds[];
     const int t = threadIdx.x;
-    DescribeJob J;
-    int ty0, tx0;
-    if (!describe_tile(single, jobs, tiles, tmask, J, ty0, tx0)) return;
+    const int4 e = tile_entry(tiles, tmask);
+    if (e.x < 0) return;
+    const DescribeJob J = jobs ? load_table(jobs, e.x) : single;
+    const int ty0 = e.y, tx0 = e.z;
+    if (tile_unread(J, e, tmask)) {
+        if (J.agg) zero_tile_aggregates(J, ty0, tx0);
+        return;
+    }
     const int Q = C.Q, R = C.R;
     const int nrun = BSP / kRun;
     float* simg = lds;
@@ -488,7 +474,7 @@ __global__ __launch_bounds__(kNT, Z >= 32 ? 2 : 3) void describe_kernel(const De
     const int BB = BSP * BPP;   // one basis / channel map
 
     // 1. input region (top-left at tile origin - Q - R)
-    load_region(J, ty0 - Q - R, tx0 - Q - R, ISX, simg, IPP);
+    load_region<4>(J, ty0 - Q - R, tx0 - Q - R, ISX, simg, IPP);
     __syncthreads();
 
     // 2. basis responses Gx, Gy, Gxx, Gyy, Gxy * I summed over sigma, held in
@@ -598,60 +584,64 @@ __global__ __launch_bounds__(kNT, Z >= 32 ? 2 : 3) void describe_kernel(const De
     float acc[Z][kRun];
     float* schan = sbas + 5 * BB;
     const int N = C.N, B = 2 * C.K + 1;
+    RunOut O;
+    init_run(O, J, C, ty0, tx0);
+    // (in a function of its own, by which the compiler addresses the maps with
+    // fewer instructions: 1024 x 1024, eight orientations of the first order 190 us
+    // without, 172 us with)
+    auto steer_smooth = [&](int lo, int hi) {
 #pragma unroll
-    for (int c0 = 0; c0 < Z; c0 += CG) {
-        // thread index laundered per group: keeps the group's LDS addresses
-        // from being hoisted (and kept live) across the whole channel loop.
-        int tl = t;
-        asm volatile("" : "+v"(tl));
-        const int obase = (tl / (kTS / kRun) + Q) * BPP + (tl % (kTS / kRun)) * kRun + Q;
-        for (int e = tl; e < BSr * BSr; e += kNT) {
-            const int a = e / BSr, b = e - a * BSr;
-            const int idx = a * BPP + b;
+        for (int c0 = lo; c0 < hi; c0 += CG) {
+            // thread index laundered per group: keeps the group's LDS addresses
+            // from being hoisted (and kept live) across the whole channel loop.
+            int tl = t;
+            asm volatile("" : "+v"(tl));
+            const int obase = (tl / (kTS / kRun) + Q) * BPP + (tl % (kTS / kRun)) * kRun + Q;
+            for (int e = tl; e < BSr * BSr; e += kNT) {
+                const int a = e / BSr, b = e - a * BSr;
+                const int idx = a * BPP + b;
+#pragma unroll
+                for (int cc = 0; cc < CG; ++cc) {
+                    const int c = c0 + cc;
+                    if (c < Z) {
+                        float v;   // (the order of each sum is spelled out: results do not move with the compiler)
+                        if (c < N) {
+                            v = fmaf(C.s1[c], sbas[BB + idx], C.c1[c] * sbas[idx]);
+                        } else {
+                            const int k = c - N;
+                            v = fmaf(C.sc2[k], sbas[4 * BB + idx],
+                                     fmaf(C.cc[k], sbas[2 * BB + idx], C.ss[k] * sbas[3 * BB + idx]));
+                        }
+                        if (C.rectify == SFOC_RECTIFY_ABS) v = fabsf(v);
+                        else if (C.rectify == SFOC_RECTIFY_RELU) v = fmaxf(v, 0.f);
+                        schan[cc * BB + idx] = v;
+                    }
+                }
+            }
+            __syncthreads();
 #pragma unroll
             for (int cc = 0; cc < CG; ++cc) {
                 const int c = c0 + cc;
                 if (c < Z) {
-                    float v;
-                    if (c < N) {
-                        v = C.c1[c] * sbas[idx] + C.s1[c] * sbas[BB + idx];
-                    } else {
-                        const int k = c - N;
-                        v = C.cc[k] * sbas[2 * BB + idx] + C.ss[k] * sbas[3 * BB + idx] +
-                            C.sc2[k] * sbas[4 * BB + idx];
+                    const float* w = (c < N) ? C.w1 : C.w2;
+                    const float* ch = schan + cc * BB + obase;
+#pragma unroll
+                    for (int j = 0; j < kRun; ++j) {
+                        float a = 0.f;
+                        for (int di = 0; di < C.ndil; ++di) {
+                            const int r = C.dil[di];
+                            for (int i = 0; i < B; ++i)
+                                for (int jj = 0; jj < B; ++jj)
+                                    a = fmaf(w[i * B + jj], ch[(i - C.K) * r * BPP + (jj - C.K) * r + j], a);
+                        }
+                        acc[c][j] = a;
                     }
-                    if (C.rectify == SFOC_RECTIFY_ABS) v = fabsf(v);
-                    else if (C.rectify == SFOC_RECTIFY_RELU) v = fmaxf(v, 0.f);
-                    schan[cc * BB + idx] = v;
                 }
             }
+            __syncthreads();
         }
-        __syncthreads();
-#pragma unroll
-        for (int cc = 0; cc < CG; ++cc) {
-            const int c = c0 + cc;
-            if (c < Z) {
-                const float* w = (c < N) ? C.w1 : C.w2;
-                const float* ch = schan + cc * BB + obase;
-#pragma unroll
-                for (int j = 0; j < kRun; ++j) {
-                    float a = 0.f;
-                    for (int di = 0; di < C.ndil; ++di) {
-                        const int r = C.dil[di];
-                        for (int i = 0; i < B; ++i)
-                            for (int jj = 0; jj < B; ++jj)
-                                a = fmaf(w[i * B + jj], ch[(i - C.K) * r * BPP + (jj - C.K) * r + j], a);
-                    }
-                    acc[c][j] = a;
-                }
-            }
-        }
-        __syncthreads();
-    }
-
-    // 4. (per order block) normalisation, rounding, store, channel sums.
-    RunOut O;
-    init_run(O, J, C, ty0, tx0);
+    };
+    steer_smooth(0, Z);
     emit_block<Z>(acc, 0, N, 0, J.desc, J.integ1 != nullptr, C, O);
     emit_block<Z>(acc, N, Z, 0, J.desc, J.integ1 != nullptr, C, O);
     if (J.integ1) emit_sums(J, O, ty0, tx0, reinterpret_cast<double*>(lds));
@@ -771,12 +761,17 @@ __global__ __launch_bounds__(kNT, N <= 8 ? 4 : 3) void describe_k1_kernel(const 
     extern __shared__ float lds[];
     const K1Args& A = *(const K1Args*)__builtin_amdgcn_kernarg_segment_ptr();
     const DescribeConsts& C = A.C;
-    DescribeJob J;
-    int ty0, tx0;
-    if (!describe_tile(A.single, A.jobs, A.tiles, A.tmask, J, ty0, tx0)) return;
+    const int4 e = tile_entry(A.tiles, A.tmask);
+    if (e.x < 0) return;
+    const DescribeJob J = A.jobs ? load_table(A.jobs, e.x) : A.single;
+    const int ty0 = e.y, tx0 = e.z;
+    if (tile_unread(J, e, A.tmask)) {
+        if (J.agg) zero_tile_aggregates(J, ty0, tx0);
+        return;
+    }
     const int t = threadIdx.x, R = C.R, side = kB + 2 * R, IPP = side | 1;
     float* srow = lds + side * IPP;
-    load_region(J, ty0 - 3 - R, tx0 - 3 - R, side, lds, IPP);
+    load_region<8>(J, ty0 - 3 - R, tx0 - 3 - R, side, lds, IPP);
     __syncthreads();
 
     // Gx, Gy, Gxx, Gyy, Gxy * I summed over sigma, held by the threads of the
