@@ -252,10 +252,12 @@ int sfoc_fastncc_match(const void* desc_sen, int64_t Hs, int64_t Ws,
  * on `stream` is ordered after the call.  Arguments as above; the
  * descriptors, integral images, the describe table of both images' tiles,
  * the match's R_ST surfaces and the reference tile mask live inside ws (see
- * sfoc_register_workspace).  For few IPs (up to 512 at 64 x 64 windows, 96 to
- * 128 at larger ones) the queried size includes up to 160 MB with which the
- * channels are matched side by side; a call with a workspace short of only
- * that takes the channels in turn, with the same result.  The CPs equal
+ * sfoc_register_workspace).  For few IPs and at least four channels (up to 512
+ * IPs whose search windows fit 64 x 64, 128 at 128 x 128, 96 above that, and no
+ * more than 160 MB hold) the queried size includes scratch with which the
+ * channels are matched side by side; a call with a workspace short of only that
+ * takes the channels in turn, with the same records and surfaces bit for bit.
+ * The CPs equal
  * those of sfoc_describe of both whole images followed by sfoc_fastncc_match
  * up to the float64 rounding of those box sums (bit for bit in every test).
  */
@@ -465,7 +467,9 @@ int64_t sfoc_sensed_tiles(const int32_t* ips, const int32_t* prior, int32_t n, i
  * stats) -> 32, ReLU; fc2 32 -> 3 = (validity logit, oy, ox).  Conv
  * weights are [out][in][3][3] then the bias [out]; fc weights [out][in]
  * then the bias.  Weights (not biases) enter every product rounded to
- * bfloat16 (round to nearest even); all sums are float32.
+ * bfloat16 (round to nearest even); all sums are float32.  A forward sum is one
+ * chain of fused multiply-adds from the bias: over input channels and then taps,
+ * or over the inputs.
  *
  * sfoc_head_forward: out (n x 3) for n samples.
  * sfoc_head_train_step: one step on a batch of n samples: forward, the
@@ -612,7 +616,9 @@ int sfoc_rectify(const float* sen, int64_t Hs, int64_t Ws, int64_t lds, const do
  *  - The region is split into nby x nbx blocks at rows
  *    b + floor(i * (H - 2b) / nby) (columns likewise); from each block the
  *    per_block kept corners of largest V, ties to the smaller raster index.
- *  img      H x W float32, pitch ld, finite values.               (input)
+ *  img      H x W float32, pitch ld, finite values.  (At pixels that are not,
+ *           a difference that is NaN counts neither for nor against an arc;
+ *           a NaN pixel is no corner.)                            (input)
  *  ips      (row, col) int32 pairs, capacity nby * nbx * per_block; the
  *           first *n_out are written, in block order (row-major), within
  *           a block by decreasing V.                               (output)
@@ -649,7 +655,7 @@ int sfoc_detect_ips(const float* img, int64_t H, int64_t W, int64_t ld, float th
 #define SFOC_K_PEAK         4
 #define SFOC_K_HEAD_FEAT    5
 #define SFOC_K_HEAD_FWD     6
-#define SFOC_K_HEAD_BWD     7
+#define SFOC_K_HEAD_BWD     7   /* a training step's forward and backward pass, one launch */
 #define SFOC_K_HEAD_ADAM    8
 #define SFOC_K_RANSAC       9
 #define SFOC_K_RECTIFY     10

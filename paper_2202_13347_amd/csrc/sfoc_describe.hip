@@ -745,8 +745,8 @@ __device__ __forceinline__ void sigma_pass_use(const float* simg, int IPP, float
 // R = 9, 128 VGPRs for N <= 8).
 // 2048 x 2048, FP32 with integral inputs: 250 us with the basis read from LDS
 // by a loop over map elements (23 issue slots a channel and element), runs of
-// four rows and two or four row-pass phases a sigma; 195 us so (85.8 M wave
-// instructions, 74 % of the issue slots).
+// four rows and two or four row-pass phases a sigma; 188 us so (86.0 M wave
+// instructions, three quarters of the issue slots).
 // The arguments are read where the launch put them: as a by-value parameter
 // with this many readers the compiler would copy them to scratch memory.
 struct K1Args {

@@ -925,7 +925,7 @@ __global__ __launch_bounds__(kFeatNT) void features_kernel(const FeatArgs A) {
 
 // ---- workspace ------------------------------------------------------------
 struct Layout {
-    size_t out;                                              // inference
+    size_t out;   // (not used: an inference's workspace keeps its size, and a short or null one is refused)
     size_t x4, h1, dh1, dout, loss, part, grad, total;       // training
     int parts;
 };
