@@ -53,9 +53,10 @@ SFOC_DEV int tid_local() {
 // So every kernel built from these pieces rounds alike (the pair call, its
 // split and spread forms, the plan's kernels), and a change of the code around
 // them does not move a result.  The choices are those that the compiler had made
-// before they were written out: the same bits at sides 128, 160 and 192; at side
-// 64, with templates of at most 32, 1 in 5000 values of a surface (BF16: 2 in
-// 100) differs from then by a few units in the last place, as far from float64.
+// before they were written out, so the bits are the same at every side.  At
+// side 64 that takes two forms, by the half of its pass that a task lies in
+// (dft8's hi): 64-side matches from bfloat16 take 0.5 % longer for it (4000 IPs,
+// m 32, r 16: 471 to 473 us), others as long.
 //   form & 2: the real part fuses the imaginary product, form & 1: the
 //   imaginary part fuses a.x * b.y.
 SFOC_DEV float2 cmulf(float2 a, float2 b, int form) {
@@ -70,10 +71,16 @@ SFOC_DEV float2 cmul_inv(float2 a, float2 w) { return cmulf(a, make_float2(w.x, 
 SFOC_DEV float2 cmulc(float2 a, float2 b) {  // a * conj(b), the spectrum product
     return make_float2(fmaf(a.y, b.y, a.x * b.x), fmaf(a.y, b.x, -(a.x * b.y)));
 }
+// a * b, every product rounded before the sum.
+SFOC_DEV float2 cmulr(float2 a, float2 b) {
+#pragma clang fp contract(off)
+    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
 // The passes a codelet serves: forward rows and columns, inverse columns,
 // inverse rows; by themselves, pass A of the rows from float16 descriptors
-// and pass A of the inverse columns with an 8-point codelet.
-constexpr int kFwd = 0, kInvCol = 1, kInvRow = 2, kFwdF16 = 3, kInvColA8 = 4;
+// and, with an 8-point codelet, pass A of the inverse columns and of the rows
+// from bfloat16 descriptors.
+constexpr int kFwd = 0, kInvCol = 1, kInvRow = 2, kFwdF16 = 3, kInvColA8 = 4, kFwdBf16A8 = 5;
 SFOC_DEV float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 // c ? a : b per component (a select of two array elements written this way
 // stays in registers; as one conditional expression the compiler may turn
@@ -144,21 +151,29 @@ SFOC_DEV void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
 }
 
 // x[k] <- sum_n x[n] W_8^(nk), W_8 = exp(-+2 pi i / 8); 2 x 4 split.  Only
-// the samples n < NV are read, the others count as zero.
+// the samples n < NV are read, the others count as zero.  hi: the task is of
+// the upper half of pass A's row pairs or columns (kFwdBf16A8, kInvColA8 only;
+// the same over a wave).
 template <int CTX, int NV = 8>
-SFOC_DEV void dft8(float2 (&x)[8]) {
+SFOC_DEV void dft8(float2 (&x)[8], bool hi = false) {
     static_assert(NV >= 2 && NV <= 8, "both halves have a sample");
-    constexpr bool INV = CTX != kFwd && CTX != kFwdF16;
-    constexpr int kF[5][2] = {{2, 2}, {2, 1}, {2, 1}, {2, 2}, {1, 1}};   // product forms of b1 and b3
+    constexpr bool INV = CTX == kInvCol || CTX == kInvRow || CTX == kInvColA8;
+    constexpr int kF[6][2] = {{2, 2}, {2, 1}, {2, 1}, {2, 2}, {1, 1}, {2, 2}};   // product forms of b1 and b3
     float2 a0 = x[0], a1 = x[2], a2 = x[4], a3 = x[6];
     float2 b0 = x[1], b1 = x[3], b2 = x[5], b3 = x[7];
     dft4<INV, (NV + 1) / 2>(a0, a1, a2, a3);
     dft4<INV, NV / 2>(b0, b1, b2, b3);
     const float h = 0.70710678118654752f;
     const float sg = INV ? 1.f : -1.f;
-    b1 = cmulf(b1, make_float2(h, sg * h), kF[CTX][0]);
+    const float2 w1 = make_float2(h, sg * h), w3 = make_float2(-h, sg * h);
     b2 = mul_mi<INV>(b2);
-    b3 = cmulf(b3, make_float2(-h, sg * h), kF[CTX][1]);
+    if (CTX == kFwdBf16A8 && hi) {
+        b1 = cmulr(b1, w1);
+        b3 = cmulr(b3, w3);
+    } else {
+        b1 = CTX == kInvColA8 && hi ? cmulf(b1, w1, 2) : cmulf(b1, w1, kF[CTX][0]);
+        b3 = cmulf(b3, w3, kF[CTX][1]);
+    }
     x[0] = cadd(a0, b0);
     x[4] = csub(a0, b0);
     x[1] = cadd(a1, b1);
@@ -328,11 +343,12 @@ SFOC_DEV void dft12(float2 (&x)[12]) {
     }
 }
 
-// N-point DFT of which only the samples n < NV are read (N = 8, 16).
+// N-point DFT of which only the samples n < NV are read (N = 8, 16); hi as in
+// dft8.
 template <int N, int CTX, int NV = N>
-SFOC_DEV void dftn(float2 (&x)[N]) {
+SFOC_DEV void dftn(float2 (&x)[N], bool hi = false) {
     static_assert(NV == N || N == 8 || N == 16, "leading samples");
-    if constexpr (N == 8) dft8<CTX, NV>(x);
+    if constexpr (N == 8) dft8<CTX, NV>(x, hi);
     else if constexpr (N == 10) dft10<CTX>(x);
     else if constexpr (N == 12) dft12<CTX>(x);
     else dft16<CTX, NV>(x);
@@ -540,7 +556,8 @@ SFOC_DEV void row_pass_a(const void* __restrict__ plane, int pitch, int y0, int 
     };
     auto finish = [&](int p, int n1, float2(&x)[C::NA]) {
         if constexpr (SUMS) add_pair<NV>(x, s1, s2);
-        dftn<C::NA, DT == 2 ? kFwdF16 : kFwd, NV>(x);
+        constexpr int CTX = DT == 2 ? kFwdF16 : DT == 1 && C::NA == 8 && !SUMS ? kFwdBf16A8 : kFwd;
+        dftn<C::NA, CTX, NV>(x, tid >= C::NT / 2);
         float2* reg = buf + C::row(2 * p);
         const float2* w = tw + n1;
 #pragma unroll
@@ -644,7 +661,7 @@ SFOC_DEV void col_pass_a(float2* buf, const float2* tw, int nvalid) {
         }
     };
     auto finish = [&](int cc, int n1, float2(&x)[C::NA]) {
-        dftn<C::NA, INV ? (C::NA == 8 ? kInvColA8 : kInvCol) : kFwd, NV>(x);
+        dftn<C::NA, INV ? (C::NA == 8 ? kInvColA8 : kInvCol) : kFwd, NV>(x, tid >= C::NT / 2);
         float2* b = buf + C::rowg(n1, 0) + cc;
         const float2* tb = tw + n1;
 #pragma unroll
