@@ -304,7 +304,7 @@ __device__ __forceinline__ void load_region(const DescribeJob& J, int y0, int x0
 struct RunOut {
     int64_t plane, off0;
     int gy, gx0, W;
-    bool row, full;    // the row lies in the image; the run can be one vector
+    bool row, full;    // the run has a pixel in the image; it can be one vector
     double d1[kRun], d2[kRun];
 };
 __device__ __forceinline__ void init_run(RunOut& O, const DescribeJob& J, const DescribeConsts& C, int ty0, int tx0) {
@@ -316,14 +316,71 @@ __device__ __forceinline__ void init_run(RunOut& O, const DescribeJob& J, const 
     const size_t align = C.dtype == SFOC_DTYPE_F32 ? 15 : 7;
     O.full = (J.W & (kRun - 1)) == 0 && (O.gx0 & (kRun - 1)) == 0 && ((uintptr_t)J.desc & align) == 0 &&
              O.gx0 + kRun <= J.W;
-    O.row = O.gy < J.H;
+    O.row = O.gy < J.H && O.gx0 < J.W;
     O.off0 = (int64_t)O.gy * J.W + O.gx0;
 #pragma unroll
     for (int j = 0; j < kRun; ++j) O.d1[j] = O.d2[j] = 0.0;
 }
 
+// Channels [lo, hi) of acc, normalised, rounded to type DT and stored in a form
+// (kEdge, kWhole, kVector: the run reaches past the row's end, all of it lies in the
+// image, it is one vector), and their channel sums.
+enum { kEdge, kWhole, kVector };
+template <int Z, int DT, int FORM>
+__device__ __forceinline__ void emit_channels(const float (&acc)[Z][kRun], const float (&inv)[kRun], int lo, int hi,
+                                              int c0, void* __restrict__ desc, bool sums, RunOut& O) {
+#pragma unroll
+    for (int c = 0; c < Z; ++c) {
+        if (c < lo || c >= hi) continue;
+        float v[kRun];
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) {
+            v[j] = acc[c][j] * inv[j];
+            // (rounded to float32 first: the compiler would fuse the conversion, for
+            // the store or for the sums alone)
+            if (DT == SFOC_DTYPE_F16) asm("" : "+v"(v[j]));
+        }
+        if constexpr (DT == SFOC_DTYPE_F32) {
+            float* dst = (float*)desc + (c0 + c) * O.plane + O.off0;
+            if constexpr (FORM == kVector) {
+                *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kRun; ++j)
+                    if (FORM == kWhole || O.gx0 + j < O.W) dst[j] = v[j];
+            }
+        } else {
+            uint16_t q[kRun];
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) {
+                q[j] = DT == SFOC_DTYPE_BF16 ? f32_to_bf16_bits(v[j]) : f32_to_f16_bits(v[j]);
+                v[j] = DT == SFOC_DTYPE_BF16 ? bf16_bits_to_f32(q[j]) : f16_bits_to_f32(q[j]);
+            }
+            uint16_t* dst = (uint16_t*)desc + (c0 + c) * O.plane + O.off0;
+            if constexpr (FORM == kVector) {
+                *(ushort4*)dst = make_ushort4(q[0], q[1], q[2], q[3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kRun; ++j)
+                    if (FORM == kWhole || O.gx0 + j < O.W) dst[j] = q[j];
+            }
+        }
+        if (sums) {
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) {
+                const double dv = (double)v[j];
+                O.d1[j] += dv;
+                O.d2[j] = fma(dv, dv, O.d2[j]);
+            }
+        }
+    }
+}
+
 // One order block, channels [lo, hi) of acc: normalisation, rounding, store
-// (channel c goes to plane c0 + c), channel sums.
+// (channel c goes to plane c0 + c), channel sums.  Type and form are chosen once
+// and not per channel, where their branches cost more than the stores: 2048 x 2048,
+// FP16, without integrals 151 us with them inside, 144 us so; 2045 x 2047, FP32,
+// whose runs check every pixel against the row's end there, 176 and 152 us.
 template <int Z>
 __device__ __forceinline__ void emit_block(const float (&acc)[Z][kRun], int lo, int hi, int c0, void* __restrict__ desc, bool sums,
                          const DescribeConsts& C, RunOut& O) {
@@ -337,46 +394,15 @@ __device__ __forceinline__ void emit_block(const float (&acc)[Z][kRun], int lo, 
         inv[j] = rsqrtf(s2 + C.eps);
     }
     if (!O.row) return;
-#pragma unroll
-    for (int c = 0; c < Z; ++c) {
-        if (c < lo || c >= hi) continue;
-        float v[kRun];
-#pragma unroll
-        for (int j = 0; j < kRun; ++j) v[j] = acc[c][j] * inv[j];
-        if (C.dtype == SFOC_DTYPE_F32) {
-            float* dst = (float*)desc + (c0 + c) * O.plane + O.off0;
-            if (O.full) {
-                *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < kRun; ++j)
-                    if (O.gx0 + j < O.W) dst[j] = v[j];
-            }
-        } else {
-            uint16_t q[kRun];
-#pragma unroll
-            for (int j = 0; j < kRun; ++j) {
-                q[j] = C.dtype == SFOC_DTYPE_BF16 ? f32_to_bf16_bits(v[j]) : f32_to_f16_bits(v[j]);
-                v[j] = C.dtype == SFOC_DTYPE_BF16 ? bf16_bits_to_f32(q[j]) : f16_bits_to_f32(q[j]);
-            }
-            uint16_t* dst = (uint16_t*)desc + (c0 + c) * O.plane + O.off0;
-            if (O.full) {
-                *(ushort4*)dst = make_ushort4(q[0], q[1], q[2], q[3]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < kRun; ++j)
-                    if (O.gx0 + j < O.W) dst[j] = q[j];
-            }
-        }
-        if (sums) {
-#pragma unroll
-            for (int j = 0; j < kRun; ++j) {
-                const double dv = (double)v[j];
-                O.d1[j] += dv;
-                O.d2[j] = fma(dv, dv, O.d2[j]);
-            }
-        }
-    }
+    auto emit = [&](auto dt) {
+        constexpr int DT = decltype(dt)::value;
+        if (O.full) emit_channels<Z, DT, kVector>(acc, inv, lo, hi, c0, desc, sums, O);
+        else if (O.gx0 + kRun <= O.W) emit_channels<Z, DT, kWhole>(acc, inv, lo, hi, c0, desc, sums, O);
+        else emit_channels<Z, DT, kEdge>(acc, inv, lo, hi, c0, desc, sums, O);
+    };
+    if (C.dtype == SFOC_DTYPE_F32) emit(std::integral_constant<int, SFOC_DTYPE_F32>{});
+    else if (C.dtype == SFOC_DTYPE_BF16) emit(std::integral_constant<int, SFOC_DTYPE_BF16>{});
+    else emit(std::integral_constant<int, SFOC_DTYPE_F16>{});
 }
 
 // Per-pixel channel sums of the stored values (zero outside the image) into
@@ -745,7 +771,7 @@ __device__ __forceinline__ void sigma_pass_use(const float* simg, int IPP, float
 // R = 9, 128 VGPRs for N <= 8).
 // 2048 x 2048, FP32 with integral inputs: 250 us with the basis read from LDS
 // by a loop over map elements (23 issue slots a channel and element), runs of
-// four rows and two or four row-pass phases a sigma; 188 us so (86.0 M wave
+// four rows and two or four row-pass phases a sigma; 185 us so (85.0 M wave
 // instructions, three quarters of the issue slots).
 // The arguments are read where the launch put them: as a by-value parameter
 // with this many readers the compiler would copy them to scratch memory.
